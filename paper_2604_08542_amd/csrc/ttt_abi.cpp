@@ -109,7 +109,7 @@ LargeLayout large_layout(const Shape& s) {
   L.W2 = take(d * h * 4);
   L.W1op = take(d * h * op);
   L.W2op = take(d * h * op);
-  L.loss_part = take((d / 128) * ((M + 127) / 128) * 4);
+  L.loss_part = take(std::max((d / 128) * ((M + 127) / 128), SUM_PARTS) * 4);
   L.total = off;
   return L;
 }
@@ -119,7 +119,7 @@ LargeLayout large_layout(const Shape& s) {
 // reverse step's buffers.
 struct LargeBwdLayout {
   LargeLayout f;
-  size_t dOn, dY, dq, dk, dv, dE, S2, P, Sq1, dZq, dP, dZa, EWh, dZ, W1nop, W2nop, Wh1, Wh2, Wh1op, Wh2op, tot1, tot2,
+  size_t dOn, dY, dq, dk, dv, dE, S2, P, Dn, Sq1, dZq, dP, dZa, EWh, dZ, W1nop, W2nop, Wh1, Wh2, Wh1op, Wh2op, tot1, tot2,
       deta_part, deta, total;
 };
 LargeBwdLayout large_bwd_layout(const Shape& s) {
@@ -141,11 +141,12 @@ LargeBwdLayout large_bwd_layout(const Shape& s) {
   L.dE = take(M * d * 4);
   L.S2 = take((M + 127) / 128 * 128 * h * op);  // tile-native
   L.P = take((M + 127) / 128 * 128 * h * op);  // tile-native
+  L.Dn = take(s.mma_bf16 ? (M + 127) / 128 * 128 * h * op : 0);  // tile-native
   L.Sq1 = take((M + 127) / 128 * 128 * h * op);  // tile-native
   L.dZq = take(M * h * op);
   L.dP = take(M * h * op);
   L.dZa = take((M + 127) / 128 * 128 * h * op);  // tile-native
-  L.EWh = take(M * h * op);
+  L.EWh = take((M + 127) / 128 * 128 * h * op);  // tile-native with BF16 products
   L.dZ = take(M * h * op);
   L.W1nop = take(d * h * op);
   L.W2nop = take(d * h * op);
@@ -155,7 +156,7 @@ LargeBwdLayout large_bwd_layout(const Shape& s) {
   L.Wh2op = take(d * h * op);
   L.tot1 = take(d * h * 4);  // GCS: the adjoint of W0 (the apply adjoint plus every chunk's update terms)
   L.tot2 = take(d * h * 4);
-  L.deta_part = take((d / 128 + h / 128) * ((M + 127) / 128) * 4);
+  L.deta_part = take(std::max((d / 128 + h / 128) * ((M + 127) / 128), 2 * SUM_PARTS) * 4);
   L.deta = take(4);
   L.total = off;
   return L;
@@ -1032,7 +1033,7 @@ LargeBwdArgs large_bwd_args(const ttt_problem_t* p, const Shape& S, const LargeB
   b.Vn = at<float>(ws, L.f.Vn); b.dq = at<float>(ws, L.dq); b.dk = at<float>(ws, L.dk);
   b.dv = at<float>(ws, L.dv); b.dE = at<float>(ws, L.dE);
   b.A = at<char>(ws, L.f.A); b.S1 = at<char>(ws, L.f.S1); b.S2 = at<char>(ws, L.S2); b.P = at<char>(ws, L.P);
-  b.D = at<char>(ws, L.f.D); b.Aq = at<char>(ws, L.f.Aq); b.Sq1 = at<char>(ws, L.Sq1);
+  b.D = at<char>(ws, L.f.D); b.Dn = at<char>(ws, L.Dn); b.Aq = at<char>(ws, L.f.Aq); b.Sq1 = at<char>(ws, L.Sq1);
   b.dZq = at<char>(ws, L.dZq); b.dP = at<char>(ws, L.dP); b.dZa = at<char>(ws, L.dZa);
   b.EWh = at<char>(ws, L.EWh); b.dZ = at<char>(ws, L.dZ);
   b.W1op = at<char>(ws, L.f.W1op); b.W2op = at<char>(ws, L.f.W2op);

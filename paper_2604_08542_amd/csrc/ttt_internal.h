@@ -10,6 +10,9 @@ namespace ttt {
 // Chunk step at large state sizes (d >= 256): the chunk's rows are read from
 // the token tensors (head offset applied), every product is a GEMM over
 // operands streamed from HBM.
+// BF16 products: a launch has at most 256 work-groups of 8 waves; its scalar
+// sums have one partial per wave.
+constexpr size_t SUM_PARTS = 256 * 8;
 struct LargeNormArgs {
   const void* K;
   const void* V;
@@ -46,9 +49,11 @@ struct LargeStepArgs {
   float* W2;
   void* W1op;     // operand copies of the masters
   void* W2op;
-  float* loss_part;  // [d/128 * ceil(rows/128)]
+  float* loss_part;  // [max(d/128 * ceil(rows/128), SUM_PARTS)]
   float* loss;       // nullable: the chunk's loss
 };
+// (BF16 products: ttt_large_bf.hip, ttt_large_bwd_bf.hip)
+hipError_t launch_large_step_bf(const LargeStepArgs& a, bool io_bf16, hipStream_t st);
 hipError_t launch_large_step(const LargeStepArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st);
 // Reverse step of one chunk of the MSE unit at large state sizes (the apply
 // adjoint at W_{c+1}, then the update adjoint at W_c along the carried
@@ -80,6 +85,7 @@ struct LargeBwdArgs {
   void* S2;
   void* P;
   void* D;
+  void* Dn;       // BF16 products: D again, tile-native
   void* Aq;
   void* Sq1;
   void* dZq;
@@ -101,9 +107,10 @@ struct LargeBwdArgs {
   void* Acc2op;
   int32_t apply;      // 1: the apply adjoint of the chunk (dQ written)
   int32_t update;     // 1: the update adjoint of the chunk (dK, dV written)
-  float* deta_part;   // per-tile partials of the step-size derivative
+  float* deta_part;   // per-tile (BF16 products: per-wave, two launches) partials of the step-size derivative
   float* deta;        // this head's running d/d eta (one float)
 };
+hipError_t launch_large_bwd_step_bf(const LargeBwdArgs& a, bool io_bf16, hipStream_t st);
 hipError_t launch_large_bwd_step(const LargeBwdArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st);
 // Reverse step of one chunk of the paper's memory unit at large state sizes
 // (apply adjoint at W' = W_{c+1} and/or update adjoint at W = W_c along the
@@ -153,6 +160,7 @@ struct LargeAmuBwdArgs {
   float* Acc[3];        // where the update adjoint's weight terms go, and
   void* Accop[3];       // their operand copies (nullable)
 };
+hipError_t launch_large_amu_bwd_step_bf(const LargeAmuBwdArgs& a, bool io_bf16, hipStream_t st);
 hipError_t launch_large_amu_bwd_step(const LargeAmuBwdArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st);
 // Fill n floats with zero.
 hipError_t launch_large_zero(float* p, int64_t n, hipStream_t st);
@@ -189,6 +197,7 @@ struct LargeAmuArgs {
   void* W2op;
   void* W3op;
 };
+hipError_t launch_large_amu_step_bf(const LargeAmuArgs& a, bool io_bf16, hipStream_t st);
 hipError_t launch_large_amu_step(const LargeAmuArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st);
 // Operand copy (BF16 or FP32) of n FP32 values.
 hipError_t launch_large_cast(const float* src, void* dst, int64_t n, bool mma_bf16, hipStream_t st);

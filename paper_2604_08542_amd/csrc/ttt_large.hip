@@ -447,7 +447,7 @@ hipError_t init_t(const float* w1, const float* w2, float* m1, float* m2, void* 
 
 hipError_t launch_large_step(const LargeStepArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st) {
   using namespace large;
-  if (mma_bf16) return io_bf16 ? step_t<bf16, bf16>(a, st) : step_t<bf16, float>(a, st);
+  if (mma_bf16) return launch_large_step_bf(a, io_bf16, st);
   return step_t<float, float>(a, st);
 }
 
@@ -467,7 +467,7 @@ hipError_t launch_large_norm(const LargeNormArgs& a, bool io_bf16, bool mma_bf16
 
 hipError_t launch_large_amu_step(const LargeAmuArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st) {
   using namespace large;
-  if (mma_bf16) return io_bf16 ? amu_step_t<bf16, bf16>(a, st) : amu_step_t<bf16, float>(a, st);
+  if (mma_bf16) return launch_large_amu_step_bf(a, io_bf16, st);
   return amu_step_t<float, float>(a, st);
 }
 

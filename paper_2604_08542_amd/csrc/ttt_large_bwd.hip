@@ -828,13 +828,13 @@ hipError_t step_t(const LargeAmuBwdArgs& a, hipStream_t st) {
 
 hipError_t launch_large_bwd_step(const LargeBwdArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st) {
   using namespace large::bwd;
-  if (mma_bf16) return io_bf16 ? step_t<bf16, bf16>(a, st) : step_t<bf16, float>(a, st);
+  if (mma_bf16) return launch_large_bwd_step_bf(a, io_bf16, st);
   return step_t<float, float>(a, st);
 }
 
 hipError_t launch_large_amu_bwd_step(const LargeAmuBwdArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st) {
   using namespace large::bwd;
-  if (mma_bf16) return io_bf16 ? amu::step_t<bf16, bf16>(a, st) : amu::step_t<bf16, float>(a, st);
+  if (mma_bf16) return launch_large_amu_bwd_step_bf(a, io_bf16, st);
   return amu::step_t<float, float>(a, st);
 }
 
