@@ -2062,7 +2062,7 @@ ttt_status_t ttt_gcm_fwd(const ttt_problem_t* p, const void* X, const void* Wqkv
 // the projection P [N][3D] (Q, K, V at column offsets 0, D, 2D, token pitch
 // 3D), so its problem is the layer's with that pitch.
 struct GcmBwdLayout {
-  size_t P, O, dO, dP, dG, G, part, ckpt, unit, total;
+  size_t P, O, dO, dP, dG, G, part, wpart, ckpt, unit, total;
   ttt_problem_t pu;
 };
 static ttt_status_t gcm_bwd_layout(const ttt_problem_t* p, GcmBwdLayout* L) {
@@ -2093,8 +2093,10 @@ static ttt_status_t gcm_bwd_layout(const ttt_problem_t* p, GcmBwdLayout* L) {
   L->dO = take((size_t)N * 3 * D * io);
   L->dP = take((size_t)N * 3 * D * io);
   L->dG = take((size_t)N * D * io);
-  L->G = take((size_t)N * D * 4);
-  L->part = take((size_t)((N + 255) / 256) * 3 * D * 4);
+  L->G = take(S.io_bf16 ? 0 : (size_t)N * D * 4);
+  const size_t runs_o = gcm_runs(D, D, N), runs_p = gcm_runs(D, 3 * D, N);  // the BF16 form's weight gradients
+  L->part = take(std::max((size_t)((N + 255) / 256) * 3 * D, S.io_bf16 ? gcm_part_floats(N, D) : 0) * 4);
+  L->wpart = take(S.io_bf16 ? std::max(runs_o > 1 ? runs_o : 0, runs_p > 1 ? 3 * runs_p : 0) * D * D * 4 : 0);
   L->ckpt = take((size_t)C * S.H * 2 * S.dh() * 4);
   L->unit = take(ub);
   L->total = off;
@@ -2143,7 +2145,7 @@ ttt_status_t ttt_gcm_bwd(const ttt_problem_t* p, const void* X, const void* Wqkv
     a.D = (int32_t)D; a.rows = N;
     a.X = X; a.Wqkv = Wqkv; a.bqkv = bqkv; a.Wo = Wo; a.bo = bo; a.alpha = alpha; a.dY = dY;
     a.P = b + L.P; a.O = b + L.O; a.G = reinterpret_cast<float*>(b + L.G); a.dG = b + L.dG; a.dO = b + L.dO;
-    a.dP = b + L.dP; a.part = reinterpret_cast<float*>(b + L.part);
+    a.dP = b + L.dP; a.part = reinterpret_cast<float*>(b + L.part); a.wpart = reinterpret_cast<float*>(b + L.wpart);
     a.dX = dX; a.dWqkv = dWqkv; a.dbqkv = dbqkv; a.dWo = dWo; a.dbo = dbo; a.dalpha = dalpha;
     // the projection, then the unit's forward with its checkpoints
     a.phase = 0;

@@ -208,11 +208,11 @@ hipError_t gcm_bwd_t(const GcmBwdArgs& a, hipStream_t st) {
 }  // namespace large
 
 hipError_t launch_gcm_gemm(const GcmGemmArgs& a, bool io_bf16, hipStream_t st) {
-  return io_bf16 ? large::gcm_t<bf16>(a, st) : large::gcm_t<float>(a, st);
+  return io_bf16 ? launch_gcm_gemm_bf(a, st) : large::gcm_t<float>(a, st);
 }
 
 hipError_t launch_gcm_bwd(const GcmBwdArgs& a, bool io_bf16, hipStream_t st) {
-  return io_bf16 ? large::gcm_bwd_t<bf16>(a, st) : large::gcm_bwd_t<float>(a, st);
+  return io_bf16 ? launch_gcm_bwd_bf(a, st) : large::gcm_bwd_t<float>(a, st);
 }
 
 }  // namespace ttt

@@ -1,9 +1,9 @@
-// Matrix-core GEMM tiles for gfx950 shared by the large-state chunk step and
-// the surrounding layer's projections: C[m][n] = sum_k A(m, k) B(k, n) over
-// BF16 (32x32x16 products) or FP32 (32x32x2) operands in their natural
-// layouts, a work-group owning one BM x 128 tile of C and its whole
-// contraction (fixed order, deterministic), the elementwise work of the
-// caller fused into an epilogue functor.
+// FP32 matrix-core GEMM tiles for gfx950 shared by the large-state chunk step
+// and the surrounding layer's projections: C[m][n] = sum_k A(m, k) B(k, n) as
+// 32x32x2 products over operands in their natural layouts, a work-group owning
+// one BM x 128 tile of C and its whole contraction (fixed order,
+// deterministic), the elementwise work of the caller fused into an epilogue
+// functor.  (BF16 products: ttt_gemm_bf.h.)
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -26,9 +26,8 @@ __device__ __forceinline__ void put(T* p, float v) {
 
 // Epilogues derive from this.  An epilogue that reads an input per element
 // (a factor, a residual target, the FP32 master) defines In and load(r, c);
-// the tile calls load for 16 elements (BF16 tiles with a small input: for all
-// of its elements) before it calls operator() for any of them, so those
-// reads are in flight together instead of each waiting behind the previous
+// the tile calls load for 16 elements before it calls operator() for any of
+// them, so those reads are in flight together instead of each waiting behind the previous
 // element's store.  finish() runs once per work-group after its last element.
 //
 // An epilogue with TILED = true instead takes each 32x32 block whole:
@@ -56,10 +55,11 @@ struct is_tiled<E, std::void_t<decltype(E::TILED)>> : std::bool_constant<E::TILE
 
 constexpr int BN = 128;   // work-group tile width
 constexpr int NTH = 256;  // 4 waves, each a (BM/2) x 64 quarter of the BM x 128 tile
-// contraction slice per LDS stage: 64 BF16 or 32 FP32 elements (128 bytes)
+// contraction slice per LDS stage
 template <typename T>
 constexpr int bk() {
-  return sizeof(T) == 2 ? 64 : 32;
+  static_assert(sizeof(T) == 4, "FP32 products");
+  return 32;
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -91,26 +91,15 @@ struct Native16 {
 //   MNMAJ the operand is stored [k][m or n] (m or n contiguous), pitch ld
 enum { KMAJ = 0, MNMAJ = 1 };
 
-// LDS tile of ROWS rows (m or n) by BK (contraction).  BF16 operands feed
-// 32x32x16 products: a lane's 8 contraction slots hold, for lane half hf and
-// product step j, k = 16j + 8hf + {0..7}, so a k-major fragment is one
-// 16-byte LDS read and an mn-major one two transposing reads of four rows
-// each; both operands use this order, so a k-major and an mn-major operand
-// can be mixed.  FP32 operands feed 32x32x2 products, lane (l32, hf) holding
-// k = 2j + hf.
-//
-// Pitches (in 4-byte LDS banks): a k-major BF16 row is 36 banks (16-byte
-// aligned), so the 16-byte reads of 8 lanes from 8 consecutive rows start 4
-// banks apart mod 32 and cover the banks once; an mn-major BF16 row is 72
-// banks (8 mod 32), so the four rows of 32 bytes that a 16-lane group of the
-// transposing read touches fall on disjoint banks.  FP32: 33 banks (k-major,
-// 4-byte reads down a column), 132 (mn-major, consecutive lanes on
+// LDS tile of ROWS rows (m or n) by BK (contraction), feeding 32x32x2 products
+// with lane (l32, hf) holding k = 2j + hf.  Pitches (in 4-byte LDS banks): 33
+// (k-major, 4-byte reads down a column), 132 (mn-major, consecutive lanes on
 // consecutive banks).
 template <typename T, int ROWS>
 struct Tile {
   static constexpr int BK = bk<T>();
-  static constexpr int KLD = sizeof(T) == 2 ? BK + 8 : BK + 1;       // pitch of a k-major tile [ROWS][BK]
-  static constexpr int MLD = sizeof(T) == 2 ? ROWS + 16 : ROWS + 4;  // pitch of an mn-major tile [BK][ROWS]
+  static constexpr int KLD = BK + 1;    // pitch of a k-major tile [ROWS][BK]
+  static constexpr int MLD = ROWS + 4;  // pitch of an mn-major tile [BK][ROWS]
   static constexpr int ELEMS = ROWS * KLD > BK * MLD ? ROWS * KLD : BK * MLD;
 };
 
@@ -168,9 +157,7 @@ struct Stage {
       }
       if constexpr (LAYOUT == MNMAJ) {
         *reinterpret_cast<u32x4*>(lds + off) = r[i];
-      } else if constexpr (sizeof(T) == 2) {  // k-major BF16 rows are 16-byte aligned
-        *reinterpret_cast<u32x4*>(lds + off) = r[i];
-      } else {  // FP32 k-major rows have an odd pitch: four 4-byte stores
+      } else {  // k-major rows have an odd pitch: four 4-byte stores
         const u32x4 v = r[i];
 #pragma unroll
         for (int e = 0; e < 4; ++e) reinterpret_cast<uint32_t*>(lds + off)[e] = v[e];
@@ -185,35 +172,16 @@ template <typename T, int LAYOUT, int ROWS>
 __device__ __forceinline__ auto frag(const T* t, int mn, int j) {
   const int l = threadIdx.x & 63, l32 = l & 31, hf = l >> 5;
   using TL = Tile<T, ROWS>;
-  if constexpr (sizeof(T) == 2) {
-    typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-    if constexpr (LAYOUT == KMAJ) {
-      return *reinterpret_cast<const bf16x8*>(t + (mn + l32) * TL::KLD + 16 * j + 8 * hf);
-    } else {
-      // transposing read: in each 16-lane group lane i addresses row
-      // t0 + i/4, columns c0 + 4(i%4)..+3 and receives T[t0 + q][c0 + i], q < 4;
-      // rows 8hf..8hf+3, then 8hf+4..8hf+7
-      const int l16 = l & 15;
-      const int off = (8 * hf + (l16 >> 2)) * TL::MLD + mn + 16 * ((l >> 4) & 1) + 4 * (l16 & 3);
-      const bf16* p0 = t + off + 16 * j * TL::MLD;
-      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-          (lds_bf16x4*)((__attribute__((address_space(3))) bf16*)(p0)));
-      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-          (lds_bf16x4*)((__attribute__((address_space(3))) bf16*)(p0 + 4 * TL::MLD)));
-      return (bf16x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    }
-  } else {
-    if constexpr (LAYOUT == KMAJ)
-      return t[(mn + l32) * TL::KLD + 2 * j + hf];
-    else
-      return t[(2 * j + hf) * TL::MLD + mn + l32];
-  }
+  if constexpr (LAYOUT == KMAJ)
+    return t[(mn + l32) * TL::KLD + 2 * j + hf];
+  else
+    return t[(2 * j + hf) * TL::MLD + mn + l32];
 }
 
 // Product steps per contraction slice.
 template <typename T>
 constexpr int ksteps() {
-  return sizeof(T) == 2 ? bk<T>() / 16 : bk<T>() / 2;
+  return bk<T>() / 2;
 }
 
 // C tile (this work-group's BM x 128) accumulated over the whole
@@ -309,25 +277,6 @@ __device__ __forceinline__ void gemm_tile(const T* A, int lda, int a_rows, const
 #pragma unroll
       for (int bn = 0; bn < 2; ++bn)
         ep.block(blk0 + 2 * bm + bn, m0 + wm + 32 * bm, n0 + wn + 32 * bn + l32, acc[bm][bn], tin[bm][bn]);
-  } else if constexpr (sizeof(T) == 2 && sizeof(typename EP::In) <= 4) {
-    // BF16 tiles with at most one 4-byte input per element request every
-    // input of the tile before the first element is stored (one load latency
-    // per tile, not one per 32x32 block); the registers fit beside the
-    // accumulators at two waves per SIMD
-    typename EP::In in[MB][2][16];
-#pragma unroll
-    for (int bm = 0; bm < MB; ++bm)
-#pragma unroll
-      for (int bn = 0; bn < 2; ++bn)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) in[bm][bn][r] = ep.load(m0 + wm + 32 * bm + c32_row(r, hf), n0 + wn + 32 * bn + l32);
-#pragma unroll
-    for (int bm = 0; bm < MB; ++bm)
-#pragma unroll
-      for (int bn = 0; bn < 2; ++bn)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          ep(m0 + wm + 32 * bm + c32_row(r, hf), n0 + wn + 32 * bn + l32, acc[bm][bn][r], in[bm][bn][r]);
   } else {
 #pragma unroll
     for (int bm = 0; bm < MB; ++bm)

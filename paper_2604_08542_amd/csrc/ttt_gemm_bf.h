@@ -577,10 +577,10 @@ __global__ __launch_bounds__(NTHR) void k_wgrad(WArgs a) {
   __shared__ __attribute__((aligned(1024))) char sm[MC::LDS];
   MC mc;
   mc.init(sm);
-  const int nks = (a.tokens + KS - 1) / KS, run = (nks + a.nsplit - 1) / a.nsplit;
-  // a tile of the launch: weight p, run of tokens, tile of the weight
+  const int nks = (a.tokens + KS - 1) / KS;
+  // a tile of the launch: weight p, run r of tokens (nk slices from k0 on), tile of the weight
   struct Pos {
-    int p, r, im, in, nk;
+    int p, r, im, in, k0, nk;
   };
   auto tiles_of = [&](int p) { return (a.p[p].M / TL::BM) * (a.p[p].N / TL::BN); };
   auto locate = [&](int t) {
@@ -591,7 +591,8 @@ __global__ __launch_bounds__(NTHR) void k_wgrad(WArgs a) {
     o.p = p;
     o.r = t / n;
     tile_at(t - o.r * n, a.p[p].M / TL::BM, a.p[p].N / TL::BN, o.im, o.in);
-    o.nk = min(run, nks - o.r * run);
+    o.k0 = __builtin_amdgcn_readfirstlane(o.r * nks / a.nsplit);
+    o.nk = __builtin_amdgcn_readfirstlane((o.r + 1) * nks / a.nsplit) - o.k0;
     return o;
   };
   int total = 0, first, count;
@@ -613,7 +614,7 @@ __global__ __launch_bounds__(NTHR) void k_wgrad(WArgs a) {
     mc.tile(w.lda, w.ldb, lp.im * TL::BM, lp.in * TL::BN);
   };
   auto load_next = [&](int slot) {  // past the last slice: the last tile's first slices again, never used
-    const int k = lp.r * run + lk;
+    const int k = lp.k0 + lk;
     mc.load(ra, rb, k * ka, k * kb, slot);
     if (++lk == lp.nk) {
       lk = 0;
@@ -681,7 +682,7 @@ inline void add_weight(WArgs& a, const bf16* A, int lda, const bf16* B, int ldb,
 // Tiles by the rounds of the launch and the measured rate of a work-group
 // (per CU, 256 x 256: 5.2 TFLOP/s, 128 x 256: 4.2, 128 x 128: 2.9).
 inline void wgrad(WArgs a, hipStream_t st) {
-  if (a.nsplit < 1) a.nsplit = 1;
+  a.nsplit = std::max(1, std::min(a.nsplit, (a.tokens + KS - 1) / KS));
   struct {
     int bm, bn;
     double rate;

@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "../../include/ttt.h"
 #include "ttt_amu.h"
 #include "ttt_common.h"
@@ -24,8 +26,8 @@ struct LargeNormArgs {
   float* Vn;
   void* Qn;
 };
-// Row normalisation of a large-state chunk (K, V, Q; the flags select which).
-hipError_t launch_large_norm(const LargeNormArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st);
+// Row normalisation of a large-state chunk (K, V, Q; the flags select which), FP32.
+hipError_t launch_large_norm(const LargeNormArgs& a, hipStream_t st);
 struct LargeStepArgs {
   const void* K;  // first token of the chunk, head offset applied
   const void* V;
@@ -43,7 +45,7 @@ struct LargeStepArgs {
   void* A;        // [rows][h] operand type
   void* D;
   void* Aq;
-  float* Vn;      // [rows][d] FP32
+  float* Vn;      // [rows][d] FP32 (BF16 products: [rows], V's normalisation factors)
   void* S1;       // operand type: SiLU'(Z), tile-native (whole 128-row tiles) in the forward step
   float* W1;      // FP32 masters [d][h], [h][d], updated in place
   float* W2;
@@ -75,7 +77,7 @@ struct LargeBwdArgs {
   void* E;
   void* dOn;
   void* dY;
-  float* Vn;      // [rows][d] FP32
+  float* Vn;      // [rows][d] FP32 (BF16 products: [rows], V's normalisation factors)
   float* dq;
   float* dk;
   float* dv;
@@ -134,7 +136,7 @@ struct LargeAmuBwdArgs {
   void* Qn;
   void* E;
   void* dOn;
-  float* Vn;     // [rows][d] FP32
+  float* Vn;     // [rows][d] FP32 (BF16 products: [rows])
   float* Ydot;
   float* dq;
   float* dk;
@@ -183,7 +185,7 @@ struct LargeAmuArgs {
   void* Kn;          // [rows][d] operand type
   void* Qn;
   void* E;
-  float* Vn;         // [rows][d] FP32
+  float* Vn;         // [rows][d] FP32 (BF16 products: [rows])
   void* Z3;          // [rows][h] operand type: x W3
   void* Hd;          // SiLU(x W1) * (x W3)
   void* G1;          // Z3 * SiLU'(Z1)
@@ -239,11 +241,12 @@ struct GcmBwdArgs {
   const void* dY;
   void* P;             // [N][3D]
   void* O;             // [N][3D], the first D columns used
-  float* G;            // [N][D]
+  float* G;            // [N][D] (FP32 form only)
   void* dG;            // [N][D]
   void* dO;            // [N][3D], the first D columns used
   const void* dP;      // [N][3D]
-  float* part;         // column partial sums [ceil(N / 256)][3D]
+  float* part;         // column partial sums: FP32 form [ceil(N / 256)][3D], BF16 form gcm_part_floats
+  float* wpart;        // BF16 form: the runs' sums of a weight gradient
   void* dX;
   float* dWqkv;        // [D][3D]
   float* dbqkv;        // [3D], nullable
@@ -251,6 +254,17 @@ struct GcmBwdArgs {
   float* dbo;          // [D], nullable
   float* dalpha;       // [D]
 };
+// (BF16 form: ttt_gcm_bf.hip)
+hipError_t launch_gcm_gemm_bf(const GcmGemmArgs& a, hipStream_t st);
+hipError_t launch_gcm_bwd_bf(const GcmBwdArgs& a, hipStream_t st);
+// Runs that the tokens of an M x N weight gradient are cut into (a work-group
+// per 256 x 256 or, where those do not divide it, 128 x 128 tile and run; at
+// least 512 tokens per run, at most 32 runs).
+inline int gcm_runs(int64_t M, int64_t N, int64_t tokens) {
+  const int64_t t = M % 256 == 0 && N % 256 == 0 ? 256 : 128, tiles = (M / t) * (N / t);
+  return (int)std::max<int64_t>(1, std::min<int64_t>({256 / tiles, tokens / 512, 32}));
+}
+inline size_t gcm_part_floats(int64_t tokens, int64_t D) { return (size_t)((tokens + 31) / 32) * 2 * D; }
 hipError_t launch_gcm_bwd(const GcmBwdArgs& a, bool io_bf16, hipStream_t st);
 hipError_t launch_large_init(const float* w1, const float* w2, float* m1, float* m2, void* o1, void* o2, int64_t n,
                              bool mma_bf16, hipStream_t st);

@@ -23,8 +23,8 @@
 //   dH     dH = E W2^T        -> D1 = dH G1, D3 = dH G3
 //   gW     W1 -= K^T D1, W3 -= K^T D3, W2 -= Hd^T E
 //   apply  Zq3 = Q W3', Hq = SiLU(Q W1') Zq3, O = Hq W2'
-// The masters stay FP32; the matrix-core operands are BF16 copies (or FP32
-// with FP32 matrix cores).  Each output element of every product is owned by
+// This file holds the FP32 form (BF16 products: ttt_large_bf.hip).  The masters
+// and operands are FP32.  Each output element of every product is owned by
 // one work-group, which sums its whole contraction in a fixed order, so the
 // result is deterministic.
 #include <hip/hip_runtime.h>
@@ -451,17 +451,8 @@ hipError_t launch_large_step(const LargeStepArgs& a, bool io_bf16, bool mma_bf16
   return step_t<float, float>(a, st);
 }
 
-hipError_t launch_large_norm(const LargeNormArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st) {
-  using namespace large;
-  const dim3 grid((a.rows + 3) / 4);
-  if (mma_bf16) {
-    if (io_bf16)
-      hipLaunchKernelGGL((k_norm<bf16, bf16>), grid, dim3(256), 0, st, a);
-    else
-      hipLaunchKernelGGL((k_norm<float, bf16>), grid, dim3(256), 0, st, a);
-  } else {
-    hipLaunchKernelGGL((k_norm<float, float>), grid, dim3(256), 0, st, a);
-  }
+hipError_t launch_large_norm(const LargeNormArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL((large::k_norm<float, float>), dim3((a.rows + 3) / 4), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

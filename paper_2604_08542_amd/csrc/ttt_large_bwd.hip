@@ -449,7 +449,7 @@ hipError_t step_t(const LargeBwdArgs& a, hipStream_t st) {
   const dim3 gh(h / BN, mt), gd(d / BN, mt), nt(NTH);
   // rows of the chunk
   LargeNormArgs na{a.K, a.V, a.Q, a.stride_tok, a.flags, M, d, a.Kn, a.Vn, a.Qn};
-  const hipError_t en = launch_large_norm(na, std::is_same_v<IOT, bf16>, std::is_same_v<T, bf16>, st);
+  const hipError_t en = launch_large_norm(na, st);
   if (en != hipSuccess) return en;
   if (a.apply)
     hipLaunchKernelGGL((k_rows<IOT, T>), dim3((M + 3) / 4), dim3(256), 0, st, static_cast<const IOT*>(a.dO),
@@ -755,7 +755,7 @@ hipError_t step_t(const LargeAmuBwdArgs& a, hipStream_t st) {
   T *Wh1o = P(a.Whop[0]), *Wh2o = P(a.Whop[1]), *Wh3o = P(a.Whop[2]);
   const dim3 gh(h / BN, mt), gd(d / BN, mt), gwh(h / BN, d / BMW), gwd(d / BN, h / BMW), nt(NTH);
   LargeNormArgs na{a.K, a.V, a.Q, a.stride_tok, a.flags, M, d, a.Kn, a.Vn, a.Qn};
-  const hipError_t en = launch_large_norm(na, std::is_same_v<IOT, bf16>, std::is_same_v<T, bf16>, st);
+  const hipError_t en = launch_large_norm(na, st);
   if (en != hipSuccess) return en;
   if (a.apply) {
     hipLaunchKernelGGL((k_rows<IOT, T>), dim3((M + 3) / 4), dim3(256), 0, st, static_cast<const IOT*>(a.dO),
