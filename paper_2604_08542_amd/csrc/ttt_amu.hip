@@ -373,14 +373,8 @@ static hipError_t launch_amu_step_t(const AmuStepArgs& a, int n_blocks, hipStrea
 }
 
 hipError_t launch_amu_step(const AmuStepArgs& a, int n_blocks, int h, bool io_bf16, bool mma_bf16, hipStream_t st) {
-  if (h == 128) {
-    if (io_bf16) return launch_amu_step_t<bf16, true, 4>(a, n_blocks, st);
-    return mma_bf16 ? launch_amu_step_t<float, true, 4>(a, n_blocks, st)
-                    : launch_amu_step_t<float, false, 4>(a, n_blocks, st);
-  }
-  if (io_bf16) return launch_amu_step_t<bf16, true, 8>(a, n_blocks, st);
-  return mma_bf16 ? launch_amu_step_t<float, true, 8>(a, n_blocks, st)
-                  : launch_amu_step_t<float, false, 8>(a, n_blocks, st);
+  if (mma_bf16) return launch_amu_step_bf(a, n_blocks, h, io_bf16, st);
+  return h == 128 ? launch_amu_step_t<float, false, 4>(a, n_blocks, st) : launch_amu_step_t<float, false, 8>(a, n_blocks, st);
 }
 
 hipError_t launch_amu_update(const AmuUpdArgs& a, hipStream_t st) {

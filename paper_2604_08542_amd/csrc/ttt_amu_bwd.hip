@@ -495,23 +495,15 @@ static hipError_t launch_update_t(const AmuBwdArgs& a, int n_blocks, hipStream_t
 
 hipError_t launch_amu_bwd_apply(const AmuBwdArgs& a, int n_blocks, int h, bool io_bf16, bool mma_bf16,
                                 hipStream_t st) {
-  if (h == 128) {
-    if (io_bf16) return launch_apply_t<bf16, true, 4>(a, n_blocks, st);
-    return mma_bf16 ? launch_apply_t<float, true, 4>(a, n_blocks, st) : launch_apply_t<float, false, 4>(a, n_blocks, st);
-  }
-  if (io_bf16) return launch_apply_t<bf16, true, 8>(a, n_blocks, st);
-  return mma_bf16 ? launch_apply_t<float, true, 8>(a, n_blocks, st) : launch_apply_t<float, false, 8>(a, n_blocks, st);
+  if (mma_bf16) return launch_amu_bwd_apply_bf(a, n_blocks, h, io_bf16, st);
+  return h == 128 ? launch_apply_t<float, false, 4>(a, n_blocks, st) : launch_apply_t<float, false, 8>(a, n_blocks, st);
 }
 
 hipError_t launch_amu_bwd_update(const AmuBwdArgs& a, int n_blocks, int h, bool io_bf16, bool mma_bf16,
                                  hipStream_t st) {
-  if (h == 128) {
-    if (io_bf16) return launch_update_t<bf16, true, 4>(a, n_blocks, st);
-    return mma_bf16 ? launch_update_t<float, true, 4>(a, n_blocks, st)
-                    : launch_update_t<float, false, 4>(a, n_blocks, st);
-  }
-  if (io_bf16) return launch_update_t<bf16, true, 8>(a, n_blocks, st);
-  return mma_bf16 ? launch_update_t<float, true, 8>(a, n_blocks, st) : launch_update_t<float, false, 8>(a, n_blocks, st);
+  if (mma_bf16) return launch_amu_bwd_update_bf(a, n_blocks, h, io_bf16, st);
+  return h == 128 ? launch_update_t<float, false, 4>(a, n_blocks, st)
+                  : launch_update_t<float, false, 8>(a, n_blocks, st);
 }
 
 hipError_t launch_amu_psum(const AmuPsumArgs& a, hipStream_t st) {

@@ -280,11 +280,14 @@ hipError_t launch_bwd_reduce(const BwdReduceArgs& a, int n_blocks, hipStream_t s
 hipError_t launch_bwd_prep(const BwdPrepArgs& a, int n_active, bool mma_bf16, hipStream_t st);
 hipError_t launch_bwd_sum(const BwdSumArgs& a, hipStream_t st);
 hipError_t launch_amu_step(const AmuStepArgs& a, int n_blocks, int h, bool io_bf16, bool mma_bf16, hipStream_t st);
+hipError_t launch_amu_step_bf(const AmuStepArgs& a, int n_blocks, int h, bool io_bf16, hipStream_t st);
 hipError_t launch_amu_update(const AmuUpdArgs& a, hipStream_t st);
 hipError_t launch_amu_prep(const AmuPrepArgs& a, bool mma_bf16, hipStream_t st);
 hipError_t launch_amu_bwd_apply(const AmuBwdArgs& a, int n_blocks, int h, bool io_bf16, bool mma_bf16, hipStream_t st);
 hipError_t launch_amu_bwd_update(const AmuBwdArgs& a, int n_blocks, int h, bool io_bf16, bool mma_bf16,
                                  hipStream_t st);
+hipError_t launch_amu_bwd_apply_bf(const AmuBwdArgs& a, int n_blocks, int h, bool io_bf16, hipStream_t st);
+hipError_t launch_amu_bwd_update_bf(const AmuBwdArgs& a, int n_blocks, int h, bool io_bf16, hipStream_t st);
 hipError_t launch_amu_psum(const AmuPsumArgs& a, hipStream_t st);
 // ttt_chunk_fwd on a caller workspace (fixed_scratch null), or on a fixed
 // scratch buffer of ws_bytes with a forward-only layout whose device address
