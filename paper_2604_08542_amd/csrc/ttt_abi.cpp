@@ -1305,9 +1305,9 @@ AmuWs amu_ws_layout(const Shape& s) {
   return L;
 }
 
-// Chain: for s = 0..C one operand-preparation launch (W_s), one step launch
-// (gradient of chunk s, apply of chunk s-1) and, while chunk s exists, one
-// update launch.  GCS: the gradients of all chunks at W0 are one
+// Chain: one operand-preparation launch (W_0), then for s = 0..C one step
+// launch (gradient of chunk s, apply of chunk s-1) and, while chunk s exists,
+// one update launch, which also writes the operand copies of W_{s+1}.  GCS: the gradients of all chunks at W0 are one
 // shard-parallel gradient over every token (the dot-product loss has no
 // per-chunk normalisation, so the sum over chunks is the sum over tokens),
 // one update, then one apply over every token.
@@ -1341,26 +1341,27 @@ ttt_status_t run_amu(const ttt_problem_t* p, const Shape& S, int sync, const voi
     a.grad_start = gs; a.grad_len = (int32_t)gl; a.app_start = as; a.app_len = (int32_t)al;
     return launched([&] { return launch_amu_step(a, (int)(H * G), S.h, S.io_bf16, S.mma_bf16, st); });
   };
-  auto do_update = [&](const AmuWeights& src, int64_t G, float* dst, bool last) {
+  auto do_update = [&](const AmuWeights& src, int64_t G, float* dst, bool last, bool to_prep) {
     AmuUpdArgs u{};
     u.src = src; u.partial = partial; u.G = (int32_t)G; u.H = (int32_t)H; u.h = S.h; u.w_dst = dst;
+    u.prep = to_prep ? prep : nullptr; u.n_mats = 4; u.prep_bf16 = S.mma_bf16;
     u.wT1 = last ? W1_T : nullptr; u.wT2 = last ? W2_T : nullptr; u.wT3 = last ? W3_T : nullptr;
     return launched([&] { return launch_amu_update(u, st); });
   };
   if (C == 0) {  // no tokens: W_T = W_0
-    if (W1_T && !do_update(w0, 0, pp[0], true)) return TTT_EHIP;
+    if (W1_T && !do_update(w0, 0, pp[0], true, false)) return TTT_EHIP;
     return TTT_OK;
   }
   auto mlen = [&](int64_t c) { return std::min<int64_t>(M, N - c * M); };
   if (sync == TTT_SYNC_CHAIN) {
     AmuWeights cur = w0;
+    if (!do_prep(cur)) return TTT_EHIP;
     for (int64_t s = 0; s <= C; ++s) {
       const int64_t gl = s < C ? mlen(s) : 0, al = s >= 1 ? mlen(s - 1) : 0;
       const int64_t G = grid_g(std::max(gl, al));
-      if (!do_prep(cur)) return TTT_EHIP;
       if (!do_step(G, s * M, gl, (s - 1) * M, al)) return TTT_EHIP;
       if (s < C) {
-        if (!do_update(cur, G, pp[s % 2], s == C - 1)) return TTT_EHIP;
+        if (!do_update(cur, G, pp[s % 2], s == C - 1, true)) return TTT_EHIP;
         cur = packed(pp[s % 2]);
       }
     }
@@ -1369,8 +1370,7 @@ ttt_status_t run_amu(const ttt_problem_t* p, const Shape& S, int sync, const voi
   const int64_t G = grid_g(N);
   if (!do_prep(w0)) return TTT_EHIP;
   if (!do_step(G, 0, N, 0, 0)) return TTT_EHIP;
-  if (!do_update(w0, G, pp[0], true)) return TTT_EHIP;
-  if (!do_prep(packed(pp[0]))) return TTT_EHIP;
+  if (!do_update(w0, G, pp[0], true, true)) return TTT_EHIP;
   if (!do_step(G, 0, 0, 0, N)) return TTT_EHIP;
   return TTT_OK;
 }
@@ -1579,11 +1579,11 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
 
 // Reverse mode of the paper's memory unit.  Workspace: shard partials, the
 // carried adjoint Wh [H][3dh], the weights the backward needs ([C+1][H][3dh]
-// for the chain: every W_c, recomputed; [1][H][3dh] for GCS: W*), and three
-// sets of six operand copies per head (weights at the update, weights at the
-// apply, Wh).
+// for the chain: every W_c, recomputed; [1][H][3dh] for GCS: W*), and sets of
+// six operand copies per head (W_0 .. W_C for the chain, W_0 and W* for GCS,
+// and Wh).
 struct AmuBwdWs {
-  size_t partial, wh, wlist, prep_u, prep_a, prep_h, total;
+  size_t partial, wh, wlist, prep_w, prep_h, total;
   int64_t slot_cap;
 };
 
@@ -1593,7 +1593,7 @@ AmuBwdWs amu_bwd_ws_layout(const Shape& s, int64_t n_tokens, int sync) {
   const size_t wbytes = (size_t)3 * s.dh() * sizeof(float);
   const int64_t C = (n_tokens + s.M - 1) / s.M;
   const int64_t n_w = sync == TTT_SYNC_CHAIN ? C + 1 : 1;
-  const size_t pbytes = (size_t)s.H * 6 * s.dh() * sizeof(float);
+  const size_t pbytes = (size_t)s.H * 6 * s.dh() * (s.mma_bf16 ? 2 : 4);
   size_t off = 0;
   L.partial = off;
   off = align_up(off + (size_t)L.slot_cap * wbytes);
@@ -1601,10 +1601,8 @@ AmuBwdWs amu_bwd_ws_layout(const Shape& s, int64_t n_tokens, int sync) {
   off = align_up(off + (size_t)s.H * wbytes);
   L.wlist = off;
   off = align_up(off + (size_t)n_w * s.H * wbytes);
-  L.prep_u = off;
-  off = align_up(off + pbytes);
-  L.prep_a = off;
-  off = align_up(off + pbytes);
+  L.prep_w = off;
+  off = align_up(off + (size_t)(sync == TTT_SYNC_CHAIN ? C + 1 : 2) * pbytes);
   L.prep_h = off;
   off = align_up(off + pbytes);
   L.total = off;
@@ -1629,8 +1627,8 @@ ttt_status_t run_amu_bwd(const ttt_problem_t* p, const Shape& S, int sync, const
   float* partial = at<float>(ws, L.partial);
   float* wh = at<float>(ws, L.wh);
   float* wlist = at<float>(ws, L.wlist);
-  void* prep_u = at<char>(ws, L.prep_u);
-  void* prep_a = at<char>(ws, L.prep_a);
+  // operand copies of W_0, W_1, .. (chain) or W_0, W* (GCS), and of Wh
+  auto prep_w = [&](int64_t c) { return at<char>(ws, L.prep_w) + c * H * 6 * dh * (S.mma_bf16 ? 2 : 4); };
   void* prep_h = at<char>(ws, L.prep_h);
   const int target = default_target_wgs(S);
   auto grid_g = [&](int64_t len) {
@@ -1644,20 +1642,21 @@ ttt_status_t run_amu_bwd(const ttt_problem_t* p, const Shape& S, int sync, const
     a.src = w; a.prep = dst; a.n_mats = 6; a.H = (int32_t)H; a.h = S.h;
     return launched([&] { return launch_amu_prep(a, S.mma_bf16, st); });
   };
-  auto do_grad = [&](int64_t start, int64_t len) {  // gradient partials at the weights in prep_u
+  auto do_grad = [&](int64_t start, int64_t len, void* prep) {  // gradient partials at the weights in prep
     AmuStepArgs a{};
     a.Q = Q; a.K = K; a.V = V; a.O = nullptr; a.eta_tok = eta_tok;
     a.stride_tok = S.stride_tok; a.stride_head = S.stride_head;
     const int64_t G = grid_g(len);
-    a.H = (int32_t)H; a.flags = p->flags; a.G = (int32_t)G; a.prep = prep_u; a.n_prep = 6; a.partial = partial;
+    a.H = (int32_t)H; a.flags = p->flags; a.G = (int32_t)G; a.prep = prep; a.n_prep = 6; a.partial = partial;
     a.grad_start = start; a.grad_len = (int32_t)len; a.app_start = 0; a.app_len = 0;
     if (!launched([&] { return launch_amu_step(a, (int)(H * G), S.h, S.io_bf16, S.mma_bf16, st); }))
       return int64_t(-1);
     return G;
   };
-  auto do_update = [&](const AmuWeights& src, int64_t G, float* dst) {
+  auto do_update = [&](const AmuWeights& src, int64_t G, float* dst, void* prep) {
     AmuUpdArgs u{};
     u.src = src; u.partial = partial; u.G = (int32_t)G; u.H = (int32_t)H; u.h = S.h; u.w_dst = dst;
+    u.prep = prep; u.n_mats = 6; u.prep_bf16 = S.mma_bf16;
     return launched([&] { return launch_amu_update(u, st); });
   };
   auto bwd_args = [&](int64_t start, int64_t len, int64_t G) {
@@ -1667,61 +1666,58 @@ ttt_status_t run_amu_bwd(const ttt_problem_t* p, const Shape& S, int sync, const
     a.start = start; a.len = (int32_t)len;
     return a;
   };
-  auto do_apply_adj = [&](int64_t start, int64_t len) {  // at the weights in prep_a
+  auto do_apply_adj = [&](int64_t start, int64_t len, void* prep) {  // at the weights in prep
     const int64_t G = grid_g(len);
     AmuBwdArgs a = bwd_args(start, len, G);
-    a.X = Q; a.Y = dO; a.dX = dQ; a.prep_w = prep_a;
+    a.X = Q; a.Y = dO; a.dX = dQ; a.prep_w = prep;
     if (!launched([&] { return launch_amu_bwd_apply(a, (int)(H * G), S.h, S.io_bf16, S.mma_bf16, st); }))
       return int64_t(-1);
     return G;
   };
-  auto do_update_adj = [&](int64_t start, int64_t len) {  // at prep_u along prep_h
+  auto do_update_adj = [&](int64_t start, int64_t len, void* prep) {  // at the weights in prep along prep_h
     const int64_t G = grid_g(len);
     AmuBwdArgs a = bwd_args(start, len, G);
     a.X = K; a.Y = V; a.dX = dK; a.dY = dV; a.eta_tok = eta_tok; a.deta_tok = deta_tok;
-    a.prep_w = prep_u; a.prep_a = prep_h;
+    a.prep_w = prep; a.prep_a = prep_h;
     if (!launched([&] { return launch_amu_bwd_update(a, (int)(H * G), S.h, S.io_bf16, S.mma_bf16, st); }))
       return int64_t(-1);
     return G;
   };
-  auto do_psum = [&](int64_t G, const float* base, float* dst, bool final) {
+  auto do_psum = [&](int64_t G, const float* base, float* dst, bool final, bool to_prep) {  // to_prep: into prep_h
     AmuPsumArgs a{};
     a.partial = partial; a.G = (int32_t)G; a.H = (int32_t)H; a.h = S.h; a.base = base; a.dst = dst;
     if (final) { a.out1 = dW1_0; a.out2 = dW2_0; a.out3 = dW3_0; }
+    a.prep = to_prep ? prep_h : nullptr; a.prep_bf16 = S.mma_bf16;
     return launched([&] { return launch_amu_psum(a, st); });
   };
 
   if (C == 0) {  // no tokens: O is empty, every adjoint is zero
-    return do_psum(0, nullptr, wh, true) ? TTT_OK : TTT_EHIP;
+    return do_psum(0, nullptr, wh, true, false) ? TTT_OK : TTT_EHIP;
   }
   if (sync == TTT_SYNC_GCS) {
     float* wstar = wlist;
-    if (!do_prep(w0, prep_u)) return TTT_EHIP;
-    const int64_t Gg = do_grad(0, N);
-    if (Gg < 0 || !do_update(w0, Gg, wstar)) return TTT_EHIP;
-    if (!do_prep(packed(wstar), prep_a)) return TTT_EHIP;
-    const int64_t Ga = do_apply_adj(0, N);
-    if (Ga < 0 || !do_psum(Ga, nullptr, wh, false)) return TTT_EHIP;
-    if (!do_prep(packed(wh), prep_h)) return TTT_EHIP;
-    const int64_t Gu = do_update_adj(0, N);
-    if (Gu < 0 || !do_psum(Gu, wh, wh, true)) return TTT_EHIP;
+    if (!do_prep(w0, prep_w(0))) return TTT_EHIP;
+    const int64_t Gg = do_grad(0, N, prep_w(0));
+    if (Gg < 0 || !do_update(w0, Gg, wstar, prep_w(1))) return TTT_EHIP;
+    const int64_t Ga = do_apply_adj(0, N, prep_w(1));
+    if (Ga < 0 || !do_psum(Ga, nullptr, wh, false, true)) return TTT_EHIP;
+    const int64_t Gu = do_update_adj(0, N, prep_w(0));
+    if (Gu < 0 || !do_psum(Gu, wh, wh, true, false)) return TTT_EHIP;
     return TTT_OK;
   }
   // chain: W_c at wlist + c * H * 3dh (c >= 1); W_0 is the caller's
   auto wc = [&](int64_t c) { return c == 0 ? w0 : packed(wlist + c * H * 3 * dh); };
   auto mlen = [&](int64_t c) { return std::min<int64_t>(M, N - c * M); };
+  if (!do_prep(w0, prep_w(0))) return TTT_EHIP;
   for (int64_t c = 0; c < C; ++c) {
-    if (!do_prep(wc(c), prep_u)) return TTT_EHIP;
-    const int64_t G = do_grad(c * M, mlen(c));
-    if (G < 0 || !do_update(wc(c), G, wlist + (c + 1) * H * 3 * dh)) return TTT_EHIP;
+    const int64_t G = do_grad(c * M, mlen(c), prep_w(c));
+    if (G < 0 || !do_update(wc(c), G, wlist + (c + 1) * H * 3 * dh, prep_w(c + 1))) return TTT_EHIP;
   }
   for (int64_t c = C - 1; c >= 0; --c) {
-    if (!do_prep(wc(c + 1), prep_a)) return TTT_EHIP;
-    const int64_t Ga = do_apply_adj(c * M, mlen(c));
-    if (Ga < 0 || !do_psum(Ga, c == C - 1 ? nullptr : wh, wh, false)) return TTT_EHIP;
-    if (!do_prep(wc(c), prep_u) || !do_prep(packed(wh), prep_h)) return TTT_EHIP;
-    const int64_t Gu = do_update_adj(c * M, mlen(c));
-    if (Gu < 0 || !do_psum(Gu, wh, wh, c == 0)) return TTT_EHIP;
+    const int64_t Ga = do_apply_adj(c * M, mlen(c), prep_w(c + 1));
+    if (Ga < 0 || !do_psum(Ga, c == C - 1 ? nullptr : wh, wh, false, true)) return TTT_EHIP;
+    const int64_t Gu = do_update_adj(c * M, mlen(c), prep_w(c));
+    if (Gu < 0 || !do_psum(Gu, wh, wh, c == 0, false)) return TTT_EHIP;
   }
   return TTT_OK;
 }

@@ -322,7 +322,8 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_step(AmuStepArgs p) {
 }
 
 // W_dst = W_src - (sum of the G shard partials, fixed order), per head; the
-// final weights are also written split when asked.
+// final weights are also written split, and the operand copies of the result,
+// when asked.
 __global__ __launch_bounds__(256) void ttt_amu_update(AmuUpdArgs p) {
   const int dh = D * p.h;
   const int n4 = (3 * dh) / 4;
@@ -340,6 +341,13 @@ __global__ __launch_bounds__(256) void ttt_amu_update(AmuUpdArgs p) {
   *reinterpret_cast<f32x4*>(p.w_dst + (int64_t)head * 3 * dh + idx) = wn;
   float* fin = mat == 0 ? p.wT1 : (mat == 1 ? p.wT2 : p.wT3);
   if (fin) *reinterpret_cast<f32x4*>(fin + (int64_t)head * dh + off) = wn;
+  if (p.prep) {
+    const int64_t po = (int64_t)head * p.n_mats * dh;
+    if (p.prep_bf16)
+      amu_put_prep(static_cast<bf16*>(p.prep) + po, mat, off, p.h, p.n_mats, wn);
+    else
+      amu_put_prep(static_cast<float*>(p.prep) + po, mat, off, p.h, p.n_mats, wn);
+  }
 }
 
 // Operand copies per head: W1 and W3 as [hid][d], W2 as [hid][d] and [d][hid],

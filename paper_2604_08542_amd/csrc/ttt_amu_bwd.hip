@@ -480,6 +480,13 @@ __global__ __launch_bounds__(256) void ttt_amu_psum(AmuPsumArgs p) {
   const int mat = idx / dh, off = idx % dh;
   float* out = mat == 0 ? p.out1 : (mat == 1 ? p.out2 : p.out3);
   if (out) *reinterpret_cast<f32x4*>(out + (int64_t)head * dh + off) = s;
+  if (p.prep) {
+    const int64_t po = (int64_t)head * 6 * dh;
+    if (p.prep_bf16)
+      amu_put_prep(static_cast<bf16*>(p.prep) + po, mat, off, p.h, 6, s);
+    else
+      amu_put_prep(static_cast<float*>(p.prep) + po, mat, off, p.h, 6, s);
+  }
 }
 
 template <typename IOT, bool BF, int NW>
