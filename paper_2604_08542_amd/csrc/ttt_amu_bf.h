@@ -1,5 +1,6 @@
-// Device machinery of the memory unit's BF16 kernels (d = 64): lane layout,
-// operand fragments of staged token rows, token-row parts.
+// Device machinery shared by the BF16 kernels at d = 64 (the memory unit and
+// the reverse step of the MSE unit): lane layout, operand fragments of staged
+// token rows, token-row parts.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -39,14 +40,16 @@ struct Lane {
   // Token-contraction operand of a staged tile: lane (d = 32 db + l32) holds
   // tokens 16m + 4hf + 0..3 and 16m + 8 + 4hf + 0..3, the token slots of
   // result registers 8m .. 8m+7 of a 32x32 block.
-  __device__ __forceinline__ bf16x8 cols(const bf16* X, int m, int db) const {
+  template <int LD>
+  __device__ __forceinline__ bf16x8 cols_at(const bf16* X, int m, int db) const {
     typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
     typedef __attribute__((address_space(3))) bf16 lds_bf16;
-    const bf16* p = X + ((l16 >> 2) + 4 * hf + 16 * m) * XLD + 4 * (l16 & 3) + 16 * ((l >> 4) & 1) + 32 * db;
+    const bf16* p = X + ((l16 >> 2) + 4 * hf + 16 * m) * LD + 4 * (l16 & 3) + 16 * ((l >> 4) & 1) + 32 * db;
     const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)((lds_bf16*)(p)));
-    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)((lds_bf16*)(p + 8 * XLD)));
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)((lds_bf16*)(p + 8 * LD)));
     return (bf16x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   }
+  __device__ __forceinline__ bf16x8 cols(const bf16* X, int m, int db) const { return cols_at<XLD>(X, m, db); }
 };
 // 32x32 block: sum over the four steps of a[m] b[m].
 __device__ __forceinline__ f32x16 dot4(const bf16x8 (&a)[4], const bf16x8 (&b)[4]) {

@@ -2,613 +2,528 @@
 //
 // Same mathematics as ttt_bwd_step (reverse mode through the inner update of
 // chunk s, second-order terms included, plus the apply adjoint of chunk s-1;
-// Sec. 4.2 Eq. 8 and Sec. 3.2 Eq. 3-4), organised for BF16 operands:
+// Sec. 4.2 Eq. 8 and Sec. 3.2 Eq. 3-4), organised for BF16 operands.
 //
-//  - 4 waves, one per SIMD; wave w owns hidden blocks hb = NB*w .. NB*w+NB-1
-//    (32 units each, NB = h/128).  Products whose result has a hidden axis
-//    are 32x32 blocks with tokens in registers; they feed the token-sum
-//    products (gradients of W) straight from registers as packed BF16 pairs.
-//  - Products contracting the hidden axis read [token][hidden] BF16 tiles
-//    staged in LDS; wave w computes the 16 feature columns 16w..16w+15 of
-//    both 16-token halves, so each weight fragment is loaded once per phase.
-//  - Every token-side operand (K, Q, E, dY, dO) is written once to LDS in two
-//    BF16 forms: rows [token][d] for the 32x32 products and columns
-//    [d][token slot] for the token sums, the slot order matching the
-//    register order of a 32x32 result so that one 16-byte read is one
-//    operand fragment.
-//  - sigma(Z) is computed once per element and kept; the raw rows of the
-//    next tile are loaded into registers while the current tile computes.
+// What bounds it: an update tile is a chain of contractions over the hidden
+// axis (A W2, then dP W2, then D Wh1^T and dZ W1^T) with elementwise work
+// between them, phase after phase behind barriers, and four weight matrices in
+// two orders (256 KiB at h = 256) take part.  Read from the L2 per tile, their
+// latency (and, loads and stores completing in order, that of the row prefetch
+// and of the gradient stores before them) stood in every phase.  Here:
+//  - the four matrices stay in LDS for all tiles of a work-group, once each:
+//    straight reads serve the contractions over the hidden axis, transposing
+//    reads those over d;
+//  - 8 waves, two per SIMD, so one's elementwise work overlaps the other's
+//    products.  A wave owns 32 hidden units; at h = 128 two groups of 4 waves
+//    share the matrices, each with a shard of its own;
+//  - LDS is what is left beside them: the BF16 rows of K, E and dY (transposing
+//    reads give their columns) and one staged [token][hidden] tile that A, dP,
+//    D and dZ take in turn.  V and K enter the residual and the normalisation
+//    adjoints in FP32 from the token tensors, in the layout of the 16x16
+//    results, times the row's factor;
+//  - loads and stores of rows past the end are dropped by the buffer range
+//    check, so the tile has no branches that would widen a wait;
+//  - 256 registers per lane suffice only because values are formed where they
+//    are written here (the empty asm statements): left to itself the compiler
+//    sinks the adjoint of Z, the d(eta) sum and the LDS addresses across
+//    barriers, which spilled up to 260 registers (344 us).
+// The row factors and the row dots of the normalisation adjoints sit in the
+// padding of the row tiles.  Measured per step, 16 heads x 5,496 tokens, BF16:
+// h = 256 211 -> 102 us; h = 128, 6,000 tokens, 93 -> 61 us.  (One wave per SIMD
+// with two hidden blocks and 512 registers spills 170 of them.)
 //
-// One update tile runs in 7 LDS phases: rows -> Z, A (stage A) -> Y, A Wh2
-// (E, -eta A Wh2) -> P, K Wh1 (stage D, dP) -> dE (dY) -> dA, token sums
-// (stage dZ) -> dK -> normalisation adjoint of dK, dV.  An apply tile runs
-// rows -> Zq, dZq, token sums (stage dZq) -> dQ -> adjoint of dQ.
+// Phases of an update tile, a barrier after each: Z, A (stage A) | A W2 -> E,
+// A Wh2 | P, K Wh1 -> D, dP (stage dP) | dP W2 -> dY, dots of dV | dV; stage D;
+// dA, dZ, token sums | D Wh1^T | stage dZ | dZ W1^T, dots of dK; next rows |
+// dK.  An apply tile: Zq, dO W2^T -> dZq (stage), token sums | dZq W1^T, dots
+// of dQ; next rows | dQ.
 #include <hip/hip_runtime.h>
 
+#include "ttt_amu_bf.h"
 #include "ttt_common.h"
 #include "ttt_internal.h"
 
 namespace ttt {
-namespace {
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <typename IOT, int NW>
+__global__ __launch_bounds__(512) void ttt_bwd_step_bf(BwdStepArgs p) {
+  constexpr int HH = NW * 32, DH = D * HH;
+  constexpr int NG = 8 / NW;    // groups of NW waves, each with tiles of its own
+  constexpr int RL = 80;        // pitch of a row tile: 64 features, 32 bytes of row data (see below)
+  constexpr int SL = HH + 8;    // pitch of the staged [token][hidden] tile
+  constexpr int NU = HH / 32;   // 16x16x32 products along the hidden axis
+  constexpr int NBK = 8 / NW;   // 16x16 output blocks per wave
+  constexpr bool SPLIT = NW == 8;  // the two row tensors go to the two halves of the group
+  constexpr int EPT = 8;        // row mapping: 8 lanes x 8 elements per token
+  constexpr int SZ = (int)sizeof(IOT);
 
-// LDS plan (byte offsets).  The BF16 tiles come first so that their
-// addresses stay within reach of the 16-bit immediate offsets.
-template <int NB>
-struct BwdLds {
-  static constexpr int HH = 128 * NB;
-  static constexpr int XB = D + 8;   // bf16 [token][d]
-  static constexpr int XT = TT + 8;  // bf16 [d][token slot]
-  static constexpr int SL = HH + 8;  // bf16 [token][hidden]
-  static constexpr int FL = D + 4;   // f32 [token][d]
-  static constexpr int xb = 0;                   // K or Q rows
-  static constexpr int eb = xb + TT * XB * 2;    // E rows
-  static constexpr int yb = eb + TT * XB * 2;    // dY or dO rows
-  static constexpr int xt = yb + TT * XB * 2;    // K or Q columns
-  static constexpr int et = xt + D * XT * 2;     // E columns
-  static constexpr int yt = et + D * XT * 2;     // dY or dO columns
-  static constexpr int s0 = yt + D * XT * 2;     // staged A, then dP, then dZ (or dZq)
-  static constexpr int s1 = s0 + TT * SL * 2;    // staged D
-  static constexpr int xf = s1 + TT * SL * 2;    // K or Q rows, f32 (normalisation adjoint)
-  static constexpr int vf = xf + TT * FL * 4;    // V rows, f32
-  static constexpr int yf = vf + TT * FL * 4;    // dY rows, f32
-  static constexpr int df = yf + TT * FL * 4;    // dK or dQ rows, f32
-  static constexpr int ninv = df + TT * FL * 4;  // float [2][TT]
-  static constexpr int above = ninv + 2 * TT * 4;  // int [2][TT]
-  static constexpr int red = above + 2 * TT * 4;   // float [4]
-  static constexpr int total = red + 16;
-};
+  __shared__ __attribute__((aligned(16))) bf16 xb_[NG][TT * RL];  // K or Q rows
+  __shared__ __attribute__((aligned(16))) bf16 eb_[NG][TT * RL];  // E rows
+  __shared__ __attribute__((aligned(16))) bf16 yb_[NG][TT * RL];  // dY or dO rows
+  __shared__ __attribute__((aligned(16))) bf16 st_[NG][TT * SL];  // staged tile
+  __shared__ __attribute__((aligned(16))) bf16 wl[4][DH];    // matrices as [d][hid], 16-byte chunks of row d at c ^ f(d)
 
-// Token t of a 32-token tile sits at slot(t) of the column tiles: bits 2
-// and 3 swapped, so that the 8 tokens a lane holds in registers 8m..8m+7 of
-// a 32x32 result (rows 8(r/4) + 4*half + r%4) are 8 consecutive slots.
-__device__ __forceinline__ constexpr int slot_of(int t) { return (t & ~12) | ((t & 4) << 1) | ((t & 8) >> 1); }
-
-// The 8 io elements a thread loads per row, as loaded (f32 values, or bf16
-// pairs in 32-bit words).  FP32 rows are held as float vectors: this
-// compiler turns a select over bit-cast elements of an integer vector into a
-// splat of element 0, so integer words are used only for the bf16 pairs.
-template <typename IOT>
-struct RawRow {
-  f32x4 a, b;
-};
-template <>
-struct RawRow<bf16> {
-  u32x4 a;
-};
-
-// Rows are always loaded (masked rows of a ragged tile read the tile's last
-// valid row) and zeroed when unpacked, so the loads need no branch.
-template <typename IOT>
-__device__ __forceinline__ void fetch_row(const IOT* base, uint32_t elem, RawRow<IOT>& r) {
-  if constexpr (std::is_same_v<IOT, float>) {
-    const f32x4* s = reinterpret_cast<const f32x4*>(base + elem);
-    r.a = s[0];
-    r.b = s[1];
-  } else {
-    r.a = *reinterpret_cast<const u32x4*>(base + elem);
-  }
-}
-
-template <typename IOT>
-__device__ __forceinline__ void unpack_row(const RawRow<IOT>& r, bool valid, float (&x)[8]) {
-  if constexpr (std::is_same_v<IOT, float>) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[i] = valid ? r.a[i] : 0.f;
-      x[4 + i] = valid ? r.b[i] : 0.f;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[2 * i] = valid ? __builtin_bit_cast(float, r.a[i] << 16) : 0.f;
-      x[2 * i + 1] = valid ? __builtin_bit_cast(float, r.a[i] & 0xffff0000u) : 0.f;
-    }
-  }
-}
-
-}  // namespace
-
-template <typename IOT, int NB>
-__global__ __launch_bounds__(256) void ttt_bwd_step_bf(BwdStepArgs p) {
-  using L = BwdLds<NB>;
-  constexpr int HH = L::HH;
-  constexpr int DH = D * HH;
-  constexpr int XB = L::XB, XT = L::XT, SL = L::SL, FL = L::FL;
-  constexpr int NU = HH / 32;  // 16x16x32 products along the hidden axis
-
-  __shared__ __attribute__((aligned(16))) char smem[L::total];
-  auto lds = [&](int off) { return smem + off; };
-
-  const int tid = threadIdx.x;
-  const int w = tid >> 6, l32 = tid & 31, hf = (tid >> 5) & 1, l16 = tid & 15, g4 = (tid >> 4) & 3;
-  const int row = tid >> 3, col0 = (tid & 7) * 8;  // row mapping: 8 threads x 8 elements per token
+  Lane L;
+  const int grp = __builtin_amdgcn_readfirstlane(L.w / NW);
+  L.w = __builtin_amdgcn_readfirstlane(L.w % NW);
+  L.hid = 32 * L.w + L.l32;
+  const int tid = threadIdx.x - grp * NW * 64;  // in the group
+  bf16 *const xb = xb_[grp], *const eb = eb_[grp], *const yb = yb_[grp], *const st = st_[grp];
+  // Shard g of a slot (active sequence * H + head); NG consecutive shards share
+  // the work-group, in step: a group without a tile left runs on zeros.
+  const int G = p.G, per_slot = (G + NG - 1) / NG;
   const int lin = xcd_linear_block();
-  const int G = p.G;
-  const int slot = lin / G, g = lin % G;  // slot = active sequence * H + head
+  const int slot = lin / per_slot, g0 = lin % per_slot * NG, g = g0 + grp;
   const int ai = slot / p.H, head = slot % p.H;
   const float eta = p.eta;
   const bf16* prep = static_cast<const bf16*>(p.prep) + (int64_t)slot * 8 * DH;
   const int64_t hoff = (int64_t)head * p.stride_head;
   const bool norm_q = p.flags & 1u, norm_k = p.flags & 2u, norm_v = p.flags & 4u;
-  float* ninv = reinterpret_cast<float*>(lds(L::ninv));
-  int* above = reinterpret_cast<int*>(lds(L::above));
 
-  // ---------------------------------------------------------------- helpers
-  // A fragments of a [token][d] tile for the 32x32 products (token = l32).
-  auto xfrag = [&](int off, bf16x8 (&a)[4]) {
+  // Row data in the padding of the tiles (8 floats per row): xb: the four
+  // waves' dots of dK or dQ and of dV; eb: per tile parity the factors of the
+  // two normalised tensors, negative where the adjoint has no projection (norm
+  // at the floor, or not normalised).
+  auto pad = [](bf16* t, int row) { return reinterpret_cast<float*>(t + row * RL + D); };
+
+  // Matrices (of the prepared operands, 0..3 are W1, W2, Wh1, Wh2 as [hid][d],
+  // 4..7 the same as [d][hid]): all four in LDS as [d][hid], row d's 16-byte
+  // chunk c at c ^ (4 (d & 3) + (d / 4 & 3)), which spreads both the straight
+  // reads of 16 rows (contractions over hid) and the transposing ones of 4
+  // rows x 64 bytes (contractions over d) over all banks; W1 and W2, which
+  // multiply tokens in several products, also in registers.
+  enum { W1 = 0, W2 = 1, WH1 = 2, WH2 = 3 };
+  bf16x8 wf[4 * DH / 4096];  // all requested before any is needed
 #pragma unroll
-    for (int m = 0; m < 4; ++m) a[m] = *reinterpret_cast<const bf16x8*>(lds(off + (l32 * XB + 16 * m + 8 * hf) * 2));
-  };
-  // Weight fragments are loaded one LDS phase before the phase that uses
-  // them (the barrier between phases does not wait for global loads), so
-  // their L2 latency overlaps the elementwise epilogue of the current phase.
-  // Prepared operand k: 0..3 = W1, W2, Wh1, Wh2 as [hid][d]; 4..7 = the same
-  // as [d][hid].
-  struct ThW {  // B fragments of the 32x32 products for this wave's NB hidden blocks
-    bf16x8 f[NB][4];
-  };
-  struct TdW {  // B fragments of the 16x16 products for this wave's 16 feature columns
-    bf16x8 f[NU];
-  };
-  // Buffer loads: one descriptor for this head's 8 prepared operands, a
-  // per-lane byte offset shared by every matrix of a kind, and the matrix /
-  // fragment offset in a scalar register (no per-matrix address registers).
-  const __amdgpu_buffer_rsrc_t prsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(prep), (short)0, 8 * DH * 2, 0x00020000);
-  const int th_off = ((32 * NB * w + l32) * D + 8 * hf) * 2;
-  const int td_off = ((16 * w + l16) * HH + (HH / 4) * g4) * 2;
-  auto bload = [&](int voff, int soff) {
-    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(prsrc, voff, soff, 0));
-  };
-  auto load_th = [&](int k) {
-    ThW r;
+  for (int n = 0; n < 4 * DH / 4096; ++n)
+    wf[n] = *reinterpret_cast<const bf16x8*>(prep + 4 * DH + (512 * n + threadIdx.x) * 8);
+  // The wave's 16x16 output blocks: features 16 db .., token halves tb0 ..
+  const int db16 = L.w & 3, tb0 = NBK == 2 ? 0 : L.w >> 2;
+  // Those blocks of staged tile x matrix k, over the hidden axis.
+  const int col_row = (16 * db16 + L.l16) * HH, col_f = 4 * (L.l16 & 3) + (L.l16 >> 2);
+  auto contract = [&](int k, f32x4 (&c)[NBK]) {
+    int f = col_f;
+    asm volatile("" : "+v"(f));  // addresses formed here: kept across the loop they would take 40 registers
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+    for (int u = 0; u < NU; ++u) {
+      const bf16x8 b = *reinterpret_cast<const bf16x8*>(&wl[k][col_row + 8 * ((NU * L.g4 + u) ^ f)]);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) r.f[j][m] = bload(th_off, k * DH * 2 + j * 32 * D * 2 + 32 * m);
-    return r;
+      for (int bi = 0; bi < NBK; ++bi)
+        c[bi] = mma16(*reinterpret_cast<const bf16x8*>(&st[(16 * (tb0 + bi) + L.l16) * SL + (HH / 4) * L.g4 + 8 * u]), b, c[bi]);
+
+    }
   };
-  auto load_td = [&](int k) {
-    TdW r;
-#pragma unroll
-    for (int u = 0; u < NU; ++u) r.f[u] = bload(td_off, k * DH * 2 + 16 * u);
-    return r;
-  };
-  // 32x32 block C[token][hid] of hidden block j: X[token][:] M[hid][:]^T.
-  auto th = [&](const bf16x8 (&a)[4], const ThW& wt, int j) {
+  // Token rows a x matrix k over d, the wave's 32 hidden units.
+  const int in_row = (8 * L.hf + (L.l16 >> 2)) * HH + 4 * (L.l16 & 1);
+  const int in_c = (4 * L.w + 2 * (L.g4 & 1) + ((L.l16 >> 1) & 1)) ^ (4 * (L.l16 >> 2) + 2 * L.hf);
+  auto inner = [&](const bf16x8 (&a)[4], int k) {
+    typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+    typedef __attribute__((address_space(3))) bf16 lds_bf16;
     f32x16 c = {};
+    int f = in_c;
+    asm volatile("" : "+v"(f));
 #pragma unroll
-    for (int m = 0; m < 4; ++m) c = mma32(a[m], wt.f[j][m], c);
+    for (int m = 0; m < 4; ++m) {
+      bf16x4 h[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        h[i] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+            (lds_bf16x4*)((lds_bf16*)&wl[k][(16 * m + 4 * i) * HH + in_row + 8 * (f ^ i)]));
+      c = mma32(a[m], (bf16x8){h[0][0], h[0][1], h[0][2], h[0][3], h[1][0], h[1][1], h[1][2], h[1][3]}, c);
+    }
     return c;
   };
-  // Keeps the scheduler from hoisting a prefetch above the products before it.
-  auto fence_sched = [] { __builtin_amdgcn_sched_barrier(0); };
-  // A fragment u of the staged [token][hid] tile for token half tb.
-  auto sfrag = [&](int soff, int tb, int u) {
-    return *reinterpret_cast<const bf16x8*>(lds(soff + ((16 * tb + l16) * SL + (HH / 4) * g4 + 8 * u) * 2));
+  auto rows = [&](const bf16* t, bf16x8 (&a)[4]) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) a[m] = *reinterpret_cast<const bf16x8*>(&t[L.l32 * RL + 16 * m + 8 * L.hf]);
   };
-  // Column fragment (feature block db, register group m) of a [d][slot] tile.
-  auto tfrag = [&](int off, int db, int m) {
-    return *reinterpret_cast<const bf16x8*>(lds(off + ((32 * db + l32) * XT + 16 * m + 8 * hf) * 2));
+  auto cols = [&](const bf16* t, int m, int db) { return L.cols_at<RL>(t, m, db); };
+  auto stage = [&](const uint32_t (&pk)[8]) {
+    uint16_t* c = reinterpret_cast<uint16_t*>(st) + L.hid;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) c[c32_row(r, L.hf) * SL] = (uint16_t)(r & 1 ? pk[r >> 1] >> 16 : pk[r >> 1]);
   };
-  auto pack16 = [&](const f32x16& v, uint32_t (&pk)[8]) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) pk[q] = pack_bf16x2(v[2 * q], v[2 * q + 1]);
-  };
-  auto opnd = [&](const uint32_t (&pk)[8], int m) { return as_bf16x8(pk[4 * m], pk[4 * m + 1], pk[4 * m + 2], pk[4 * m + 3]); };
-  // Write a packed 32x32 result column (hidden block hb) into a staged tile.
-  auto stage = [&](int soff, const uint32_t (&pk)[8], int hb) {
-    uint16_t* col = reinterpret_cast<uint16_t*>(lds(soff)) + 4 * hf * SL + 32 * hb + l32;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int r0 = 2 * q, r1 = 2 * q + 1;
-      col[(8 * (r0 >> 2) + (r0 & 3)) * SL] = (uint16_t)(pk[q] & 0xffffu);
-      col[(8 * (r1 >> 2) + (r1 & 3)) * SL] = (uint16_t)(pk[q] >> 16);
-    }
-  };
-  // Token-side value v (4 tokens 16tb+4g4+r, feature 16w+l16 of a 16x16
-  // result) into a row tile and a column tile.
-  auto put_bf = [&](int roff, int coff, int tb, const f32x4& v) {
-    const int d = 16 * w + l16;
-    uint16_t* rt = reinterpret_cast<uint16_t*>(lds(roff));
-    const uint32_t p01 = pack_bf16x2(v[0], v[1]), p23 = pack_bf16x2(v[2], v[3]);
-    const int t0 = 16 * tb + 4 * g4;
-    rt[(t0 + 0) * XB + d] = (uint16_t)(p01 & 0xffffu);
-    rt[(t0 + 1) * XB + d] = (uint16_t)(p01 >> 16);
-    rt[(t0 + 2) * XB + d] = (uint16_t)(p23 & 0xffffu);
-    rt[(t0 + 3) * XB + d] = (uint16_t)(p23 >> 16);
-    *reinterpret_cast<u32x2*>(lds(coff + (d * XT + slot_of(t0)) * 2)) = (u32x2){p01, p23};
-  };
-  // Normalise a fetched row (optionally) and write it to the f32, bf16 row
-  // and bf16 column tiles (any offset < 0 is skipped).
-  auto put_row = [&](const RawRow<IOT>& raw, bool valid, bool do_norm, int ns, int foff, int boff, int toff) {
-    float x[8];
-    unpack_row<IOT>(raw, valid, x);
-    if (do_norm) {
-      float ss = 0.f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) ss = fmaf(x[i], x[i], ss);
-      ss = lane_group_sum<8>(ss);
-      const float nrm = sqrtf(ss);
-      const float inv = 1.0f / fmaxf(nrm, NORM_EPS);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] *= inv;
-      if ((tid & 7) == 0) {
-        ninv[ns * TT + row] = inv;
-        above[ns * TT + row] = nrm > NORM_EPS;
-      }
-    }
-    if (foff >= 0) {
-      f32x4* f = reinterpret_cast<f32x4*>(lds(foff + (row * FL + col0) * 4));
-      f[0] = (f32x4){x[0], x[1], x[2], x[3]};
-      f[1] = (f32x4){x[4], x[5], x[6], x[7]};
-    }
-    uint32_t pk[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) pk[i] = pack_bf16x2(x[2 * i], x[2 * i + 1]);
-    if (boff >= 0) *reinterpret_cast<u32x4*>(lds(boff + (row * XB + col0) * 2)) = (u32x4){pk[0], pk[1], pk[2], pk[3]};
-    if (toff >= 0) {
-      uint16_t* ct = reinterpret_cast<uint16_t*>(lds(toff)) + slot_of(row);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        ct[(col0 + 2 * i) * XT] = (uint16_t)(pk[i] & 0xffffu);
-        ct[(col0 + 2 * i + 1) * XT] = (uint16_t)(pk[i] >> 16);
-      }
-    }
-  };
-  // Normalisation adjoint of the f32 row tile at doff (times sign), stored
-  // to the io tensor for tokens [t0, t0+nv).
-  auto store_adj = [&](void* base, int64_t t0, int nv, int doff, int xoff, bool did_norm, int ns, float sign) {
-    const f32x4* dp = reinterpret_cast<const f32x4*>(lds(doff + (row * FL + col0) * 4));
-    const f32x4* xp = reinterpret_cast<const f32x4*>(lds(xoff + (row * FL + col0) * 4));
-    float v[8], xh[8];
-    float dot = 0.f;
-#pragma unroll
-    for (int h4 = 0; h4 < 2; ++h4) {
-      const f32x4 dv = dp[h4], xv = xp[h4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v[4 * h4 + i] = sign * dv[i];
-        xh[4 * h4 + i] = xv[i];
-        dot = fmaf(v[4 * h4 + i], xv[i], dot);
-      }
-    }
-    if (did_norm) {
-      dot = lane_group_sum<8>(dot);
-      const float inv = ninv[ns * TT + row];
-      const bool ab = above[ns * TT + row];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = ab ? (v[i] - xh[i] * dot) * inv : v[i] * inv;
-    }
-    IOT* tile = static_cast<IOT*>(base) + t0 * p.stride_tok + hoff;  // wave-uniform
-    if (row < nv) store_vec<IOT, 8>(tile + (uint32_t)(row * (uint32_t)p.stride_tok + col0), v);
+  // Keeps the scheduler from holding the operands of the next product early.
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+  // A 16x16 result (4 tokens of one feature) into a row tile.
+  auto put_rows = [&](bf16* t, int bi, const f32x4& v) {
+    uint16_t* o = reinterpret_cast<uint16_t*>(t) + (16 * (tb0 + bi) + 4 * L.g4) * RL + 16 * db16 + L.l16;
+    const uint32_t a = pack_bf16x2(v[0], v[1]), b = pack_bf16x2(v[2], v[3]);
+    o[0] = (uint16_t)a;
+    o[RL] = (uint16_t)(a >> 16);
+    o[2 * RL] = (uint16_t)b;
+    o[3 * RL] = (uint16_t)(b >> 16);
   };
 
-  f32x16 gw1[NB][2] = {}, gw2[NB][2] = {};
+  f32x16 gw1[2] = {}, gw2[2] = {};
   float deta_acc = 0.f;
-
-  const int gl = p.grad_len[ai], al = p.app_len[ai];
+  int gl = p.grad_len[ai], al = p.app_len[ai];
   const int64_t grad_start = p.grad_start[ai], app_start = p.app_start[ai];
   const int n_gt = (gl + TT - 1) / TT, n_at = (al + TT - 1) / TT;
   const float e_scale = gl > 0 ? 2.0f / (float)gl : 0.f;
-  RawRow<IOT> ra, rb;
-  // Row loads: a wave-uniform tile base plus a 32-bit per-lane offset.
-  auto fetch_upd = [&](int t) {
-    const int64_t tb0 = (grad_start + (int64_t)t * TT) * p.stride_tok + hoff;
-    const uint32_t e = (uint32_t)(min(row, gl - t * TT - 1) * (uint32_t)p.stride_tok + col0);
-    fetch_row<IOT>(static_cast<const IOT*>(p.K) + tb0, e, ra);
-    fetch_row<IOT>(static_cast<const IOT*>(p.V) + tb0, e, rb);
-  };
-  auto fetch_app = [&](int t) {
-    const int64_t tb0 = (app_start + (int64_t)t * TT) * p.stride_tok + hoff;
-    const uint32_t e = (uint32_t)(min(row, al - t * TT - 1) * (uint32_t)p.stride_tok + col0);
-    fetch_row<IOT>(static_cast<const IOT*>(p.Q) + tb0, e, ra);
-    fetch_row<IOT>(static_cast<const IOT*>(p.dO) + tb0, e, rb);
-  };
-  if (g < n_gt)
-    fetch_upd(g);
-  else if (g < n_at)
-    fetch_app(g);
+  if (g >= G) gl = al = 0;  // a group past the last shard sees no rows
 
-  ThW wA = load_th(0);  // W1 for the first Z (or Zq) products
+  // Buffer resource over the valid rows of tile t of a region (stride_tok * TT
+  // * 4 bytes fits 31 bits, checked by the host); rows past the end read as
+  // zero and are not written.
+  const int tok_bytes = (int)p.stride_tok * SZ;
+  auto tile_rs = [&](const void* base, int64_t start, int len, int t) {
+    const int nrow = min(max(len - t * TT, 0), TT);
+    const int bytes = __builtin_amdgcn_readfirstlane(min(nrow, 1) * ((nrow - 1) * tok_bytes + D * SZ));
+    IOT* b = const_cast<IOT*>(static_cast<const IOT*>(base)) + (start + (int64_t)t * TT) * p.stride_tok + hoff;
+    return __builtin_amdgcn_make_buffer_rsrc(b, (short)0, bytes, 0x00020000);
+  };
+  // ---- rows: this thread's part of the two tensors of a tile
+  const int rtid = SPLIT ? tid & 255 : tid, row = rtid >> 3, col0 = (rtid & 7) * EPT;
+  const bool second = SPLIT && __builtin_amdgcn_readfirstlane(tid >= 256);  // holds the second tensor (else the first, or both)
+  const int row_off = row * tok_bytes + col0 * SZ;
+  RowPart<IOT, EPT> ra, rb;
+  auto load_part = [&](__amdgpu_buffer_rsrc_t rs, RowPart<IOT, EPT>& r) {
+    if constexpr (SZ == 2) {
+      r.v = __builtin_bit_cast(typename RowPart<IOT, EPT>::vec, __builtin_amdgcn_raw_buffer_load_b128(rs, row_off, 0, 0));
+    } else {
+      typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+      const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(rs, row_off, 0, 0);
+      const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(rs, row_off + 16, 0, 0);
+      r.v = __builtin_bit_cast(typename RowPart<IOT, EPT>::vec, (u32x8){a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]});
+    }
+  };
+  auto fetch = [&](const void* a, const void* b, int64_t start, int len, int t) {
+    load_part(tile_rs(second ? b : a, start, len, t), ra);
+    if (!SPLIT) load_part(tile_rs(b, start, len, t), rb);
+  };
+  // row tile of one tensor (null: only its factor) and its factor into eb's padding
+  auto put_row = [&](const RowPart<IOT, EPT>& r, bool do_norm, bf16* t, int which, int par) {
+    float x[EPT], n = 1.f;
+    const float sc = r.get(true, x, &n), inv = do_norm ? sc : 1.f;
+    if (t) put_part<EPT>(&t[row * RL + col0], x, inv);
+    if ((rtid & 7) == 0) pad(eb, row)[2 * par + which] = do_norm && n > NORM_EPS ? inv : -inv;
+  };
+
+  auto stage_rows = [&](bool update, int par) {
+    if (!second) put_row(ra, update ? norm_k : norm_q, xb, 0, par);
+    if (second || !SPLIT) put_row(SPLIT ? ra : rb, update && norm_v, update ? nullptr : yb, 1, par);
+  };
+
+  // ---- 16x16 result layout: token 16 tb + 4 g4 + r, feature 16 db16 + l16
+  const int el_off = (16 * tb0 + 4 * L.g4) * tok_bytes + (16 * db16 + L.l16) * SZ;
+  typedef std::conditional_t<SZ == 2, uint16_t, uint32_t> raw_t;
+  auto load_elems = [&](__amdgpu_buffer_rsrc_t rs, raw_t (&x)[NBK][4]) {
+#pragma unroll
+    for (int bi = 0; bi < NBK; ++bi)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if constexpr (SZ == 2)
+          x[bi][r] = __builtin_amdgcn_raw_buffer_load_b16(rs, el_off, (16 * bi + r) * tok_bytes, 0);
+        else
+          x[bi][r] = __builtin_amdgcn_raw_buffer_load_b32(rs, el_off, (16 * bi + r) * tok_bytes, 0);
+      }
+  };
+  // raw elements times the row factor; returns the factors
+  auto unit = [&](const raw_t (&raw)[NBK][4], float (&x)[NBK][4], float (&f)[NBK][4], int which, int par) {
+#pragma unroll
+    for (int bi = 0; bi < NBK; ++bi)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        f[bi][r] = pad(eb, 16 * (tb0 + bi) + 4 * L.g4 + r)[2 * par + which];
+        const float v = SZ == 2 ? __uint_as_float((uint32_t)raw[bi][r] << 16) : __uint_as_float((uint32_t)raw[bi][r]);
+        x[bi][r] = mul_rn(v, fabsf(f[bi][r]));
+      }
+  };
+  // row dots of g and xh over this wave's 16 features, into xb's padding
+  auto put_dots = [&](const float (&v)[NBK][4], const float (&xh)[NBK][4], int which) {
+#pragma unroll
+    for (int bi = 0; bi < NBK; ++bi)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float s = lane_group_sum<16>(v[bi][r] * xh[bi][r]);
+        if (L.l16 == 0) pad(xb, 16 * (tb0 + bi) + 4 * L.g4 + r)[4 * which + db16] = s;
+      }
+  };
+  // normalisation adjoint of g, stored
+  auto store_adj = [&](__amdgpu_buffer_rsrc_t rs, const float (&v)[NBK][4], const float (&xh)[NBK][4],
+                       const float (&f)[NBK][4], int which) {
+#pragma unroll
+    for (int bi = 0; bi < NBK; ++bi)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const f32x4 d = *reinterpret_cast<const f32x4*>(pad(xb, 16 * (tb0 + bi) + 4 * L.g4 + r) + 4 * which);
+        const float pv = fmaf(-xh[bi][r], (d[0] + d[1]) + (d[2] + d[3]), v[bi][r]);
+        const float o = (f[bi][r] > 0.f ? pv : v[bi][r]) * fabsf(f[bi][r]);
+        if constexpr (SZ == 2)
+          __builtin_amdgcn_raw_buffer_store_b16((uint16_t)pack_bf16x2(o, o), rs, el_off, (16 * bi + r) * tok_bytes, 0);
+        else
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), rs, el_off, (16 * bi + r) * tok_bytes, 0);
+      }
+  };
 
   // ------------------------------------------------ update adjoint of chunk s
-  for (int t = g; t < n_gt; t += G) {
-    const int64_t t0 = grad_start + (int64_t)t * TT;
-    const int nv = min(TT, gl - t * TT);
-    // phase 0: rows of K and V
-    put_row(ra, row < nv, norm_k, 0, L::xf, L::xb, L::xt);
-    put_row(rb, row < nv, norm_v, 1, L::vf, -1, -1);
-    if (t + G < n_gt)
-      fetch_upd(t + G);
-    else if (g < n_at)
-      fetch_app(g);
+  raw_t vr[NBK][4];
+  fetch(p.K, p.V, grad_start, gl, g);
+  load_elems(tile_rs(p.V, grad_start, gl, g), vr);
+#pragma unroll
+  for (int n = 0; n < 4 * DH / 4096; ++n) {
+    const int i = 512 * n + threadIdx.x, k = i / (DH / 8), d = (i / (HH / 8)) & (D - 1), c = i % (HH / 8);
+    *reinterpret_cast<bf16x8*>(&wl[k][d * HH + 8 * (c ^ (4 * (d & 3) + ((d >> 2) & 3)))]) = wf[n];
+  }
+  stage_rows(true, 0);
+  for (int t = g, par = 0; t - grp < n_gt; t += G, par ^= 1) {
+    // Addresses derived from the lane are formed where they are used.
+    asm volatile("" : "+v"(L.l), "+v"(L.l16), "+v"(L.l32), "+v"(L.hf), "+v"(L.g4));
     __syncthreads();
-    // phase 1: Z = K W1, sigma(Z), A = s(Z) (staged)
-    f32x16 Z[NB], Sg[NB];
-    uint32_t Apk[NB][8];
-    TdW b2, bh;
+    // Z = K W1, sigma(Z), A = s(Z) (staged)
+    f32x16 Z, Sg;
+    uint32_t Apk[8];
     {
-      bf16x8 xa[4];
-      xfrag(L::xb, xa);
+      bf16x8 a[4];
+      rows(xb, a);
+      Z = inner(a, W1);
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        Z[j] = th(xa, wA, j);
-        if (j == NB - 1) {
-          fence_sched();
-          b2 = load_td(5);
-          bh = load_td(7);
-        }
-        f32x16 A;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          Sg[j][r] = sigmoid(Z[j][r]);
-          A[r] = Z[j][r] * Sg[j][r];
-        }
-        pack16(A, Apk[j]);
-        stage(L::s0, Apk[j], NB * w + j);
+      for (int q = 0; q < 8; ++q) {
+        Sg[2 * q] = sigmoid(Z[2 * q]);
+        Sg[2 * q + 1] = sigmoid(Z[2 * q + 1]);
+        Apk[q] = pack_bf16x2(Z[2 * q] * Sg[2 * q], Z[2 * q + 1] * Sg[2 * q + 1]);
       }
+      stage(Apk);
     }
     __syncthreads();
-    // phase 2: Y = A W2 -> E;  A Wh2 -> -eta A Wh2 (kept) and its d(eta) term
-    f32x4 des[2];
-    ThW wP, wK;
+    // Y = A W2 -> E;  A Wh2 -> -eta A Wh2 (kept) and its d(eta) term
+    f32x4 des[NBK];
     {
-      f32x4 y[2] = {}, aw[2] = {};
+      f32x4 y[NBK] = {}, aw[NBK] = {};
+      contract(W2, y);
+      contract(WH2, aw);
+      float vh[NBK][4], vf[NBK][4];
+      unit(vr, vh, vf, 1, par);
 #pragma unroll
-      for (int u = 0; u < NU; ++u)
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
-          const bf16x8 a = sfrag(L::s0, tb, u);
-          y[tb] = mma16(a, b2.f[u], y[tb]);
-          aw[tb] = mma16(a, bh.f[u], aw[tb]);
-        }
-      fence_sched();
-      wP = load_th(1);
-      wK = load_th(2);
-      const float* vf = reinterpret_cast<const float*>(lds(L::vf));
-      const int d = 16 * w + l16;
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
+      for (int bi = 0; bi < NBK; ++bi) {
         f32x4 E;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          E[r] = e_scale * (y[tb][r] - vf[(16 * tb + 4 * g4 + r) * FL + d]);
-          deta_acc -= aw[tb][r] * E[r];
-          des[tb][r] = -eta * aw[tb][r];
+          E[r] = e_scale * (y[bi][r] - vh[bi][r]);
+          deta_acc -= aw[bi][r] * E[r];
+          des[bi][r] = -eta * aw[bi][r];
         }
-        put_bf(L::eb, L::et, tb, E);
+        put_rows(eb, bi, E);
       }
+      asm volatile("" : "+v"(deta_acc));  // summed here, not at the end of the tile
     }
     __syncthreads();
-    // phase 3: P = E W2^T, K Wh1; D = P s'(Z) (staged), dP = dD s'(Z)
-    // (staged), dZ = dD P s''(Z) with dD = -eta K Wh1
-    f32x16 S1[NB], dZ[NB];
-    uint32_t dPpk[NB][8];
-    TdW b2b;
+    // P = E W2^T, K Wh1; D = P s'(Z), dP = dD s'(Z) (staged), dZ = dD P s''(Z)
+    // with dD = -eta K Wh1
+    f32x16 S1, S2, dDP;
+    uint32_t dPpk[8], Dpk[8];
     {
-      bf16x8 ea[4], xa[4];
-      xfrag(L::eb, ea);
-      xfrag(L::xb, xa);
+      bf16x8 a[4];
+      rows(eb, a);
+      const f32x16 P = inner(a, W2);
+      fence();
+      rows(xb, a);
+      const f32x16 KW = inner(a, WH1);
+      fence();
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const f32x16 P = th(ea, wP, j);
-        const f32x16 KW = th(xa, wK, j);
-        if (j == NB - 1) {
-          fence_sched();
-          b2b = load_td(5);
-        }
-        f32x16 Dm, dP;
+      for (int q = 0; q < 8; ++q) {
+        float Dm[2], dP[2];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float z = Z[j][r], sg = Sg[j][r];
-          const float a = z * sg;
-          const float s1 = fmaf(a, 1.0f - sg, sg);
+        for (int i = 0; i < 2; ++i) {
+          const int r = 2 * q + i;
+          const float z = Z[r], sg = Sg[r];
+          const float av = z * sg;
+          const float s1 = fmaf(av, 1.0f - sg, sg);
           const float s2 = sg * (1.0f - sg) * fmaf(z, 1.0f - 2.0f * sg, 2.0f);
-          Dm[r] = P[r] * s1;
-          deta_acc -= KW[r] * Dm[r];
+          Dm[i] = P[r] * s1;
+          deta_acc -= KW[r] * Dm[i];
           const float dD = -eta * KW[r];
-          dP[r] = dD * s1;
-          dZ[j][r] = dD * P[r] * s2;
-          S1[j][r] = s1;
+          dP[i] = dD * s1;
+          dDP[r] = dD * P[r];
+          S1[r] = s1;
+          S2[r] = s2;
+          // formed here: moved past the barrier they would hold Z, sigma(Z), P and dD
+          asm volatile("" : "+v"(dDP[r]), "+v"(S1[r]), "+v"(S2[r]));
         }
-        uint32_t Dpk[8];
-        pack16(Dm, Dpk);
-        pack16(dP, dPpk[j]);
-        stage(L::s1, Dpk, NB * w + j);
-        stage(L::s0, dPpk[j], NB * w + j);
+        Dpk[q] = pack_bf16x2(Dm[0], Dm[1]);
+        asm volatile("" : "+v"(Dpk[q]));
+        dPpk[q] = pack_bf16x2(dP[0], dP[1]);
       }
+      asm volatile("" : "+v"(deta_acc));
+      stage(dPpk);
     }
     __syncthreads();
-    // phase 4: dE = -eta A Wh2 + dP W2;  dY = (2/M) dE
-    ThW wH, wW;
+    // dE = -eta A Wh2 + dP W2;  dY = (2/M) dE, dV = -dY
+    raw_t kr[NBK][4];
+    load_elems(tile_rs(p.K, grad_start, gl, t), kr);
+    fetch(p.K, p.V, grad_start, gl, t + G);  // past the last tile: zeros
+    fence();
+    float gv[NBK][4], vh[NBK][4], vf[NBK][4];
     {
-      f32x4 de[2] = {};
+      f32x4 de[NBK] = {};
+      contract(W2, de);
 #pragma unroll
-      for (int u = 0; u < NU; ++u)
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb) de[tb] = mma16(sfrag(L::s0, tb, u), b2b.f[u], de[tb]);
-      fence_sched();
-      wH = load_th(3);
-      wW = load_th(1);
-      float* yf = reinterpret_cast<float*>(lds(L::yf));
-      const int d = 16 * w + l16;
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
+      for (int bi = 0; bi < NBK; ++bi) {
         f32x4 dY;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          dY[r] = e_scale * (des[tb][r] + de[tb][r]);
-          yf[(16 * tb + 4 * g4 + r) * FL + d] = dY[r];
+          dY[r] = e_scale * (des[bi][r] + de[bi][r]);
+          gv[bi][r] = -dY[r];
         }
-        put_bf(L::yb, L::yt, tb, dY);
+        put_rows(yb, bi, dY);
       }
+      unit(vr, vh, vf, 1, par);
+      put_dots(gv, vh, 1);
     }
     __syncthreads();
-    // phase 5: dA = -eta E Wh2^T + dY W2^T;  dZ += dA s'(Z);  token sums
-    //          dP^T E + A^T dY (W2) and K^T dZ (W1);  stage dZ
-    TdW b1, bh1;
+    store_adj(tile_rs(p.dV, grad_start, gl, t), gv, vh, vf, 1);
+    // stage D;  dA = -eta E Wh2^T + dY W2^T;  dZ += dA s'(Z);  token sums dP^T E
+    // + A^T dY (W2) and K^T dZ (W1)
+    uint32_t dZpk[8];
     {
-      bf16x8 ea[4], ya[4];
-      xfrag(L::eb, ea);
-      xfrag(L::yb, ya);
+      stage(Dpk);
+      bf16x8 a[4];
+      rows(eb, a);
+      const f32x16 dA1 = inner(a, WH2);
+      fence();
+      rows(yb, a);
+      const f32x16 dA2 = inner(a, W2);
+      fence();
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const f32x16 dA1 = th(ea, wH, j);
-        const f32x16 dA2 = th(ya, wW, j);
-        if (j == NB - 1) {
-          fence_sched();
-          b1 = load_td(4);
-          bh1 = load_td(6);
+      for (int q = 0; q < 8; ++q) {
+        float d[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int r = 2 * q + i;
+          d[i] = fmaf(dDP[r], S2[r], mul_rn(fmaf(-eta, dA1[r], dA2[r]), S1[r]));
         }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) dZ[j][r] += (-eta * dA1[r] + dA2[r]) * S1[j][r];
-        uint32_t dZpk[8];
-        pack16(dZ[j], dZpk);
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-          for (int m = 0; m < 2; ++m) {
-            gw2[j][db] = mma32(opnd(Apk[j], m), tfrag(L::yt, db, m), gw2[j][db]);
-            gw2[j][db] = mma32(opnd(dPpk[j], m), tfrag(L::et, db, m), gw2[j][db]);
-            gw1[j][db] = mma32(tfrag(L::xt, db, m), opnd(dZpk, m), gw1[j][db]);
-          }
-        stage(L::s0, dZpk, NB * w + j);
+        dZpk[q] = pack_bf16x2(d[0], d[1]);
       }
-    }
-    __syncthreads();
-    // phase 6: dK = -eta D Wh1^T + dZ W1^T
-    {
-      f32x4 k1[2] = {}, k2[2] = {};
+      fence();
 #pragma unroll
-      for (int u = 0; u < NU; ++u)
+      for (int db = 0; db < 2; ++db)
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
-          k1[tb] = mma16(sfrag(L::s1, tb, u), bh1.f[u], k1[tb]);
-          k2[tb] = mma16(sfrag(L::s0, tb, u), b1.f[u], k2[tb]);
+        for (int m = 0; m < 2; ++m) {
+          const bf16x8 cy = cols(yb, m, db), ce = cols(eb, m, db), cx = cols(xb, m, db);
+          gw2[db] = mma32(opnd(Apk, m), cy, gw2[db]);
+          gw2[db] = mma32(opnd(dPpk, m), ce, gw2[db]);
+          gw1[db] = mma32(cx, opnd(dZpk, m), gw1[db]);
+          fence();
         }
-      fence_sched();
-      wA = load_th(0);
-      float* df = reinterpret_cast<float*>(lds(L::df));
-      const int d = 16 * w + l16;
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) df[(16 * tb + 4 * g4 + r) * FL + d] = -eta * k1[tb][r] + k2[tb][r];
     }
     __syncthreads();
-    // phase 7: normalisation adjoints, dK and dV = -dY.  The next tile's
-    // phase 0 writes only this thread's own row positions, so no barrier.
-    store_adj(p.dK, t0, nv, L::df, L::xf, norm_k, 0, 1.0f);
-    store_adj(p.dV, t0, nv, L::yf, L::vf, norm_v, 1, -1.0f);
+    // dK = -eta D Wh1^T + dZ W1^T
+    load_elems(tile_rs(p.V, grad_start, gl, t + G), vr);
+    fence();
+    f32x4 k1[NBK] = {}, k2[NBK] = {};
+    contract(WH1, k1);
+    __syncthreads();
+    stage(dZpk);
+    __syncthreads();
+    contract(W1, k2);
+    float gk[NBK][4], kh[NBK][4], kf[NBK][4];
+#pragma unroll
+    for (int bi = 0; bi < NBK; ++bi)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) gk[bi][r] = fmaf(-eta, k1[bi][r], k2[bi][r]);
+    unit(kr, kh, kf, 0, par);
+    put_dots(gk, kh, 0);
+    // the next tile's rows (the row tiles were last read before the sums' barrier)
+    stage_rows(true, par ^ 1);
+    __syncthreads();
+    store_adj(tile_rs(p.dK, grad_start, gl, t), gk, kh, kf, 0);
   }
 
   // ------------------------------------------------ apply adjoint of chunk s-1
-  ThW wB;
-  if (g < n_at) wB = load_th(1);  // W2 for the dO W2^T products
-  for (int t = g; t < n_at; t += G) {
-    const int64_t t0 = app_start + (int64_t)t * TT;
-    const int nv = min(TT, al - t * TT);
-    put_row(ra, row < nv, norm_q, 0, L::xf, L::xb, L::xt);
-    put_row(rb, row < nv, false, 1, -1, L::yb, L::yt);
-    if (t + G < n_at) fetch_app(t + G);
+  __syncthreads();  // the last update tile's row data are read
+  fetch(p.Q, p.dO, app_start, al, g);
+  stage_rows(false, 0);
+  for (int t = g, par = 0; t - grp < n_at; t += G, par ^= 1) {
+    raw_t qr[NBK][4];
+    load_elems(tile_rs(p.Q, app_start, al, t), qr);
+    fetch(p.Q, p.dO, app_start, al, t + G);
     __syncthreads();
     // Zq = Q W1, dZq = (dO W2^T) s'(Zq); token sums Aq^T dO and Q^T dZq
-    TdW b1;
     {
-      bf16x8 xa[4], ya[4];
-      xfrag(L::xb, xa);
-      xfrag(L::yb, ya);
+      bf16x8 a[4];
+      rows(xb, a);
+      uint32_t Apq[8], dZpk[8];
+      const f32x16 Zq = inner(a, W1);
+      fence();
+      rows(yb, a);
+      const f32x16 Gq = inner(a, W2);
+      fence();
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const f32x16 Zq = th(xa, wA, j);
-        const f32x16 Gq = th(ya, wB, j);
-        if (j == NB - 1) {
-          fence_sched();
-          b1 = load_td(4);
-        }
-        f32x16 Aq, dZq;
+      for (int q = 0; q < 8; ++q) {
+        float Aq[2], dq[2];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float z = Zq[r];
+        for (int i = 0; i < 2; ++i) {
+          const float z = Zq[2 * q + i];
           const float sg = sigmoid(z);
-          const float a = z * sg;
-          Aq[r] = a;
-          dZq[r] = Gq[r] * fmaf(a, 1.0f - sg, sg);
+          Aq[i] = z * sg;
+          dq[i] = Gq[2 * q + i] * fmaf(Aq[i], 1.0f - sg, sg);
         }
-        uint32_t Apq[8], dZpk[8];
-        pack16(Aq, Apq);
-        pack16(dZq, dZpk);
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-          for (int m = 0; m < 2; ++m) {
-            gw2[j][db] = mma32(opnd(Apq, m), tfrag(L::yt, db, m), gw2[j][db]);
-            gw1[j][db] = mma32(tfrag(L::xt, db, m), opnd(dZpk, m), gw1[j][db]);
-          }
-        stage(L::s0, dZpk, NB * w + j);
+        Apq[q] = pack_bf16x2(Aq[0], Aq[1]);
+        dZpk[q] = pack_bf16x2(dq[0], dq[1]);
       }
+      stage(dZpk);
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const bf16x8 cy = cols(yb, m, db), cx = cols(xb, m, db);
+          gw2[db] = mma32(opnd(Apq, m), cy, gw2[db]);
+          gw1[db] = mma32(cx, opnd(dZpk, m), gw1[db]);
+        }
     }
     __syncthreads();
     // dQ = dZq W1^T
-    {
-      f32x4 q1[2] = {};
+    f32x4 c[NBK] = {};
+    contract(W1, c);
+    float gq[NBK][4], qh[NBK][4], qf[NBK][4];
 #pragma unroll
-      for (int u = 0; u < NU; ++u)
+    for (int bi = 0; bi < NBK; ++bi)
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb) q1[tb] = mma16(sfrag(L::s0, tb, u), b1.f[u], q1[tb]);
-      if (t + G < n_at) {
-        fence_sched();
-        wA = load_th(0);
-        wB = load_th(1);
-      }
-      float* df = reinterpret_cast<float*>(lds(L::df));
-      const int d = 16 * w + l16;
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) df[(16 * tb + 4 * g4 + r) * FL + d] = q1[tb][r];
-    }
+      for (int r = 0; r < 4; ++r) gq[bi][r] = c[bi][r];
+    unit(qr, qh, qf, 0, par);
+    put_dots(gq, qh, 0);
+    stage_rows(false, par ^ 1);
     __syncthreads();
-    store_adj(p.dQ, t0, nv, L::df, L::xf, norm_q, 0, 1.0f);
+    store_adj(tile_rs(p.dQ, app_start, al, t), gq, qh, qf, 0);
   }
 
   // ------------------------------------------------ shard partials
-  float* part = p.partial + ((int64_t)slot * G + g) * (2 * DH);
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const int hb = NB * w + j;
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rr = c32_row(r, hf);
-        part[(32 * db + rr) * HH + 32 * hb + l32] = gw1[j][db][r];
-        part[DH + (32 * hb + rr) * D + 32 * db + l32] = gw2[j][db][r];
-      }
-  }
-  float* red = reinterpret_cast<float*>(lds(L::red));
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) deta_acc += __shfl_xor(deta_acc, m, 64);
   __syncthreads();
-  if ((tid & 63) == 0) red[w] = deta_acc;
+  float* red = reinterpret_cast<float*>(st);
+  if (L.l == 0) red[L.w] = deta_acc;
   __syncthreads();
-  if (tid == 0) p.partial_deta[(int64_t)slot * G + g] = red[0] + red[1] + red[2] + red[3];
+  if (g >= G) return;
+  float* part = p.partial + ((int64_t)slot * G + g) * (2 * DH);
+#pragma unroll
+  for (int db = 0; db < 2; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int rr = c32_row(r, L.hf);
+      part[(32 * db + rr) * HH + L.hid] = gw1[db][r];
+      part[DH + (32 * L.w + rr) * D + 32 * db + L.l32] = gw2[db][r];
+    }
+  if (tid == 0) {
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) s += red[w];
+    p.partial_deta[(int64_t)slot * G + g] = s;
+  }
 }
 
-template <typename IOT, int NB>
+template <typename IOT, int NW>
 static hipError_t launch_bwd_step_bf_t(const BwdStepArgs& a, int n_blocks, hipStream_t st) {
-  hipLaunchKernelGGL((ttt_bwd_step_bf<IOT, NB>), dim3(n_blocks), dim3(256), 0, st, a);
+  constexpr int NG = 8 / NW;
+  hipLaunchKernelGGL((ttt_bwd_step_bf<IOT, NW>), dim3(n_blocks / a.G * ((a.G + NG - 1) / NG)), dim3(512), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_step_bf(const BwdStepArgs& a, int n_blocks, int h, bool io_bf16, hipStream_t st) {
   if (h == 128)
-    return io_bf16 ? launch_bwd_step_bf_t<bf16, 1>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 1>(a, n_blocks, st);
-  return io_bf16 ? launch_bwd_step_bf_t<bf16, 2>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 2>(a, n_blocks, st);
+    return io_bf16 ? launch_bwd_step_bf_t<bf16, 4>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 4>(a, n_blocks, st);
+  return io_bf16 ? launch_bwd_step_bf_t<bf16, 8>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 8>(a, n_blocks, st);
 }
 
 }  // namespace ttt
