@@ -75,11 +75,6 @@ __device__ __forceinline__ Packed pack32(const f32x16& y) {
 __device__ __forceinline__ bf16x8 opnd(const uint32_t (&pk)[8], int m) {
   return as_bf16x8(pk[4 * m], pk[4 * m + 1], pk[4 * m + 2], pk[4 * m + 3]);
 }
-// x * y with its own rounding (not fused into an addition that follows).
-__device__ __forceinline__ float mul_rn(float x, float y) {
-#pragma clang fp contract(off)
-  return x * y;
-}
 
 // EPT consecutive elements of a token row, as loaded.
 template <typename IOT, int EPT>

@@ -23,9 +23,18 @@
 // units [32w, 32w+32) for the products whose result has a hidden axis
 // (32x32 blocks with tokens in registers, which also feed the token-sum
 // products directly); products contracting the hidden axis read staged
-// [token][hidden] tiles from LDS as 16x16 blocks.  This first backward reads
-// its weight operands straight from memory (they are L2-resident per chain)
-// instead of keeping four weight matrices on chip.
+// [token][hidden] tiles from LDS as 16x16 blocks.  Weight operands are read
+// from memory per tile (L2-resident per chain; eight FP32 matrices of 32 or 64
+// KiB do not fit the LDS).
+//
+// What bounds it: the FP32 matrix products (18 of 32 x 64 x h per pair of
+// tiles, 71% of the rate of a large FP32 product).  With 313 registers and 87
+// KB of LDS a work-group had its CU to itself at h = 128, and at h = 256 it
+// spilled 70 registers, because the compiler kept the terms of the d(eta) sum
+// and the factors of dZ across barriers; formed where they are written (the
+// empty asm statements), with the tile of dK on that of dE, two work-groups fit
+// a CU and nothing spills: per step of 32 heads x 2,999 tokens at h = 128 336 ->
+// 265 us, 16 heads x 5,000 tokens at h = 256 466 -> 371 us.
 #include <hip/hip_runtime.h>
 
 #include "ttt_common.h"
@@ -41,12 +50,8 @@ __device__ __forceinline__ T* opaque(T* ptr) {
   return ptr;
 }
 
-#ifndef BWD_F32_NW256
-#define BWD_F32_NW256 8
-#endif
-
 template <typename IOT, int NW, int NB>
-__global__ __launch_bounds__(NW * 64) void ttt_bwd_step(BwdStepArgs p) {
+__global__ __launch_bounds__(NW * 64, 2) void ttt_bwd_step(BwdStepArgs p) {
   constexpr int HH = NW * 32 * NB;  // hidden size: NW waves x NB 32-wide blocks each
   constexpr int NT = NW * 64;
   constexpr int EPT = D * TT / NT;
@@ -61,7 +66,7 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_step(BwdStepArgs p) {
   __shared__ __attribute__((aligned(16))) float es[TT * LD];    // E
   __shared__ __attribute__((aligned(16))) float des[TT * LD];   // -eta A Wh2, then dE
   __shared__ __attribute__((aligned(16))) float dys[TT * LD];   // dY, or dO rows for apply tiles
-  __shared__ __attribute__((aligned(16))) float dxs[TT * LD];   // dK or dQ before the norm adjoint
+  float* const dxs = des;                                       // dK or dQ before the norm adjoint (dE is consumed)
   __shared__ __attribute__((aligned(16))) MT sta[TT * AS_LD];   // staged A, then D, or dZq
   __shared__ __attribute__((aligned(16))) MT stb[TT * AS_LD];   // staged dP, then dZ
   __shared__ float ninv[2][TT];   // 1 / max(||x||, eps) of the two staged row sets
@@ -255,9 +260,10 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_step(BwdStepArgs p) {
         deta_acc -= aw[r] * E;
       }
     }
+    asm volatile("" : "+v"(deta_acc));  // summed here: moved to the end of the tile its terms would be held
     __syncthreads();
     // P = E W2^T, D = P s'(Z) (staged), K Wh1 -> dD and its deta term,
-    // dP = dD s'(Z) (staged), dZ = dD P s''(Z)
+    // dP = dD s'(Z) (staged), dD P (kept for dZ)
     f32x16 dP[NB], dZ[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
@@ -270,13 +276,14 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_step(BwdStepArgs p) {
         const float sg = sigmoid(z);
         const float a = z * sg;
         const float s1 = fmaf(a, 1.0f - sg, sg);
-        const float s2 = sg * (1.0f - sg) * fmaf(z, 1.0f - 2.0f * sg, 2.0f);
         Dm[r] = P[r] * s1;
         deta_acc -= KW[r] * Dm[r];
         const float dD = -eta * KW[r];
         dP[j][r] = dD * s1;
-        dZ[j][r] = dD * P[r] * s2;
+        dZ[j][r] = dD * P[r];
+        asm volatile("" : "+v"(dP[j][r]), "+v"(dZ[j][r]));  // formed before the barrier
       }
+      asm volatile("" : "+v"(deta_acc));
       stage(sta, Dm, j);
       stage(stb, dP[j], j);
     }
@@ -294,7 +301,7 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_step(BwdStepArgs p) {
       }
     }
     __syncthreads();
-    // dA = -eta E Wh2^T + dY W2^T ; dZ += dA s'(Z) ; token sums
+    // dA = -eta E Wh2^T + dY W2^T ; dZ = dD P s''(Z) + dA s'(Z) ; token sums
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const f32x16 dA1 = th(es, H2n, j);
@@ -306,7 +313,8 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_step(BwdStepArgs p) {
         const float sg = sigmoid(z);
         const float a = z * sg;
         A[r] = a;
-        dZ[j][r] += (-eta * dA1[r] + dA2[r]) * fmaf(a, 1.0f - sg, sg);
+        const float s2 = sg * (1.0f - sg) * fmaf(z, 1.0f - 2.0f * sg, 2.0f);
+        dZ[j][r] = fmaf(dZ[j][r], s2, mul_rn(fmaf(-eta, dA1[r], dA2[r]), fmaf(a, 1.0f - sg, sg)));
       }
       tok_sum_w2(gw2[j], A, dys);
       tok_sum_w2(gw2[j], dP[j], es);
@@ -544,7 +552,7 @@ static hipError_t launch_bwd_step_t(const BwdStepArgs& a, int n_blocks, hipStrea
 
 hipError_t launch_bwd_step(const BwdStepArgs& a, int n_blocks, int h, bool io_bf16, bool mma_bf16, hipStream_t st) {
   if (mma_bf16 || io_bf16) return launch_bwd_step_bf(a, n_blocks, h, io_bf16, st);
-  return h == 128 ? launch_bwd_step_t<4, 1>(a, n_blocks, st) : launch_bwd_step_t<BWD_F32_NW256, 256 / (32 * BWD_F32_NW256)>(a, n_blocks, st);
+  return h == 128 ? launch_bwd_step_t<4, 1>(a, n_blocks, st) : launch_bwd_step_t<8, 1>(a, n_blocks, st);
 }
 
 hipError_t launch_bwd_reduce(const BwdReduceArgs& a, int n_blocks, hipStream_t st) {

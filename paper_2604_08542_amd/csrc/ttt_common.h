@@ -173,6 +173,12 @@ __device__ __forceinline__ int xcd_linear_block() {
   return (nb % 8 == 0) ? (bid % 8) * (nb / 8) + bid / 8 : bid;
 }
 
+// x * y with its own rounding (not fused into an addition that follows).
+__device__ __forceinline__ float mul_rn(float x, float y) {
+#pragma clang fp contract(off)
+  return x * y;
+}
+
 // ----------------------------------------------------------------- launch plans
 // One chunk step of the forward for a list of active sequences: the gradient
 // partials of chunk s and the apply of chunk s-1 (both use the weights W_s).

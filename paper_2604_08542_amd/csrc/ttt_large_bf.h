@@ -44,11 +44,6 @@ __device__ __forceinline__ float fixed_sum(const float* part, int n) {
   return tot;
 }
 
-// x * y with its own rounding (not fused into an addition that follows).
-__device__ __forceinline__ float mul_rn(float x, float y) {
-#pragma clang fp contract(off)
-  return x * y;
-}
 // x rounded to BF16.
 __device__ __forceinline__ float round_bf(float x) { return __uint_as_float(pack_bf16x2(x, x) << 16); }
 
