@@ -336,7 +336,8 @@ __device__ __forceinline__ void fwd_body_bf(const StepCtx& p) {
   // out of the loop (it would hold registers across the whole loop)
   int tid = threadIdx.x;
   if constexpr (OPAQUE_TID) asm volatile("" : "+v"(tid));
-  const int w = tid >> 6, l = tid & 63, l32 = l & 31, hf = l >> 5, l16 = l & 15, g4 = l >> 4;
+  const int w = tid >> 6;
+  int l = tid & 63, l32 = l & 31, hf = l >> 5, l16 = l & 15, g4 = l >> 4;
   const int G = p.G, g = p.g, head = p.head;
   const int hid = w * 32 + l32;
   const float* W1 = p.W1;
@@ -679,6 +680,10 @@ __device__ __forceinline__ void fwd_body_bf(const StepCtx& p) {
     fetch(2);
     __syncthreads();
     for (int it = 0; it < iters; it += 2) {
+      // h = 128, BF16 rows: LDS addresses are formed where they are used; held
+      // across the loop they spill 29 registers of the 256 (with FP32 rows the
+      // compiler does better with them held)
+      if constexpr (NW == 4 && sizeof(IOT) == 2) asm volatile("" : "+v"(l), "+v"(l32), "+v"(hf), "+v"(l16), "+v"(g4));
       phase_a(it, std::integral_constant<int, 0>{});
       __syncthreads();
       phase_b(it, std::integral_constant<int, 0>{});
@@ -825,9 +830,14 @@ __global__ __launch_bounds__(256) void ttt_update(UpdStepArgs p) {
 
 // ----------------------------------------------------------------- step kernel
 // One chunk step for every active chain of a launch plan (one work-group per
-// (chain, token shard)); the partials are reduced by ttt_update.
+// (chain, token shard)); the partials are reduced by ttt_update.  At h = 128
+// with BF16 operands the body takes 277 registers when it is left to, one wave
+// per SIMD, and the 512 work-groups of a launch ran in two rounds; bounded to
+// 256 two work-groups share a CU: 16 heads x 6,000 tokens x 8 chunks 424 -> 347
+// us, all chunks synchronised 262 -> 183 us (FP32 rows, which spill: 431 -> 409
+// and 284 -> 238 us).
 template <typename IOT, int NW, bool BF>
-__global__ __launch_bounds__(NW * 64) void ttt_fwd_step(FwdStepArgs p) {
+__global__ __launch_bounds__(NW * 64, NW == 4 && BF ? 2 : 1) void ttt_fwd_step(FwdStepArgs p) {
   constexpr int DH = D * NW * 32;
   const int lin = xcd_linear_block();
   const int slot = lin / p.G, g = lin % p.G;
