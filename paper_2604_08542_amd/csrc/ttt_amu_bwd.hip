@@ -35,64 +35,66 @@
 namespace ttt {
 namespace {
 
-// Per-kernel tile machinery shared by the two reverse-mode kernels.
-template <typename MT, int NW>
+// Tile machinery shared by the two reverse-mode kernels (FP32 operands; BF16
+// operands: ttt_amu_bwd_bf.hip).
+template <int NW, bool BUF>
 struct AmuTiles {
-  static constexpr bool BF = std::is_same_v<MT, bf16>;
   static constexpr int HH = NW * 32;
+  // h = 256: 256 registers per lane, so two steps of a product in flight and
+  // no operand of the next one; h = 128 has the room, and a work-group's
+  // single tile is faster with all of them.
+  static constexpr bool TIGHT = NW == 8;
   static constexpr int DH = D * HH;
   static constexpr int LD = D + 4;                 // f32 [token][d] tiles
-  static constexpr int AS_LD = HH + (BF ? 8 : 4);  // staged [token][hidden] tiles
+  static constexpr int AS_LD = HH + 4;          // staged [token][hidden] tiles
   int hid, l32, hf, l16, g4;
 
-  // 32x32 block C[token][hid] = X[token][:] M[hid][:]^T (M rows contiguous).
-  __device__ f32x16 th(const float* X, const MT* M) const {
+  // Operand copies of one head's weights.  BUF: read through a buffer resource
+  // with matrix and step in the scalar offset, so that no address is held per
+  // matrix (all but the update adjoint at h = 128, which is faster without: 91
+  // against 103 us at 16 heads x 1,500 tokens).
+  struct Weights {
+    const float* p;
+    __amdgpu_buffer_rsrc_t rs;
+  };
+  static __device__ Weights weights(const void* prep, int head) {
+    float* b = const_cast<float*>(static_cast<const float*>(prep)) + (int64_t)head * 6 * DH;
+    return {b, __builtin_amdgcn_make_buffer_rsrc(b, (short)0, 6 * DH * 4, 0x00020000)};
+  }
+  // four elements of matrix k, lane offset off, step offset step (elements)
+  static __device__ f32x4 wload(const Weights& m, int k, int off, int step) {
+    if constexpr (BUF)
+      return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(m.rs, off * 4, (k * DH + step) * 4, 0));
+    else
+      return *reinterpret_cast<const f32x4*>(m.p + k * DH + off + step);
+  }
+  // 32x32 block C[token][hid] = X[token][:] M[hid][:]^T, M matrix k of m (rows of d).
+  __device__ f32x16 th(const float* X, const Weights& m, int k) const {
     f32x16 c = {};
-    const MT* mrow = M + hid * D;
-    if constexpr (BF) {
+    const int off = hid * D + 32 * hf;
+#pragma unroll TIGHT ? 2 : 8
+    for (int s4 = 0; s4 < 8; ++s4) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(&X[l32 * LD + 32 * hf + 4 * s4]);
+      const f32x4 b = wload(m, k, off, 4 * s4);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int d0 = 16 * m + 8 * hf;
-        const f32x4 x0 = *reinterpret_cast<const f32x4*>(&X[l32 * LD + d0]);
-        const f32x4 x1 = *reinterpret_cast<const f32x4*>(&X[l32 * LD + d0 + 4]);
-        const bf16x8 a = as_bf16x8(pack_bf16x2(x0[0], x0[1]), pack_bf16x2(x0[2], x0[3]),
-                                   pack_bf16x2(x1[0], x1[1]), pack_bf16x2(x1[2], x1[3]));
-        c = mma32(a, *reinterpret_cast<const bf16x8*>(mrow + d0), c);
-      }
-    } else {
-#pragma unroll
-      for (int s4 = 0; s4 < 8; ++s4) {
-        const int d0 = 32 * hf + 4 * s4;
-        const f32x4 x = *reinterpret_cast<const f32x4*>(&X[l32 * LD + d0]);
-        const f32x4 b = *reinterpret_cast<const f32x4*>(mrow + d0);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c = mma32(x[e], b[e], c);
-      }
+      for (int e = 0; e < 4; ++e) c = mma32(x[e], b[e], c);
     }
+    if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
     return c;
   }
   // 16x16 block C[token][d] (token half tb, feature block db) += S[token][:] F,
-  // S a staged tile, F(hid, d) = M[d][hid].
-  __device__ f32x4 td(const MT* S, int tb, int db, const MT* M, f32x4 c) const {
+  // S a staged tile, F(hid, d) = M[d][hid], M matrix k of m.
+  __device__ f32x4 td(const float* S, int tb, int db, const Weights& m, int k, f32x4 c) const {
     const int arow = 16 * tb + l16;
-    const MT* mrow = M + (16 * db + l16) * HH;
-    if constexpr (BF) {
+    const int off = (16 * db + l16) * HH + (HH / 4) * g4;
+#pragma unroll TIGHT ? 2 : HH / 16
+    for (int u = 0; u < HH / 16; ++u) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(&S[arow * AS_LD + (HH / 4) * g4 + 4 * u]);
+      const f32x4 b = wload(m, k, off, 4 * u);
 #pragma unroll
-      for (int u = 0; u < HH / 32; ++u) {
-        const int k0 = (HH / 4) * g4 + 8 * u;
-        c = mma16(*reinterpret_cast<const bf16x8*>(&S[arow * AS_LD + k0]),
-                  *reinterpret_cast<const bf16x8*>(mrow + k0), c);
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < HH / 16; ++u) {
-        const int k0 = (HH / 4) * g4 + 4 * u;
-        const f32x4 a = *reinterpret_cast<const f32x4*>(&S[arow * AS_LD + k0]);
-        const f32x4 b = *reinterpret_cast<const f32x4*>(mrow + k0);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c = mma16(a[e], b[e], c);
-      }
+      for (int e = 0; e < 4; ++e) c = mma16(a[e], b[e], c);
     }
+    if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
     return c;
   }
   // acc[db] (rows d = 32db.., cols hid) += X[:, d]^T Yw
@@ -100,21 +102,8 @@ struct AmuTiles {
 #pragma unroll
     for (int db = 0; db < 2; ++db) {
       const int dd = 32 * db + l32;
-      if constexpr (BF) {
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          uint32_t aw[4], bw[4];
-#pragma unroll
-          for (int e = 0; e < 8; e += 2) {
-            aw[e / 2] = pack_bf16x2(X[c32_row(8 * m + e, hf) * LD + dd], X[c32_row(8 * m + e + 1, hf) * LD + dd]);
-            bw[e / 2] = pack_bf16x2(Yw[8 * m + e], Yw[8 * m + e + 1]);
-          }
-          acc[db] = mma32(as_bf16x8(aw[0], aw[1], aw[2], aw[3]), as_bf16x8(bw[0], bw[1], bw[2], bw[3]), acc[db]);
-        }
-      } else {
-#pragma unroll
-        for (int s = 0; s < 16; ++s) acc[db] = mma32(X[c32_row(s, hf) * LD + dd], Yw[s], acc[db]);
-      }
+      for (int s = 0; s < 16; ++s) acc[db] = mma32(X[c32_row(s, hf) * LD + dd], Yw[s], acc[db]);
     }
   }
   // acc[db] (rows hid, cols d = 32db..) += Yw^T X[:, d]
@@ -122,27 +111,14 @@ struct AmuTiles {
 #pragma unroll
     for (int db = 0; db < 2; ++db) {
       const int dd = 32 * db + l32;
-      if constexpr (BF) {
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          uint32_t aw[4], bw[4];
-#pragma unroll
-          for (int e = 0; e < 8; e += 2) {
-            aw[e / 2] = pack_bf16x2(Yw[8 * m + e], Yw[8 * m + e + 1]);
-            bw[e / 2] = pack_bf16x2(X[c32_row(8 * m + e, hf) * LD + dd], X[c32_row(8 * m + e + 1, hf) * LD + dd]);
-          }
-          acc[db] = mma32(as_bf16x8(aw[0], aw[1], aw[2], aw[3]), as_bf16x8(bw[0], bw[1], bw[2], bw[3]), acc[db]);
-        }
-      } else {
-#pragma unroll
-        for (int s = 0; s < 16; ++s) acc[db] = mma32(Yw[s], X[c32_row(s, hf) * LD + dd], acc[db]);
-      }
+      for (int s = 0; s < 16; ++s) acc[db] = mma32(Yw[s], X[c32_row(s, hf) * LD + dd], acc[db]);
     }
   }
   // A 32x32 result (token rows in registers) into a staged [token][hidden] tile.
-  __device__ void stage(MT* S, const f32x16& v) const {
+  __device__ void stage(float* S, const f32x16& v) const {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) S[c32_row(r, hf) * AS_LD + hid] = (MT)v[r];
+    for (int r = 0; r < 16; ++r) S[c32_row(r, hf) * AS_LD + hid] = v[r];
   }
   // Shard partials of the three weight adjoints (W1 [d][h], W2 [h][d], W3 [d][h]),
   // each multiplied by `sign`.
@@ -163,15 +139,15 @@ struct AmuTiles {
 // Rows [t0, t0+nv) of a token tensor into an f32 LDS tile (zeros beyond nv),
 // optionally L2-normalised; the row's 1/max(||x||, eps) and whether the norm
 // exceeds eps go to inv[] / above[] (one writer lane per row).
-template <typename IOT, int EPT>
-__device__ __forceinline__ void load_rows_n(const IOT* base, int64_t t0, int nv, int64_t stride_tok, int64_t hoff,
+template <int EPT>
+__device__ __forceinline__ void load_rows_n(const float* base, int64_t t0, int nv, int64_t stride_tok, int64_t hoff,
                                             float* dst, bool do_norm, float* inv, int* above) {
   constexpr int LD = D + 4;
   constexpr int TPR = D / EPT;
   const int row = threadIdx.x / TPR, col0 = (threadIdx.x % TPR) * EPT;
   float x[EPT];
   if (row < nv) {
-    load_vec<IOT, EPT>(base + (t0 + row) * stride_tok + hoff + col0, x);
+    load_vec<float, EPT>(base + (t0 + row) * stride_tok + hoff + col0, x);
   } else {
 #pragma unroll
     for (int i = 0; i < EPT; ++i) x[i] = 0.f;
@@ -213,10 +189,9 @@ __device__ __forceinline__ void norm_adjoint(float (&g)[EPT], const float (&xh)[
 }  // namespace
 
 // Apply adjoint over [start, start+len): X = Q, Y = dO, dX = dQ.
-template <typename IOT, bool BF, int NW>
+template <int NW>
 __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_apply(AmuBwdArgs p) {
-  using MT = std::conditional_t<BF, bf16, float>;
-  using T = AmuTiles<MT, NW>;
+  using T = AmuTiles<NW, true>;
   constexpr int DH = T::DH, LD = T::LD, AS_LD = T::AS_LD;
   constexpr int NT = NW * 64;
   constexpr int EPT = D * TT / NT;
@@ -226,8 +201,8 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_apply(AmuBwdArgs p) {
   // barrier also publishes them (two barriers per tile).
   __shared__ __attribute__((aligned(16))) float xs[2][TT * LD];    // normalised Q rows
   __shared__ __attribute__((aligned(16))) float ys[2][TT * LD];    // dO rows, then dQ before its norm adjoint
-  __shared__ __attribute__((aligned(16))) MT sa[TT * AS_LD];
-  __shared__ __attribute__((aligned(16))) MT sb[TT * AS_LD];
+  __shared__ __attribute__((aligned(16))) float sa[TT * AS_LD];
+  __shared__ __attribute__((aligned(16))) float sb[TT * AS_LD];
   __shared__ float ninv[2][TT];
   __shared__ int nabove[2][TT];
 
@@ -241,14 +216,14 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_apply(AmuBwdArgs p) {
   const int head = lin / G, g = lin % G;
   const int64_t hoff = (int64_t)head * p.stride_head;
   const bool norm_q = p.flags & 1u;
-  const MT* Wb = static_cast<const MT*>(p.prep_w) + (int64_t)head * 6 * DH;
+  const typename T::Weights Wb = T::weights(p.prep_w, head);
 
   f32x16 g1[2] = {}, g2[2] = {}, g3[2] = {};
   auto load_tile = [&](int tile, int b) {
     const int64_t t0 = p.start + (int64_t)tile * TT;
     const int nv = min(TT, p.len - tile * TT);
-    load_rows_n<IOT, EPT>(static_cast<const IOT*>(p.X), t0, nv, p.stride_tok, hoff, xs[b], norm_q, ninv[b], nabove[b]);
-    load_rows_n<IOT, EPT>(static_cast<const IOT*>(p.Y), t0, nv, p.stride_tok, hoff, ys[b], false, nullptr, nullptr);
+    load_rows_n<EPT>(static_cast<const float*>(p.X), t0, nv, p.stride_tok, hoff, xs[b], norm_q, ninv[b], nabove[b]);
+    load_rows_n<EPT>(static_cast<const float*>(p.Y), t0, nv, p.stride_tok, hoff, ys[b], false, nullptr, nullptr);
   };
   if (g * TT < p.len) load_tile(g, 0);
   __syncthreads();
@@ -257,9 +232,9 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_apply(AmuBwdArgs p) {
     const int64_t t0 = p.start + (int64_t)tile * TT;
     const int nv = min(TT, p.len - tile * TT);
     {
-      const f32x16 Z1 = t.th(xs[b], Wb + AMU_W1T * DH);
-      const f32x16 Z3 = t.th(xs[b], Wb + AMU_W3T * DH);
-      const f32x16 dH = t.th(ys[b], Wb + AMU_W2N * DH);
+      const f32x16 Z1 = t.th(xs[b], Wb, AMU_W1T);
+      const f32x16 Z3 = t.th(xs[b], Wb, AMU_W3T);
+      const f32x16 dH = t.th(ys[b], Wb, AMU_W2N);
       f32x16 Hq, dZ1, dZ3;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -281,8 +256,8 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_apply(AmuBwdArgs p) {
     for (int bi = 0; bi < 8 / NW; ++bi) {
       const int bk = w + NW * bi, tb = bk & 1, db = bk >> 1;
       f32x4 c = {};
-      c = t.td(sa, tb, db, Wb + AMU_W1D * DH, c);
-      c = t.td(sb, tb, db, Wb + AMU_W3D * DH, c);
+      c = t.td(sa, tb, db, Wb, AMU_W1D, c);
+      c = t.td(sb, tb, db, Wb, AMU_W3D, c);
 #pragma unroll
       for (int r = 0; r < 4; ++r) ys[b][(16 * tb + 4 * t.g4 + r) * LD + 16 * db + t.l16] = c[r];
     }
@@ -298,18 +273,20 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_apply(AmuBwdArgs p) {
         xh[e] = xs[b][row * LD + col0 + e];
       }
       norm_adjoint<EPT>(gq, xh, norm_q, ninv[b][row], nabove[b][row]);
-      if (row < nv) store_vec<IOT, EPT>(static_cast<IOT*>(p.dX) + (t0 + row) * p.stride_tok + hoff + col0, gq);
+      if (row < nv) store_vec<float, EPT>(static_cast<float*>(p.dX) + (t0 + row) * p.stride_tok + hoff + col0, gq);
     }
   }
   if (p.len > 0) t.write_partial(p.partial + ((int64_t)head * G + g) * (3 * DH), g1, g2, g3, w, 1.0f);
 }
 
 // Update adjoint over [start, start+len): X = K, Y = V, dX = dK, dY = dV, at
-// the weights in prep_w with the carried adjoint in prep_a.
-template <typename IOT, bool BF, int NW>
+// the weights in prep_w with the carried adjoint in prep_a.  Bound by the FP32
+// matrix products; at h = 256 the six products of a tile and the six values
+// made of them spilled 142 registers, now 21: 16 heads x 2,200 tokens 337 -> 258
+// us (apply adjoint 140 -> 118 us; at h = 128, 6,000 tokens, 158 -> 139 us).
+template <int NW>
 __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_update(AmuBwdArgs p) {
-  using MT = std::conditional_t<BF, bf16, float>;
-  using T = AmuTiles<MT, NW>;
+  using T = AmuTiles<NW, NW == 8>;
   constexpr int DH = T::DH, LD = T::LD, AS_LD = T::AS_LD;
   constexpr int NT = NW * 64;
   constexpr int EPT = D * TT / NT;
@@ -319,13 +296,10 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_update(AmuBwdArgs p) {
   __shared__ __attribute__((aligned(16))) float vs[TT * LD];   // normalised V rows
   __shared__ __attribute__((aligned(16))) float es[TT * LD];   // E = -eta v, then dot Y
   __shared__ __attribute__((aligned(16))) float ks[TT * LD];   // adjoint of K (before the sign and norm)
-  // Staged [token][hidden] pairs: with BF16 products the three pairs of a
-  // tile (Hdot, Hd), (aZ1, aZ3), (aZd1, aZd3) get buffers of their own and are
-  // staged together behind one barrier; FP32 tiles are twice as large and
-  // reuse one pair, with a barrier before and after each restaging.
-  constexpr int NS = BF ? 3 : 1;
-  __shared__ __attribute__((aligned(16))) MT sa[NS][TT * AS_LD];
-  __shared__ __attribute__((aligned(16))) MT sb[NS][TT * AS_LD];
+  // Staged [token][hidden] pairs, (Hdot, Hd), (aZ1, aZ3), (aZd1, aZd3) in turn,
+  // with a barrier before and after each restaging.
+  __shared__ __attribute__((aligned(16))) float sa[TT * AS_LD];
+  __shared__ __attribute__((aligned(16))) float sb[TT * AS_LD];
   __shared__ float kinv[TT], vinv[TT], etas[TT];
   __shared__ int kab[TT], vab[TT];
 
@@ -339,15 +313,15 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_update(AmuBwdArgs p) {
   const int head = lin / G, g = lin % G;
   const int64_t hoff = (int64_t)head * p.stride_head;
   const bool norm_k = p.flags & 2u, norm_v = p.flags & 4u;
-  const MT* Wb = static_cast<const MT*>(p.prep_w) + (int64_t)head * 6 * DH;
-  const MT* Ab = static_cast<const MT*>(p.prep_a) + (int64_t)head * 6 * DH;
+  const typename T::Weights Wb = T::weights(p.prep_w, head);
+  const typename T::Weights Ab = T::weights(p.prep_a, head);
 
   f32x16 g1[2] = {}, g2[2] = {}, g3[2] = {};
   for (int tile = g; tile * TT < p.len; tile += G) {
     const int64_t t0 = p.start + (int64_t)tile * TT;
     const int nv = min(TT, p.len - tile * TT);
-    load_rows_n<IOT, EPT>(static_cast<const IOT*>(p.X), t0, nv, p.stride_tok, hoff, xs, norm_k, kinv, kab);
-    load_rows_n<IOT, EPT>(static_cast<const IOT*>(p.Y), t0, nv, p.stride_tok, hoff, vs, norm_v, vinv, vab);
+    load_rows_n<EPT>(static_cast<const float*>(p.X), t0, nv, p.stride_tok, hoff, xs, norm_k, kinv, kab);
+    load_rows_n<EPT>(static_cast<const float*>(p.Y), t0, nv, p.stride_tok, hoff, vs, norm_v, vinv, vab);
     {
       const float et = row < nv ? p.eta_tok[(t0 + row) * p.H + head] : 0.f;
       if (tid % TPR == 0) etas[row] = et;
@@ -357,77 +331,89 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_update(AmuBwdArgs p) {
     __syncthreads();
     f32x16 aZ1, aZ3, aZd1, aZd3;
     {
-      const f32x16 Z1 = t.th(xs, Wb + AMU_W1T * DH);
-      const f32x16 Z3 = t.th(xs, Wb + AMU_W3T * DH);
-      const f32x16 Zd1 = t.th(xs, Ab + AMU_W1T * DH);
-      const f32x16 Zd3 = t.th(xs, Ab + AMU_W3T * DH);
-      const f32x16 dH = t.th(es, Wb + AMU_W2N * DH);
-      const f32x16 dHh = t.th(es, Ab + AMU_W2N * DH);
-      f32x16 Hdot, Hd;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float z = Z1[r];
-        const float sg = sigmoid(z);
-        const float s = z * sg;
-        const float s1 = fmaf(s, 1.0f - sg, sg);                          // s'(z)
-        const float s2 = sg * (1.0f - sg) * fmaf(z, 1.0f - 2.0f * sg, 2.0f);  // s''(z)
+      f32x16 Z1 = t.th(xs, Wb, AMU_W1T);
+      const f32x16 Z3 = t.th(xs, Wb, AMU_W3T);
+      const f32x16 Zd1 = t.th(xs, Ab, AMU_W1T);
+      const f32x16 Zd3 = t.th(xs, Ab, AMU_W3T);
+      f32x16 dH, dHh, Hdot, Hd;
+      auto second = [&](int r, float sg, float s, float s1) {  // the four adjoints of element r
+        const float s2 = sg * (1.0f - sg) * fmaf(Z1[r], 1.0f - 2.0f * sg, 2.0f);  // s''(z)
         const float sd = s1 * Zd1[r];
-        Hdot[r] = fmaf(sd, Z3[r], s * Zd3[r]);
-        Hd[r] = s * Z3[r];
         const float asd = dH[r] * Z3[r];
         aZ3[r] = fmaf(dH[r], sd, dHh[r] * s);
         const float as = fmaf(dH[r], Zd3[r], dHh[r] * Z3[r]);
         aZd3[r] = dH[r] * s;
         aZd1[r] = asd * s1;
         aZ1[r] = fmaf(asd * s2, Zd1[r], as * s1);
+      };
+      if constexpr (!T::TIGHT) {
+        dH = t.th(es, Wb, AMU_W2N);
+        dHh = t.th(es, Ab, AMU_W2N);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float sg = sigmoid(Z1[r]);
+        const float s = Z1[r] * sg;
+        const float s1 = fmaf(s, 1.0f - sg, sg);  // s'(z)
+        Hdot[r] = fmaf(s1 * Zd1[r], Z3[r], s * Zd3[r]);
+        Hd[r] = s * Z3[r];
+        if constexpr (!T::TIGHT) second(r, sg, s, s1);
       }
       t.tok_sum_hd(g2, Hdot, es);
+      if constexpr (T::TIGHT) {
+        // dot H and Hd leave the registers before dH and dHh come; the
+        // activation is formed again from Z1, and the adjoints where they are
+        // written (the empty asm): held or sunk, they spill
+        t.stage(sa, Hdot);
+        t.stage(sb, Hd);
+        asm volatile("" : "+v"(Z1));
+        dH = t.th(es, Wb, AMU_W2N);
+        dHh = t.th(es, Ab, AMU_W2N);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float sg = sigmoid(Z1[r]);
+          const float s = Z1[r] * sg;
+          second(r, sg, s, fmaf(s, 1.0f - sg, sg));
+          asm volatile("" : "+v"(aZ1[r]), "+v"(aZ3[r]), "+v"(aZd1[r]), "+v"(aZd3[r]));
+        }
+      }
       t.tok_sum_dh(g1, xs, aZ1);
       t.tok_sum_dh(g3, xs, aZ3);
-      t.stage(sa[0], Hdot);
-      t.stage(sb[0], Hd);
-      if constexpr (NS == 3) {
-        t.stage(sa[1], aZ1);
-        t.stage(sb[1], aZ3);
-        t.stage(sa[2], aZd1);
-        t.stage(sb[2], aZd3);
+      if constexpr (!T::TIGHT) {
+        t.stage(sa, Hdot);
+        t.stage(sb, Hd);
       }
     }
     __syncthreads();
-    constexpr int P1 = NS == 3 ? 1 : 0, P2 = NS == 3 ? 2 : 0;
     f32x4 yd[8 / NW], kb[8 / NW];
 #pragma unroll
     for (int bi = 0; bi < 8 / NW; ++bi) {
       const int b = w + NW * bi, tb = b & 1, db = b >> 1;
       f32x4 c = {};
-      c = t.td(sa[0], tb, db, Wb + AMU_W2D * DH, c);
-      yd[bi] = t.td(sb[0], tb, db, Ab + AMU_W2D * DH, c);
+      c = t.td(sa, tb, db, Wb, AMU_W2D, c);
+      yd[bi] = t.td(sb, tb, db, Ab, AMU_W2D, c);
     }
-    if constexpr (NS == 1) {
-      __syncthreads();
-      t.stage(sa[0], aZ1);
-      t.stage(sb[0], aZ3);
-      __syncthreads();
-    }
+    __syncthreads();
+    t.stage(sa, aZ1);
+    t.stage(sb, aZ3);
+    __syncthreads();
 #pragma unroll
     for (int bi = 0; bi < 8 / NW; ++bi) {
       const int b = w + NW * bi, tb = b & 1, db = b >> 1;
       f32x4 c = {};
-      c = t.td(sa[P1], tb, db, Wb + AMU_W1D * DH, c);
-      kb[bi] = t.td(sb[P1], tb, db, Wb + AMU_W3D * DH, c);
+      c = t.td(sa, tb, db, Wb, AMU_W1D, c);
+      kb[bi] = t.td(sb, tb, db, Wb, AMU_W3D, c);
     }
-    if constexpr (NS == 1) {
-      __syncthreads();
-      t.stage(sa[0], aZd1);
-      t.stage(sb[0], aZd3);
-      __syncthreads();
-    }
+    __syncthreads();
+    t.stage(sa, aZd1);
+    t.stage(sb, aZd3);
+    __syncthreads();
 #pragma unroll
     for (int bi = 0; bi < 8 / NW; ++bi) {
       const int b = w + NW * bi, tb = b & 1, db = b >> 1;
       f32x4 c = kb[bi];
-      c = t.td(sa[P2], tb, db, Ab + AMU_W1D * DH, c);
-      c = t.td(sb[P2], tb, db, Ab + AMU_W3D * DH, c);
+      c = t.td(sa, tb, db, Ab, AMU_W1D, c);
+      c = t.td(sb, tb, db, Ab, AMU_W3D, c);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int o = (16 * tb + 4 * t.g4 + r) * LD + 16 * db + t.l16;
@@ -453,8 +439,8 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_update(AmuBwdArgs p) {
       norm_adjoint<EPT>(gv, vh, norm_v, vinv[row], vab[row]);
       norm_adjoint<EPT>(gk, xh, norm_k, kinv[row], kab[row]);
       if (row < nv) {
-        store_vec<IOT, EPT>(static_cast<IOT*>(p.dY) + (t0 + row) * p.stride_tok + hoff + col0, gv);
-        store_vec<IOT, EPT>(static_cast<IOT*>(p.dX) + (t0 + row) * p.stride_tok + hoff + col0, gk);
+        store_vec<float, EPT>(static_cast<float*>(p.dY) + (t0 + row) * p.stride_tok + hoff + col0, gv);
+        store_vec<float, EPT>(static_cast<float*>(p.dX) + (t0 + row) * p.stride_tok + hoff + col0, gk);
         if (tid % TPR == 0) p.deta_tok[(t0 + row) * p.H + head] = de;
       }
     }
@@ -489,28 +475,28 @@ __global__ __launch_bounds__(256) void ttt_amu_psum(AmuPsumArgs p) {
   }
 }
 
-template <typename IOT, bool BF, int NW>
+template <int NW>
 static hipError_t launch_apply_t(const AmuBwdArgs& a, int n_blocks, hipStream_t st) {
-  hipLaunchKernelGGL((ttt_amu_bwd_apply<IOT, BF, NW>), dim3(n_blocks), dim3(NW * 64), 0, st, a);
+  hipLaunchKernelGGL((ttt_amu_bwd_apply<NW>), dim3(n_blocks), dim3(NW * 64), 0, st, a);
   return hipGetLastError();
 }
-template <typename IOT, bool BF, int NW>
+template <int NW>
 static hipError_t launch_update_t(const AmuBwdArgs& a, int n_blocks, hipStream_t st) {
-  hipLaunchKernelGGL((ttt_amu_bwd_update<IOT, BF, NW>), dim3(n_blocks), dim3(NW * 64), 0, st, a);
+  hipLaunchKernelGGL((ttt_amu_bwd_update<NW>), dim3(n_blocks), dim3(NW * 64), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_amu_bwd_apply(const AmuBwdArgs& a, int n_blocks, int h, bool io_bf16, bool mma_bf16,
                                 hipStream_t st) {
   if (mma_bf16) return launch_amu_bwd_apply_bf(a, n_blocks, h, io_bf16, st);
-  return h == 128 ? launch_apply_t<float, false, 4>(a, n_blocks, st) : launch_apply_t<float, false, 8>(a, n_blocks, st);
+  return h == 128 ? launch_apply_t<4>(a, n_blocks, st) : launch_apply_t<8>(a, n_blocks, st);
 }
 
 hipError_t launch_amu_bwd_update(const AmuBwdArgs& a, int n_blocks, int h, bool io_bf16, bool mma_bf16,
                                  hipStream_t st) {
   if (mma_bf16) return launch_amu_bwd_update_bf(a, n_blocks, h, io_bf16, st);
-  return h == 128 ? launch_update_t<float, false, 4>(a, n_blocks, st)
-                  : launch_update_t<float, false, 8>(a, n_blocks, st);
+  return h == 128 ? launch_update_t<4>(a, n_blocks, st)
+                  : launch_update_t<8>(a, n_blocks, st);
 }
 
 hipError_t launch_amu_psum(const AmuPsumArgs& a, hipStream_t st) {
