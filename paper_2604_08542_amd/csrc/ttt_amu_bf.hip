@@ -22,7 +22,7 @@ namespace ttt {
 namespace {
 
 template <typename IOT, int NW>
-__global__ __launch_bounds__(NW * 64) void ttt_amu_step_bf(AmuStepArgs p) {
+__global__ __launch_bounds__(NW * 64, 2) void ttt_amu_step_bf(AmuStepArgs p) {
   constexpr int HH = NW * 32, NT = NW * 64, EPT = D * TT / NT, TPR = D / EPT, DH = D * HH;
   constexpr int AS_LD = HH + 8;
   // two copies of the row tiles, one barrier per tile: a copy is rewritten

@@ -355,9 +355,10 @@ __global__ __launch_bounds__(256) void ttt_amu_bwd_tokens_bf(AmuBwdArgs p) {
   }
 }
 
-// Apply adjoint: X = Q, Y = dO, dX = dQ.
+// Apply adjoint: X = Q, Y = dO, dX = dQ.  Two waves per SIMD: at h = 128 two
+// work-groups per CU (16 heads x 6,000 tokens 44 -> 37 us).
 template <typename IOT, int NW>
-__global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_apply_bf(AmuBwdArgs p) {
+__global__ __launch_bounds__(NW * 64, 2) void ttt_amu_bwd_apply_bf(AmuBwdArgs p) {
   constexpr int HH = NW * 32, NT = NW * 64, EPT = D * TT / NT, TPR = D / EPT, DH = D * HH;
   constexpr int AS_LD = HH + 8, FLD = D + 4, NU = HH / 32, NBK = 8 / NW;
   __shared__ __attribute__((aligned(16))) bf16 xs[2][TT * XLD];
