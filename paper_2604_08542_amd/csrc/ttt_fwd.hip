@@ -61,19 +61,6 @@ __device__ __forceinline__ void fwd_body_f32(const StepCtx& p) {
   const float* W1 = p.W1;
   const float* W2 = p.W2;
 
-  // B operand of Y = A W2 over the full hidden axis, from LDS (W2^T).
-  for (int idx = tid; idx < DH; idx += NT) {
-    const int hh = idx / D, dd = idx % D;
-    w2t[dd * W2T_LD + hh] = W2[idx];
-  }
-  // Register-resident operand slices of this wave's hidden block.
-  float w1f[32], w2f[32];
-#pragma unroll
-  for (int s = 0; s < 32; ++s) {
-    w1f[s] = W1[(32 * hf + s) * HH + hid];
-    w2f[s] = W2[hid * D + 32 * hf + s];
-  }
-
   const bool norm_q = p.flags & 1u, norm_k = p.flags & 2u, norm_v = p.flags & 4u;
   const int row = tid / TPR, col0 = (tid % TPR) * EPT;
   const int64_t hoff = (int64_t)head * p.stride_head;
@@ -106,6 +93,37 @@ __device__ __forceinline__ void fwd_body_f32(const StepCtx& p) {
 #pragma unroll
     for (int i = 0; i < EPT; ++i) x[i] *= inv;
   };
+  // The rows of the first tile, W2 for LDS and this wave's operand slices are
+  // all requested before the first is used: with one tile per work-group (43
+  // work-groups, h = 128) the step is latency, 18.8 us with the loads in a row,
+  // 14.0 us so.
+  float rk[EPT], rv[EPT], rq[EPT];
+  if (my_g > 0) {
+    fetch_row(p.K, gs, gl, 0, rk);
+    fetch_row(p.V, gs, gl, 0, rv);
+  } else if (my_a > 0) {
+    fetch_row(p.Q, as0, al, 0, rq);
+  }
+  constexpr int N4 = DH / 4 / NT;  // float4s of W2 per thread
+  f32x4 w2r[N4];
+#pragma unroll
+  for (int n = 0; n < N4; ++n) w2r[n] = *reinterpret_cast<const f32x4*>(W2 + 4 * (n * NT + tid));
+  // Register-resident operand slices of this wave's hidden block.
+  float w1f[32], w2f[32];
+#pragma unroll
+  for (int s = 0; s < 32; ++s) {
+    w1f[s] = W1[(32 * hf + s) * HH + hid];
+    w2f[s] = W2[hid * D + 32 * hf + s];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  // B operand of Y = A W2 over the full hidden axis, from LDS (W2^T).
+#pragma unroll
+  for (int n = 0; n < N4; ++n) {
+    const int idx = 4 * (n * NT + tid), hh = idx / D, dd = idx % D;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w2t[(dd + e) * W2T_LD + hh] = w2r[n][e];
+  }
+
   // Z = X W1 for this wave's hidden block: 32x32 result, rows = tokens.
   auto z_block = [&](const float* X) {
     f32x16 z = {};
@@ -214,13 +232,7 @@ __device__ __forceinline__ void fwd_body_f32(const StepCtx& p) {
 
   f32x16 gw1[2] = {}, gw2[2] = {};
   float lacc = 0.f;
-  float rk[EPT], rv[EPT], rq[EPT];
 
-  // gradient tiles
-  if (my_g > 0) {
-    fetch_row(p.K, gs, gl, 0, rk);
-    fetch_row(p.V, gs, gl, 0, rv);
-  }
   for (int it = 0; it < my_g; ++it) {
     stage_kv(rk, rv);
     if (it + 1 < my_g) {
@@ -238,7 +250,7 @@ __device__ __forceinline__ void fwd_body_f32(const StepCtx& p) {
     __syncthreads();
   }
   // apply tiles
-  if (my_a > 0) fetch_row(p.Q, as0, al, 0, rq);
+  if (my_g > 0 && my_a > 0) fetch_row(p.Q, as0, al, 0, rq);
   for (int it = 0; it < my_a; ++it) {
     normalise(rq, norm_q);
 #pragma unroll
@@ -762,17 +774,30 @@ __global__ __launch_bounds__(256) void ttt_update(UpdStepArgs p) {
       for (int e = 0; e < n_ent; ++e) {
         const int64_t sl = gcs ? (int64_t)e * p.H + head : slot;
         const f32x4* part = reinterpret_cast<const f32x4*>(p.partial + sl * p.G * 2 * dh) + i4;
-        int gg = q;
-        for (; gg + 28 < g4; gg += 32) {  // 8 loads in flight, added in shard order
+        // the shards past the last multiple of 4, for stream 0
+        const int nr = q == 0 ? p.G - g4 : 0;
+        f32x4 r[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) r[j] = part[(int64_t)(g4 < p.G ? min(g4 + j, p.G - 1) : 0) * n4];
+        // 8 loads in flight (past the stream's end: of its last shard, not
+        // added), added in shard order.  Before, only full eights were loaded
+        // together and the rest one by one: of 282 shards a chain of 8 chunks of
+        // 9,000 tokens, h = 128, takes 370 us against 399.
+        for (int gg = q; gg < g4; gg += 32) {
           f32x4 v[8];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) v[j] = part[(int64_t)(gg + 4 * j) * n4];
+          for (int j = 0; j < 8; ++j) v[j] = part[(int64_t)min(gg + 4 * j, g4 - 4 + q) * n4];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) sq += v[j];
+          for (int j = 0; j < 8; ++j) {
+            const f32x4 a = sq + v[j];
+            sq = gg + 4 * j < g4 ? a : sq;
+          }
         }
-        for (; gg < g4; gg += 4) sq += part[(int64_t)gg * n4];
-        if (q == 0)
-          for (gg = g4; gg < p.G; ++gg) sq += part[(int64_t)gg * n4];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          const f32x4 a = sq + r[j];
+          sq = j < nr ? a : sq;
+        }
       }
       f32x4 t;  // lanes 0 and 2: s0 + s1 and s2 + s3
 #pragma unroll
@@ -831,13 +856,13 @@ __global__ __launch_bounds__(256) void ttt_update(UpdStepArgs p) {
 // ----------------------------------------------------------------- step kernel
 // One chunk step for every active chain of a launch plan (one work-group per
 // (chain, token shard)); the partials are reduced by ttt_update.  At h = 128
-// with BF16 operands the body takes 277 registers when it is left to, one wave
-// per SIMD, and the 512 work-groups of a launch ran in two rounds; bounded to
-// 256 two work-groups share a CU: 16 heads x 6,000 tokens x 8 chunks 424 -> 347
-// us, all chunks synchronised 262 -> 183 us (FP32 rows, which spill: 431 -> 409
-// and 284 -> 238 us).
+// the body takes 277 registers when it is left to (FP32 operands: 264), one
+// wave per SIMD, and the 512 work-groups of a launch ran in two rounds; bounded
+// to 256 two work-groups share a CU: BF16, 16 heads x 6,000 tokens x 8 chunks 424
+// -> 347 us, all chunks synchronised 262 -> 183 us (BF16 products of FP32 rows,
+// which spill: 431 -> 409 and 284 -> 238 us).
 template <typename IOT, int NW, bool BF>
-__global__ __launch_bounds__(NW * 64, NW == 4 && BF ? 2 : 1) void ttt_fwd_step(FwdStepArgs p) {
+__global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void ttt_fwd_step(FwdStepArgs p) {
   constexpr int DH = D * NW * 32;
   const int lin = xcd_linear_block();
   const int slot = lin / p.G, g = lin % p.G;
