@@ -15,7 +15,8 @@
 //    reads those over d;
 //  - 8 waves, two per SIMD, so one's elementwise work overlaps the other's
 //    products.  A wave owns 32 hidden units; at h = 128 two groups of 4 waves
-//    share the matrices, each with a shard of its own;
+//    share the matrices, each with a shard of its own (one group, where the
+//    shards do not fill the CUs);
 //  - LDS is what is left beside them: the BF16 rows of K, E and dY (transposing
 //    reads give their columns) and one staged [token][hidden] tile that A, dP,
 //    D and dZ take in turn.  V and K enter the residual and the normalisation
@@ -45,10 +46,10 @@
 
 namespace ttt {
 
-template <typename IOT, int NW>
-__global__ __launch_bounds__(512) void ttt_bwd_step_bf(BwdStepArgs p) {
+template <typename IOT, int NW, int NG>
+__global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
   constexpr int HH = NW * 32, DH = D * HH;
-  constexpr int NG = 8 / NW;    // groups of NW waves, each with tiles of its own
+  constexpr int NT = NW * NG * 64;  // NG groups of NW waves, each with tiles of its own
   constexpr int RL = 80;        // pitch of a row tile: 64 features, 32 bytes of row data (see below)
   constexpr int SL = HH + 8;    // pitch of the staged [token][hidden] tile
   constexpr int NU = HH / 32;   // 16x16x32 products along the hidden axis
@@ -93,10 +94,10 @@ __global__ __launch_bounds__(512) void ttt_bwd_step_bf(BwdStepArgs p) {
   // rows x 64 bytes (contractions over d) over all banks; W1 and W2, which
   // multiply tokens in several products, also in registers.
   enum { W1 = 0, W2 = 1, WH1 = 2, WH2 = 3 };
-  bf16x8 wf[4 * DH / 4096];  // all requested before any is needed
+  bf16x8 wf[4 * DH / 8 / NT];  // all requested before any is needed
 #pragma unroll
-  for (int n = 0; n < 4 * DH / 4096; ++n)
-    wf[n] = *reinterpret_cast<const bf16x8*>(prep + 4 * DH + (512 * n + threadIdx.x) * 8);
+  for (int n = 0; n < 4 * DH / 8 / NT; ++n)
+    wf[n] = *reinterpret_cast<const bf16x8*>(prep + 4 * DH + (NT * n + threadIdx.x) * 8);
   // The wave's 16x16 output blocks: features 16 db .., token halves tb0 ..
   const int db16 = L.w & 3, tb0 = NBK == 2 ? 0 : L.w >> 2;
   // Those blocks of staged tile x matrix k, over the hidden axis.
@@ -262,8 +263,8 @@ __global__ __launch_bounds__(512) void ttt_bwd_step_bf(BwdStepArgs p) {
   fetch(p.K, p.V, grad_start, gl, g);
   load_elems(tile_rs(p.V, grad_start, gl, g), vr);
 #pragma unroll
-  for (int n = 0; n < 4 * DH / 4096; ++n) {
-    const int i = 512 * n + threadIdx.x, k = i / (DH / 8), d = (i / (HH / 8)) & (D - 1), c = i % (HH / 8);
+  for (int n = 0; n < 4 * DH / 8 / NT; ++n) {
+    const int i = NT * n + threadIdx.x, k = i / (DH / 8), d = (i / (HH / 8)) & (D - 1), c = i % (HH / 8);
     *reinterpret_cast<bf16x8*>(&wl[k][d * HH + 8 * (c ^ (4 * (d & 3) + ((d >> 2) & 3)))]) = wf[n];
   }
   stage_rows(true, 0);
@@ -513,17 +514,22 @@ __global__ __launch_bounds__(512) void ttt_bwd_step_bf(BwdStepArgs p) {
   }
 }
 
-template <typename IOT, int NW>
+template <typename IOT, int NW, int NG>
 static hipError_t launch_bwd_step_bf_t(const BwdStepArgs& a, int n_blocks, hipStream_t st) {
-  constexpr int NG = 8 / NW;
-  hipLaunchKernelGGL((ttt_bwd_step_bf<IOT, NW>), dim3(n_blocks / a.G * ((a.G + NG - 1) / NG)), dim3(512), 0, st, a);
+  hipLaunchKernelGGL((ttt_bwd_step_bf<IOT, NW, NG>), dim3(n_blocks / a.G * ((a.G + NG - 1) / NG)), dim3(NW * NG * 64), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_step_bf(const BwdStepArgs& a, int n_blocks, int h, bool io_bf16, hipStream_t st) {
-  if (h == 128)
-    return io_bf16 ? launch_bwd_step_bf_t<bf16, 4>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 4>(a, n_blocks, st);
-  return io_bf16 ? launch_bwd_step_bf_t<bf16, 8>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 8>(a, n_blocks, st);
+  if (h == 128) {
+    // Up to one shard per CU each has a work-group of its own, past that two
+    // share one: 160 shards of one tile 14.2 against 16.2 us, 352 shards 18.5
+    // shared (22.4 for one work-group per shard without matrices in LDS).
+    if (n_blocks <= 256)
+      return io_bf16 ? launch_bwd_step_bf_t<bf16, 4, 1>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 4, 1>(a, n_blocks, st);
+    return io_bf16 ? launch_bwd_step_bf_t<bf16, 4, 2>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 4, 2>(a, n_blocks, st);
+  }
+  return io_bf16 ? launch_bwd_step_bf_t<bf16, 8, 1>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 8, 1>(a, n_blocks, st);
 }
 
 }  // namespace ttt

@@ -1,7 +1,8 @@
 """The BF16 reverse step of the MSE unit where its tiles and shards can go
 wrong: tokens around the 32-token tile, shards without a tile, an odd number of
-shards (two share a work-group at h = 128), both hidden sizes, float32 and
-bfloat16 tokens.  Against the FP64 oracle at the BF16 gate of the other parity
+shards (at h = 128 two share a work-group when there are more than 256: the last
+two cases, 304 shards, 19 per head), both hidden sizes, float32 and bfloat16
+tokens.  Against the FP64 oracle at the BF16 gate of the other parity
 tests.  d(eta) is left to those: over a few dozen tokens its terms cancel, and
 BF16 products alone then move it by more than the gate."""
 import pytest
@@ -20,6 +21,8 @@ pytestmark = pytest.mark.gpu
     (289, 96, 2, 128, "bf16"),
     (700, 225, 2, 128, "f32"),
     (1700, 600, 16, 256, "bf16"),
+    (1300, 600, 16, 128, "f32"),
+    (1300, 600, 16, 128, "bf16"),
 ])
 def test_reverse_step(gpu, N, M, H, h, io):
     from paper_2604_08542_amd import ops
