@@ -365,23 +365,49 @@ __device__ __forceinline__ void fwd_body_bf(const StepCtx& p) {
     asm volatile("" : "+v"(u));
     v = __builtin_bit_cast(bf16x8, u);
   };
+  if constexpr (NW == 4) {
+    // h = 128, where chains of few tiles a step run: all elements are requested
+    // before the first is packed (a step of one tile 11.1 -> 10.4 us; one head,
+    // 256 chunks of 1,374 tokens 3.87 -> 3.73 ms).  At h = 256 the compiler's own
+    // order is faster (16 heads, 64 frames: 694 against 711 us).
+    float r1[32], r2[32], ry[2][32];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    uint32_t a[4], b[4];
+    for (int k = 0; k < 32; ++k) {
+      r1[k] = W1[(16 * (k / 8) + 8 * hf + k % 8) * HH + hid];
+      r2[k] = W2[hid * D + 16 * (k / 8) + 8 * hf + k % 8];
 #pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      a[e / 2] = pack_bf16x2(-LOG2E * W1[(16 * m + 8 * hf + e) * HH + hid],
-                             -LOG2E * W1[(16 * m + 8 * hf + e + 1) * HH + hid]);
-      b[e / 2] = pack_bf16x2(W2[hid * D + 16 * m + 8 * hf + e], W2[hid * D + 16 * m + 8 * hf + e + 1]);
+      for (int bi = 0; bi < 2; ++bi) ry[bi][k] = W2[(32 * g4 + k) * D + 16 * ((w + 4 * bi) >> 1) + l16];
     }
-    w1b[m] = as_bf16x8(a[0], a[1], a[2], a[3]);
-    w2b[m] = as_bf16x8(b[0], b[1], b[2], b[3]);
-    pin8(w1b[m]);
-    pin8(w2b[m]);
-  }
+    __builtin_amdgcn_sched_barrier(0);
+    auto pack8 = [&](const float* r, float f) {
+      bf16x8 v = as_bf16x8(pack_bf16x2(f * r[0], f * r[1]), pack_bf16x2(f * r[2], f * r[3]),
+                           pack_bf16x2(f * r[4], f * r[5]), pack_bf16x2(f * r[6], f * r[7]));
+      pin8(v);
+      return v;
+    };
 #pragma unroll
-  for (int bi = 0; bi < 8 / NW; ++bi) {
-    const int dcol = 16 * ((w + NW * bi) >> 1) + l16;
+    for (int m = 0; m < 4; ++m) {
+      w1b[m] = pack8(r1 + 8 * m, -LOG2E);
+      w2b[m] = pack8(r2 + 8 * m, 1.0f);
+#pragma unroll
+      for (int bi = 0; bi < 2; ++bi) w2y[bi][m] = pack8(ry[bi] + 8 * m, -LN2);
+    }
+  } else {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      uint32_t a[4], b[4];
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        a[e / 2] = pack_bf16x2(-LOG2E * W1[(16 * m + 8 * hf + e) * HH + hid],
+                               -LOG2E * W1[(16 * m + 8 * hf + e + 1) * HH + hid]);
+        b[e / 2] = pack_bf16x2(W2[hid * D + 16 * m + 8 * hf + e], W2[hid * D + 16 * m + 8 * hf + e + 1]);
+      }
+      w1b[m] = as_bf16x8(a[0], a[1], a[2], a[3]);
+      w2b[m] = as_bf16x8(b[0], b[1], b[2], b[3]);
+      pin8(w1b[m]);
+      pin8(w2b[m]);
+    }
+    const int dcol = 16 * (w >> 1) + l16;
 #pragma unroll
     for (int u = 0; u < HH / 32; ++u) {
       uint32_t c[4];
@@ -389,8 +415,8 @@ __device__ __forceinline__ void fwd_body_bf(const StepCtx& p) {
       for (int e = 0; e < 8; e += 2)
         c[e / 2] = pack_bf16x2(-LN2 * W2[((HH / 4) * g4 + 8 * u + e) * D + dcol],
                                -LN2 * W2[((HH / 4) * g4 + 8 * u + e + 1) * D + dcol]);
-      w2y[bi][u] = as_bf16x8(c[0], c[1], c[2], c[3]);
-      pin8(w2y[bi][u]);
+      w2y[0][u] = as_bf16x8(c[0], c[1], c[2], c[3]);
+      pin8(w2y[0][u]);
     }
   }
 
