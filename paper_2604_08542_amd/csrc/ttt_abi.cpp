@@ -1114,13 +1114,17 @@ ttt_status_t backward_large_seq(const ttt_problem_t* p, const Shape& S, const La
       a.W1 = W1; a.W2 = W2; a.W1op = at<char>(ws, L.f.W1op); a.W2op = at<char>(ws, L.f.W2op);
       a.loss_part = at<float>(ws, L.f.loss_part);
       if (!launched([&] { return launch_large_step(a, S.io_bf16, S.mma_bf16, st); })) return TTT_EHIP;
-      if (!cast(W1, L.W1nop) || !cast(W2, L.W2nop)) return TTT_EHIP;
     }
+    // Operand copies of W_{c+1}: the forward step's (W_C), then those of W_c of
+    // the chunk before, the two sets changing places.
+    size_t opn[2] = {L.f.W1op, L.f.W2op}, op[2] = {L.W1nop, L.W2nop};
     for (int64_t c = C - 1; c >= 0; --c) {
-      if (c + 1 < C && (!cast(row(c + 1), L.W1nop) || !cast(row(c + 1) + dh, L.W2nop))) return TTT_EHIP;
-      if (!cast(row(c), L.f.W1op) || !cast(row(c) + dh, L.f.W2op)) return TTT_EHIP;
+      if (!cast(row(c), op[0]) || !cast(row(c) + dh, op[1])) return TTT_EHIP;
       LargeBwdArgs b = large_bwd_args(p, S, L, ws, chunk_off(c), (int32_t)std::min<int64_t>(M, N - c * M), Q, K, V,
                                       dO, dQ, dK, dV);
+      b.W1op = at<char>(ws, op[0]); b.W2op = at<char>(ws, op[1]);
+      b.W1nop = at<char>(ws, opn[0]); b.W2nop = at<char>(ws, opn[1]);
+      std::swap(op, opn);
       b.Acc1 = Wh1; b.Acc2 = Wh2; b.Acc1op = b.Wh1op; b.Acc2op = b.Wh2op;
       b.apply = 1; b.update = 1;
       b.deta = dt;
@@ -1484,6 +1488,7 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
   if (!launched([&] { return launch_zero_words(at<uint32_t>(ws, L.f.sync) + SYNC_ERR, 1, st); })) return TTT_EHIP;
   float* Wm[3] = {at<float>(ws, L.f.W1), at<float>(ws, L.f.W2), at<float>(ws, L.f.W3)};
   const size_t Wo[3] = {L.f.W1op, L.f.W2op, L.f.W3op};
+  size_t op[3] = {L.f.W1op, L.f.W2op, L.f.W3op}, opn[3] = {L.Wnop[0], L.Wnop[1], L.Wnop[2]};  // of W, W'
   const float* W0[3] = {W1_0, W2_0, W3_0};
   float* dW0[3] = {dW1_0, dW2_0, dW3_0};
   float* wl = at<float>(ws, L.wlist);
@@ -1516,7 +1521,7 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
       a.W1op = at<char>(ws, Wo[0]); a.W2op = at<char>(ws, Wo[1]); a.W3op = at<char>(ws, Wo[2]);
       return launched([&] { return launch_large_amu_step(a, S.io_bf16, S.mma_bf16, st); });
     };
-    // the reverse step of chunk c with W (operand copies in Wo) and W' (in Wnop)
+    // the reverse step of chunk c with W (operand copies in op) and W' (in opn)
     auto bwd_step = [&](int64_t c, bool apply, bool update, float* const* acc, bool acc_op) {
       const int64_t off = chunk_off(c);
       LargeAmuBwdArgs b{};
@@ -1544,8 +1549,8 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
       b.aZ1 = at<char>(ws, L.aZ1); b.aZ3 = at<char>(ws, L.aZ3); b.aZd1 = at<char>(ws, L.aZd1);
       b.aZd3 = at<char>(ws, L.aZd3);
       for (int m = 0; m < 3; ++m) {
-        b.Wop[m] = at<char>(ws, Wo[m]);
-        b.Wnop[m] = at<char>(ws, L.Wnop[m]);
+        b.Wop[m] = at<char>(ws, op[m]);
+        b.Wnop[m] = at<char>(ws, opn[m]);
         b.Wh[m] = at<float>(ws, L.Wh[m]);
         b.Whop[m] = at<char>(ws, L.Whop[m]);
         b.Acc[m] = acc[m];
@@ -1569,10 +1574,17 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
         for (int m = 0; m < 3; ++m)
           if (!copy(wl_at(c + 1, m), Wm[m])) return TTT_EHIP;
       }
+      // the forward steps left the operand copies of W_C in Wo; those of W_c
+      // serve chunk c - 1 as its W', the two sets changing places
+      for (int m = 0; m < 3; ++m) {
+        opn[m] = Wo[m];
+        op[m] = L.Wnop[m];
+      }
       for (int64_t c = C - 1; c >= 0; --c) {
         for (int m = 0; m < 3; ++m)
-          if (!cast(wl_at(c + 1, m), L.Wnop[m]) || !cast(wl_at(c, m), Wo[m])) return TTT_EHIP;
+          if (!cast(wl_at(c, m), op[m])) return TTT_EHIP;
         if (!bwd_step(c, true, true, Wh, true)) return TTT_EHIP;
+        std::swap(op, opn);
       }
     } else {
       for (int64_t c = 0; c < C; ++c)
