@@ -1501,8 +1501,9 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
   for (int64_t hd = 0; hd < H; ++hd) {
     auto chunk_off = [&](int64_t c) { return (c * M * S.stride_tok + hd * S.stride_head) * (int64_t)iob; };
     auto rows = [&](int64_t c) { return (int32_t)std::min<int64_t>(M, N - c * M); };
-    // a forward step of chunk c (the gradient and the update, no apply)
-    auto fwd_step = [&](int64_t c, bool write_op) {
+    // a forward step of chunk c (the gradient and the update, no apply), from
+    // the masters `from` to `to`
+    auto fwd_step = [&](int64_t c, bool write_op, float* const* from, float* const* to) {
       LargeAmuArgs a{};
       a.K = static_cast<const char*>(K) + chunk_off(c);
       a.V = static_cast<const char*>(V) + chunk_off(c);
@@ -1517,7 +1518,8 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
       a.Kn = at<char>(ws, L.f.Kn); a.Qn = at<char>(ws, L.f.Qn); a.E = at<char>(ws, L.f.E); a.Vn = at<float>(ws, L.f.Vn);
       a.Z3 = at<char>(ws, L.f.Z3); a.Hd = at<char>(ws, L.f.Hd); a.G1 = at<char>(ws, L.f.G1); a.G3 = at<char>(ws, L.f.G3);
       a.D1 = at<char>(ws, L.f.D1); a.D3 = at<char>(ws, L.f.D3);
-      a.W1 = Wm[0]; a.W2 = Wm[1]; a.W3 = Wm[2];
+      a.W1 = to[0]; a.W2 = to[1]; a.W3 = to[2];
+      a.from1 = from[0]; a.from2 = from[1]; a.from3 = from[2];
       a.W1op = at<char>(ws, Wo[0]); a.W2op = at<char>(ws, Wo[1]); a.W3op = at<char>(ws, Wo[2]);
       return launched([&] { return launch_large_amu_step(a, S.io_bf16, S.mma_bf16, st); });
     };
@@ -1562,17 +1564,16 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
     float* tot[3] = {at<float>(ws, L.tot[0]), at<float>(ws, L.tot[1]), at<float>(ws, L.tot[2])};
     for (int m = 0; m < 3; ++m)
       if (!launched([&] { return launch_large_zero(Wh[m], dh, st); }) || !cast(Wh[m], L.Whop[m])) return TTT_EHIP;
-    for (int m = 0; m < 3; ++m)
-      if (!copy(Wm[m], W0[m] + hd * dh) || !cast(Wm[m], Wo[m])) return TTT_EHIP;
     float* const* result = Wh;
     if (sync == TTT_SYNC_CHAIN) {
+      // W_0 .. W_C, each step's update written beside what it started from
       auto wl_at = [&](int64_t c, int m) { return wl + (c * 3 + m) * dh; };
       for (int m = 0; m < 3; ++m)
-        if (!copy(wl_at(0, m), Wm[m])) return TTT_EHIP;
+        if (!copy(wl_at(0, m), W0[m] + hd * dh) || !cast(wl_at(0, m), Wo[m])) return TTT_EHIP;
       for (int64_t c = 0; c < C; ++c) {
-        if (!fwd_step(c, true)) return TTT_EHIP;
-        for (int m = 0; m < 3; ++m)
-          if (!copy(wl_at(c + 1, m), Wm[m])) return TTT_EHIP;
+        float* from[3] = {wl_at(c, 0), wl_at(c, 1), wl_at(c, 2)};
+        float* to[3] = {wl_at(c + 1, 0), wl_at(c + 1, 1), wl_at(c + 1, 2)};
+        if (!fwd_step(c, true, from, to)) return TTT_EHIP;
       }
       // the forward steps left the operand copies of W_C in Wo; those of W_c
       // serve chunk c - 1 as its W', the two sets changing places
@@ -1587,8 +1588,10 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
         std::swap(op, opn);
       }
     } else {
+      for (int m = 0; m < 3; ++m)
+        if (!copy(Wm[m], W0[m] + hd * dh) || !cast(Wm[m], Wo[m])) return TTT_EHIP;
       for (int64_t c = 0; c < C; ++c)
-        if (!fwd_step(c, false)) return TTT_EHIP;
+        if (!fwd_step(c, false, Wm, Wm)) return TTT_EHIP;
       for (int m = 0; m < 3; ++m)
         if (!cast(Wm[m], L.Wnop[m])) return TTT_EHIP;
       for (int64_t c = 0; c < C; ++c)

@@ -562,8 +562,9 @@ struct WProb {
   const bf16* B[2];
   int lda, ldb, M, N, nterm;
   float* w;        // FP32 [M][N]
+  const float* from;  // the W added to (w itself, or the masters of the step before)
   bf16* op;        // operand copy of the result, nullable
-  float coef;      // W = (add ? W : 0) + coef * sum
+  float coef;      // w = (add ? from : 0) + coef * sum
   int add;
 };
 struct WArgs {
@@ -651,7 +652,7 @@ __global__ __launch_bounds__(NTHR) void k_wgrad(WArgs a) {
               (int64_t)(o.im * TL::BM + mc.wm + 32 * i + l32) * w.N + o.in * TL::BN + mc.wn + 32 * n + 16 * hf;
           float wv[16], nv[16];
           if (w.add) {
-            load16(wr + at, wv);
+            load16((term == 0 ? w.from : wr) + at, wv);
           } else {
 #pragma unroll
             for (int r = 0; r < 16; ++r) wv[r] = 0.f;
@@ -673,11 +674,11 @@ __global__ __launch_bounds__(NTHR) void k_wgrad(WArgs a) {
 
 // Adds a weight term to a launch.
 inline void add_weight(WArgs& a, const bf16* A, int lda, const bf16* B, int ldb, int M, int N, float* w, bf16* op,
-                       float coef, int add) {
+                       float coef, int add, const float* from = nullptr) {
   WProb& p = a.p[a.np++];
   p.A[0] = A; p.B[0] = B;
   p.lda = lda; p.ldb = ldb; p.M = M; p.N = N; p.nterm = 1;
-  p.w = w; p.op = op; p.coef = coef; p.add = add;
+  p.w = w; p.from = from ? from : w; p.op = op; p.coef = coef; p.add = add;
 }
 // Tiles by the rounds of the launch and the measured rate of a work-group
 // (per CU, 256 x 256: 5.2 TFLOP/s, 128 x 256: 4.2, 128 x 128: 2.9).

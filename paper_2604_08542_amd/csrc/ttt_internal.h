@@ -192,9 +192,12 @@ struct LargeAmuArgs {
   void* G3;          // SiLU(Z1)
   void* D1;          // hidden adjoint times G1
   void* D3;          // hidden adjoint times G3
-  float* W1;         // FP32 masters [d][h], [h][d], [d][h], updated in place
+  float* W1;         // FP32 masters [d][h], [h][d], [d][h] after the update
   float* W2;
   float* W3;
+  const float* from1;  // the masters before it (null: W1 .. W3, in place)
+  const float* from2;
+  const float* from3;
   void* W1op;        // operand copies of the masters
   void* W2op;
   void* W3op;

@@ -134,8 +134,9 @@ struct EpUpd : EpBase {
   T* wop;
   int ld;
   float eta;
+  const float* from;  // the W stepped from (w itself, or the masters of the step before)
   typedef float In;
-  __device__ __forceinline__ float load(int r, int c) const { return w[(int64_t)r * ld + c]; }
+  __device__ __forceinline__ float load(int r, int c) const { return from[(int64_t)r * ld + c]; }
   __device__ __forceinline__ void operator()(int r, int c, float g, float wv) {
     const int64_t i = (int64_t)r * ld + c;
     const float wn = wv - eta * g;
@@ -360,10 +361,10 @@ hipError_t step_t(const LargeStepArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((k_gemm<T, KMAJ, KMAJ, BMT, EpD<T>>), dim3(h / BN, mt), dim3(NTH), 0, st, E, d, M, W2o, d, h, d,
                        e3);
     // W1 -= eta Kn^T D ; W2 -= eta A^T E (contractions over the chunk's tokens)
-    EpUpd<T> e4{{}, a.W1, a.masters_only ? nullptr : W1o, h, a.eta};
+    EpUpd<T> e4{{}, a.W1, a.masters_only ? nullptr : W1o, h, a.eta, a.W1};
     hipLaunchKernelGGL((k_gemm<T, MNMAJ, MNMAJ, BMW, EpUpd<T>>), dim3(h / BN, d / BMW), dim3(NTH), 0, st, Kn, d, M, Dd,
                        h, M, M, e4);
-    EpUpd<T> e5{{}, a.W2, a.masters_only ? nullptr : W2o, d, a.eta};
+    EpUpd<T> e5{{}, a.W2, a.masters_only ? nullptr : W2o, d, a.eta, a.W2};
     hipLaunchKernelGGL((k_gemm<T, MNMAJ, MNMAJ, BMW, EpUpd<T>>), dim3(d / BN, h / BMW), dim3(NTH), 0, st, Aa, h, M, E, d,
                        M, M, e5);
   }
@@ -411,13 +412,13 @@ hipError_t amu_step_t(const LargeAmuArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((k_gemm<T, KMAJ, KMAJ, BMT, EpD2<T>>), dim3(h / BN, mt), dim3(NTH), 0, st, E, d, M, W2o, d, h,
                        d, e3);
     // the step sizes are inside the loss: W <- W - grad
-    EpUpd<T> u1{{}, a.W1, a.write_op ? W1o : nullptr, h, 1.0f};
+    EpUpd<T> u1{{}, a.W1, a.write_op ? W1o : nullptr, h, 1.0f, a.from1 ? a.from1 : a.W1};
     hipLaunchKernelGGL((k_gemm<T, MNMAJ, MNMAJ, BMW, EpUpd<T>>), dim3(h / BN, d / BMW), dim3(NTH), 0, st, Kn, d, M, D1,
                        h, M, M, u1);
-    EpUpd<T> u3{{}, a.W3, a.write_op ? W3o : nullptr, h, 1.0f};
+    EpUpd<T> u3{{}, a.W3, a.write_op ? W3o : nullptr, h, 1.0f, a.from3 ? a.from3 : a.W3};
     hipLaunchKernelGGL((k_gemm<T, MNMAJ, MNMAJ, BMW, EpUpd<T>>), dim3(h / BN, d / BMW), dim3(NTH), 0, st, Kn, d, M, D3,
                        h, M, M, u3);
-    EpUpd<T> u2{{}, a.W2, a.write_op ? W2o : nullptr, d, 1.0f};
+    EpUpd<T> u2{{}, a.W2, a.write_op ? W2o : nullptr, d, 1.0f, a.from2 ? a.from2 : a.W2};
     hipLaunchKernelGGL((k_gemm<T, MNMAJ, MNMAJ, BMW, EpUpd<T>>), dim3(d / BN, h / BMW), dim3(NTH), 0, st, Hd, h, M, E,
                        d, M, M, u2);
   }

@@ -228,9 +228,9 @@ static hipError_t amu_step_bf(const LargeAmuArgs& a, hipStream_t st) {
     // the step sizes are inside the loss: W <- W - grad
     WArgs w{};
     w.tokens = M;
-    add_weight(w, Kn, d, D1, h, d, h, a.W1, a.write_op ? W1 : nullptr, -1.0f, 1);
-    add_weight(w, Kn, d, D3, h, d, h, a.W3, a.write_op ? W3 : nullptr, -1.0f, 1);
-    add_weight(w, Hd, h, E, d, h, d, a.W2, a.write_op ? W2 : nullptr, -1.0f, 1);
+    add_weight(w, Kn, d, D1, h, d, h, a.W1, a.write_op ? W1 : nullptr, -1.0f, 1, a.from1);
+    add_weight(w, Kn, d, D3, h, d, h, a.W3, a.write_op ? W3 : nullptr, -1.0f, 1, a.from3);
+    add_weight(w, Hd, h, E, d, h, d, a.W2, a.write_op ? W2 : nullptr, -1.0f, 1, a.from2);
     wgrad(w, st);
   }
   if (a.O) {
