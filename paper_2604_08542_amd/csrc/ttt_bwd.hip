@@ -405,8 +405,9 @@ __global__ __launch_bounds__(NW * 64, 2) void ttt_bwd_step(BwdStepArgs p) {
 
 // Operand copies for one backward step, per (active sequence, head): W_s and
 // the carried adjoint Wh (zeros when absent), each of W1 [d][h] and W2 [h][d]
-// written in both orientations ([hid][d] and [d][hid]) in the matrix-core
-// operand type, so that every operand fragment is one contiguous vector load.
+// written in the matrix-core operand type as [hid][d] and [d][hid] (BF16: only
+// the latter, ttt_bwd_step_bf transposes as it reads), so that every operand
+// fragment is one contiguous vector load.
 template <typename MT>
 __global__ __launch_bounds__(256) void ttt_bwd_prep(BwdPrepArgs p) {
   const int dh = D * p.h;
@@ -422,10 +423,12 @@ __global__ __launch_bounds__(256) void ttt_bwd_prep(BwdPrepArgs p) {
   const int hh2 = idx / D, d2 = idx % D;  // idx = hh2*D + d2: W2 element (hh2, d2)
   const float w1 = W[idx], h1 = Wh ? Wh[idx] : 0.f;
   const float w2 = W[dh + idx], h2 = Wh ? Wh[dh + idx] : 0.f;
-  o[0 * dh + hh * D + d] = (MT)w1;     // W1 as [hid][d]
-  o[1 * dh + idx] = (MT)w2;            // W2 as [hid][d]
-  o[2 * dh + hh * D + d] = (MT)h1;
-  o[3 * dh + idx] = (MT)h2;
+  if constexpr (std::is_same_v<MT, float>) {
+    o[0 * dh + hh * D + d] = (MT)w1;     // W1 as [hid][d]
+    o[1 * dh + idx] = (MT)w2;            // W2 as [hid][d]
+    o[2 * dh + hh * D + d] = (MT)h1;
+    o[3 * dh + idx] = (MT)h2;
+  }
   o[4 * dh + idx] = (MT)w1;            // W1 as [d][hid]
   o[5 * dh + d2 * h + hh2] = (MT)w2;   // W2 as [d][hid]
   o[6 * dh + idx] = (MT)h1;
@@ -442,24 +445,33 @@ hipError_t launch_bwd_prep(const BwdPrepArgs& a, int n_active, bool mma_bf16, hi
 }
 
 // Four consecutive elements idx..idx+3 of one chain's [W1 | W2] (W) and of
-// its adjoint (Wh) into the 8 operand matrices of ttt_bwd_prep.
+// its adjoint (Wh) into the operand matrices of ttt_bwd_prep.
 template <typename MT>
 __device__ __forceinline__ void prep_scatter4(MT* o, int idx, int dh, int h, const f32x4& w, const f32x4& wh) {
+  typedef MT mt4 __attribute__((ext_vector_type(4)));
+  const mt4 m = {(MT)w[0], (MT)w[1], (MT)w[2], (MT)w[3]}, mh = {(MT)wh[0], (MT)wh[1], (MT)wh[2], (MT)wh[3]};
+  constexpr bool HD = std::is_same_v<MT, float>;  // [hid][d] too
+  if (idx < dh) {
+    *reinterpret_cast<mt4*>(o + 4 * dh + idx) = m;
+    *reinterpret_cast<mt4*>(o + 6 * dh + idx) = mh;
+    if constexpr (HD) {
+      const int d = idx / h, hh = idx % h;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int ie = idx + e;
-    if (ie < dh) {
-      const int d = ie / h, hh = ie % h;
-      o[0 * dh + hh * D + d] = (MT)w[e];
-      o[4 * dh + ie] = (MT)w[e];
-      o[2 * dh + hh * D + d] = (MT)wh[e];
-      o[6 * dh + ie] = (MT)wh[e];
-    } else {
-      const int i2 = ie - dh, hh2 = i2 / D, d2 = i2 % D;
-      o[1 * dh + i2] = (MT)w[e];
-      o[5 * dh + d2 * h + hh2] = (MT)w[e];
-      o[3 * dh + i2] = (MT)wh[e];
-      o[7 * dh + d2 * h + hh2] = (MT)wh[e];
+      for (int e = 0; e < 4; ++e) {
+        o[0 * dh + (hh + e) * D + d] = m[e];
+        o[2 * dh + (hh + e) * D + d] = mh[e];
+      }
+    }
+  } else {
+    const int i2 = idx - dh, hh = i2 / D, d = i2 % D;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o[5 * dh + (d + e) * h + hh] = m[e];
+      o[7 * dh + (d + e) * h + hh] = mh[e];
+    }
+    if constexpr (HD) {
+      *reinterpret_cast<mt4*>(o + 1 * dh + i2) = m;
+      *reinterpret_cast<mt4*>(o + 3 * dh + i2) = mh;
     }
   }
 }
