@@ -3,6 +3,9 @@
 // Eq. 8-10): forward step, update, operand preparation, and the reverse mode.
 #pragma once
 #include <stdint.h>
+#ifdef __HIPCC__
+#include "ttt_common.h"
+#endif
 
 namespace ttt {
 
@@ -100,26 +103,21 @@ struct AmuPsumArgs {
 #ifdef __HIPCC__
 // Operand copies (see the list above) of four consecutive elements v at
 // offset off of matrix mat (0 W1, 1 W2, 2 W3) of one head, o = the head's
-// n_mats matrices of dh = 64 h elements.  Written by the kernels that step
+// n_mats matrices of dh = 64 h elements; called by all 256 threads of a
+// work-group for 1,024 consecutive elements.  Written by the kernels that step
 // the weights or sum an adjoint, so that no launch of its own has to read
 // them back (7.7 us per launch at 16 heads, h = 256).
 template <typename MT>
-__device__ __forceinline__ void amu_put_prep(MT* o, int mat, int off, int h, int n_mats,
-                                             float __attribute__((ext_vector_type(4))) v) {
+__device__ __forceinline__ void amu_put_prep(MT* o, int mat, int off, int h, int n_mats, const f32x4& v) {
   typedef MT mt4 __attribute__((ext_vector_type(4)));
-  const int dh = 64 * h;
+  const int dh = D * h, off0 = off - 4 * (int)threadIdx.x;
   const mt4 m = {(MT)v[0], (MT)v[1], (MT)v[2], (MT)v[3]};
   if (mat == 1) {
-    const int hh = off / 64, d = off % 64;
     *reinterpret_cast<mt4*>(o + AMU_W2N * dh + off) = m;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[AMU_W2D * dh + (d + e) * h + hh] = m[e];
+    put_transposed(o + AMU_W2D * dh + off0 / D, h, D, h, v);
   } else {
-    const int d = off / h, hh = off % h;
-    MT* t = o + (mat ? AMU_W3T : AMU_W1T) * dh;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) t[(hh + e) * 64 + d] = m[e];
     if (n_mats == 6) *reinterpret_cast<mt4*>(o + (mat ? AMU_W3D : AMU_W1D) * dh + off) = m;
+    put_transposed(o + (mat ? AMU_W3T : AMU_W1T) * dh + off0 / h, D, h, h, v);
   }
 }
 #endif

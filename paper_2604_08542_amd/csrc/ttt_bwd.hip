@@ -445,30 +445,25 @@ hipError_t launch_bwd_prep(const BwdPrepArgs& a, int n_active, bool mma_bf16, hi
 }
 
 // Four consecutive elements idx..idx+3 of one chain's [W1 | W2] (W) and of
-// its adjoint (Wh) into the operand matrices of ttt_bwd_prep.
+// its adjoint (Wh) into the operand matrices of ttt_bwd_prep; called by all 256
+// threads of a work-group for 1,024 consecutive elements.
 template <typename MT>
-__device__ __forceinline__ void prep_scatter4(MT* o, int idx, int dh, int h, const f32x4& w, const f32x4& wh) {
+__device__ __forceinline__ void put_prep(MT* o, int idx, int dh, int h, const f32x4& w, const f32x4& wh) {
   typedef MT mt4 __attribute__((ext_vector_type(4)));
   const mt4 m = {(MT)w[0], (MT)w[1], (MT)w[2], (MT)w[3]}, mh = {(MT)wh[0], (MT)wh[1], (MT)wh[2], (MT)wh[3]};
   constexpr bool HD = std::is_same_v<MT, float>;  // [hid][d] too
-  if (idx < dh) {
+  const int i0 = idx - 4 * (int)threadIdx.x;
+  if (i0 < dh) {
     *reinterpret_cast<mt4*>(o + 4 * dh + idx) = m;
     *reinterpret_cast<mt4*>(o + 6 * dh + idx) = mh;
     if constexpr (HD) {
-      const int d = idx / h, hh = idx % h;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        o[0 * dh + (hh + e) * D + d] = m[e];
-        o[2 * dh + (hh + e) * D + d] = mh[e];
-      }
+      put_transposed(o + 0 * dh + i0 / h, D, h, h, w);
+      put_transposed(o + 2 * dh + i0 / h, D, h, h, wh);
     }
   } else {
-    const int i2 = idx - dh, hh = i2 / D, d = i2 % D;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      o[5 * dh + (d + e) * h + hh] = m[e];
-      o[7 * dh + (d + e) * h + hh] = mh[e];
-    }
+    const int i2 = idx - dh;
+    put_transposed(o + 5 * dh + (i0 - dh) / D, h, D, h, w);
+    put_transposed(o + 7 * dh + (i0 - dh) / D, h, D, h, wh);
     if constexpr (HD) {
       *reinterpret_cast<mt4*>(o + 1 * dh + i2) = m;
       *reinterpret_cast<mt4*>(o + 3 * dh + i2) = mh;
@@ -511,9 +506,9 @@ __global__ __launch_bounds__(256) void ttt_bwd_reduce(BwdReduceArgs p) {
       const f32x4 wv =
           *reinterpret_cast<const f32x4*>(p.ckpt + (p.ckpt_row[ai] * p.H + head) * 2 * dh + idx);
       if (p.prep_bf16)
-        prep_scatter4(static_cast<bf16*>(p.prep_next) + pc, idx, dh, p.h, wv, s);
+        put_prep(static_cast<bf16*>(p.prep_next) + pc, idx, dh, p.h, wv, s);
       else
-        prep_scatter4(static_cast<float*>(p.prep_next) + pc, idx, dh, p.h, wv, s);
+        put_prep(static_cast<float*>(p.prep_next) + pc, idx, dh, p.h, wv, s);
     }
   }
   if (k == 0 && threadIdx.x == 0) {
