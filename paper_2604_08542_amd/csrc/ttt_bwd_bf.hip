@@ -30,7 +30,7 @@
 //    barriers, which spilled up to 260 registers (344 us).
 // The row factors and the row dots of the normalisation adjoints sit in the
 // padding of the row tiles.  Measured per step, 16 heads x 5,496 tokens, BF16:
-// h = 256 211 -> 102 us; h = 128, 6,000 tokens, 93 -> 61 us.  (One wave per SIMD
+// h = 256 211 -> 107 us; h = 128, 6,000 tokens, 93 -> 63 us.  (One wave per SIMD
 // with two hidden blocks and 512 registers spills 170 of them.)
 //
 // Phases of an update tile, a barrier after each: Z, A (stage A) | A W2 -> E,
@@ -81,8 +81,8 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
   const int64_t hoff = (int64_t)head * p.stride_head;
   const bool norm_q = p.flags & 1u, norm_k = p.flags & 2u, norm_v = p.flags & 4u;
 
-  // Row data in the padding of the tiles (8 floats per row): xb: the four
-  // waves' dots of dK or dQ and of dV; eb: per tile parity the factors of the
+  // Row data in the padding of the tiles (8 floats per row): xb, yb: the eight
+  // partial dots of dK or dQ, of dV; eb: per tile parity the factors of the
   // two normalised tensors, negative where the adjoint has no projection (norm
   // at the floor, or not normalised).
   auto pad = [](bf16* t, int row) { return reinterpret_cast<float*>(t + row * RL + D); };
@@ -231,25 +231,30 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
         x[bi][r] = mul_rn(v, fabsf(f[bi][r]));
       }
   };
-  // row dots of g and xh over this wave's 16 features, into xb's padding
-  auto put_dots = [&](const float (&v)[NBK][4], const float (&xh)[NBK][4], int which) {
+  // Row dots of g and xh over this wave's 16 features, as two sums of eight
+  // features in a row (in feature order, along the lanes), into t's padding.
+  auto put_dots = [&](const float (&v)[NBK][4], const float (&xh)[NBK][4], bf16* t) {
 #pragma unroll
     for (int bi = 0; bi < NBK; ++bi)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float s = lane_group_sum<16>(v[bi][r] * xh[bi][r]);
-        if (L.l16 == 0) pad(xb, 16 * (tb0 + bi) + 4 * L.g4 + r)[4 * which + db16] = s;
+        float s = v[bi][r] * xh[bi][r];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) s = fmaf(v[bi][r], xh[bi][r], dpp_move<0x111>(s));  // row_shr:1
+        if ((L.l16 & 7) == 7) pad(t, 16 * (tb0 + bi) + 4 * L.g4 + r)[2 * db16 + (L.l16 >> 3)] = s;
       }
   };
-  // normalisation adjoint of g, stored
+  // normalisation adjoint of g (its dots in t's padding), stored
   auto store_adj = [&](__amdgpu_buffer_rsrc_t rs, const float (&v)[NBK][4], const float (&xh)[NBK][4],
-                       const float (&f)[NBK][4], int which) {
+                       const float (&f)[NBK][4], bf16* t) {
 #pragma unroll
     for (int bi = 0; bi < NBK; ++bi)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const f32x4 d = *reinterpret_cast<const f32x4*>(pad(xb, 16 * (tb0 + bi) + 4 * L.g4 + r) + 4 * which);
-        const float pv = fmaf(-xh[bi][r], (d[0] + d[1]) + (d[2] + d[3]), v[bi][r]);
+        const f32x4* d = reinterpret_cast<const f32x4*>(pad(t, 16 * (tb0 + bi) + 4 * L.g4 + r));
+        const f32x4 a = d[0], b = d[1];
+        const float dot = ((a[0] + a[1]) + (a[2] + a[3])) + ((b[0] + b[1]) + (b[2] + b[3]));
+        const float pv = fmaf(-xh[bi][r], dot, v[bi][r]);
         const float o = (f[bi][r] > 0.f ? pv : v[bi][r]) * fabsf(f[bi][r]);
         if constexpr (SZ == 2)
           __builtin_amdgcn_raw_buffer_store_b16((uint16_t)pack_bf16x2(o, o), rs, el_off, (16 * bi + r) * tok_bytes, 0);
@@ -370,10 +375,10 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
         put_rows(yb, bi, dY);
       }
       unit(vr, vh, vf, 1, par);
-      put_dots(gv, vh, 1);
+      put_dots(gv, vh, yb);
     }
     __syncthreads();
-    store_adj(tile_rs(p.dV, grad_start, gl, t), gv, vh, vf, 1);
+    store_adj(tile_rs(p.dV, grad_start, gl, t), gv, vh, vf, yb);
     // stage D;  dA = -eta E Wh2^T + dY W2^T;  dZ += dA s'(Z);  token sums dP^T E
     // + A^T dY (W2) and K^T dZ (W1)
     uint32_t dZpk[8];
@@ -424,11 +429,11 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) gk[bi][r] = fmaf(-eta, k1[bi][r], k2[bi][r]);
     unit(kr, kh, kf, 0, par);
-    put_dots(gk, kh, 0);
+    put_dots(gk, kh, xb);
     // the next tile's rows (the row tiles were last read before the sums' barrier)
     stage_rows(true, par ^ 1);
     __syncthreads();
-    store_adj(tile_rs(p.dK, grad_start, gl, t), gk, kh, kf, 0);
+    store_adj(tile_rs(p.dK, grad_start, gl, t), gk, kh, kf, xb);
   }
 
   // ------------------------------------------------ apply adjoint of chunk s-1
@@ -483,10 +488,10 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) gq[bi][r] = c[bi][r];
     unit(qr, qh, qf, 0, par);
-    put_dots(gq, qh, 0);
+    put_dots(gq, qh, xb);
     stage_rows(false, par ^ 1);
     __syncthreads();
-    store_adj(tile_rs(p.dQ, app_start, al, t), gq, qh, qf, 0);
+    store_adj(tile_rs(p.dQ, app_start, al, t), gq, qh, qf, xb);
   }
 
   // ------------------------------------------------ shard partials
