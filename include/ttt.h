@@ -258,8 +258,9 @@ ttt_status_t ttt_amu_fwd(const ttt_problem_t* p, int32_t sync, const void* Q, co
  * chunks in reverse; TTT_SYNC_GCS recomputes W* and needs one apply-adjoint
  * and one update-adjoint pass over all tokens.  Every output is overwritten;
  * with n_tokens = 0 the weight adjoints are zero.  ws_bytes >=
- * ttt_amu_bwd_workspace_bytes(p, sync) (it grows with the chunk count for the
- * chain).  Errors as ttt_amu_fwd.  At large state sizes every product is a
+ * ttt_amu_bwd_workspace_bytes(p, sync) (for the chain it grows by the FP32
+ * weights, 12 d h bytes per head, with every chunk; 12 d h per chunk at large
+ * state sizes).  Errors as ttt_amu_fwd.  At large state sizes every product is a
  * GEMM over weights streamed from HBM, one head and one chunk at a time. */
 size_t ttt_amu_bwd_workspace_bytes(const ttt_problem_t* p, int32_t sync);
 ttt_status_t ttt_amu_bwd(const ttt_problem_t* p, int32_t sync, const void* Q, const void* K, const void* V,

@@ -1364,7 +1364,7 @@ ttt_status_t run_amu(const ttt_problem_t* p, const Shape& S, int sync, const voi
   auto do_update = [&](const AmuWeights& src, int64_t G, float* dst, bool last, bool to_prep) {
     AmuUpdArgs u{};
     u.src = src; u.partial = partial; u.G = (int32_t)G; u.H = (int32_t)H; u.h = S.h; u.w_dst = dst;
-    u.prep = to_prep ? prep : nullptr; u.n_mats = 4; u.prep_bf16 = S.mma_bf16;
+    u.prep = to_prep ? prep : nullptr; u.n_mats = u.n_copies = 4; u.prep_bf16 = S.mma_bf16;
     u.wT1 = last ? W1_T : nullptr; u.wT2 = last ? W2_T : nullptr; u.wT3 = last ? W3_T : nullptr;
     return launched([&] { return launch_amu_update(u, st); });
   };
@@ -1610,9 +1610,12 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
 
 // Reverse mode of the paper's memory unit.  Workspace: shard partials, the
 // carried adjoint Wh [H][3dh], the weights the backward needs ([C+1][H][3dh]
-// for the chain: every W_c, recomputed; [1][H][3dh] for GCS: W*), and sets of
-// six operand copies per head (W_0 .. W_C for the chain, W_0 and W* for GCS,
-// and Wh).
+// for the chain: every W_c, recomputed; [1][H][3dh] for GCS: W*), and sets of six
+// operand copies per head: of Wh, and a ring of those of the last W_c written
+// (GCS: W_0 and W*).  A ring of five sets in BF16 (two in FP32) takes, with Wh's,
+// the bytes of three FP32 sets; the copies of every W_c would double (FP32:
+// triple) what a long chain takes.
+inline int64_t amu_bwd_ring(const Shape& s) { return s.mma_bf16 ? 5 : 2; }
 struct AmuBwdWs {
   size_t partial, wh, wlist, prep_w, prep_h, total;
   int64_t slot_cap;
@@ -1633,7 +1636,7 @@ AmuBwdWs amu_bwd_ws_layout(const Shape& s, int64_t n_tokens, int sync) {
   L.wlist = off;
   off = align_up(off + (size_t)n_w * s.H * wbytes);
   L.prep_w = off;
-  off = align_up(off + (size_t)(sync == TTT_SYNC_CHAIN ? C + 1 : 2) * pbytes);
+  off = align_up(off + amu_bwd_ring(s) * pbytes);
   L.prep_h = off;
   off = align_up(off + pbytes);
   L.total = off;
@@ -1658,8 +1661,9 @@ ttt_status_t run_amu_bwd(const ttt_problem_t* p, const Shape& S, int sync, const
   float* partial = at<float>(ws, L.partial);
   float* wh = at<float>(ws, L.wh);
   float* wlist = at<float>(ws, L.wlist);
-  // operand copies of W_0, W_1, .. (chain) or W_0, W* (GCS), and of Wh
-  auto prep_w = [&](int64_t c) { return at<char>(ws, L.prep_w) + c * H * 6 * dh * (S.mma_bf16 ? 2 : 4); };
+  // operand copies of W_c (GCS: of W_0 and W*), and of Wh
+  const int64_t ring = amu_bwd_ring(S);
+  auto prep_w = [&](int64_t c) { return at<char>(ws, L.prep_w) + c % ring * H * 6 * dh * (S.mma_bf16 ? 2 : 4); };
   void* prep_h = at<char>(ws, L.prep_h);
   const int target = default_target_wgs(S);
   auto grid_g = [&](int64_t len) {
@@ -1684,10 +1688,10 @@ ttt_status_t run_amu_bwd(const ttt_problem_t* p, const Shape& S, int sync, const
       return int64_t(-1);
     return G;
   };
-  auto do_update = [&](const AmuWeights& src, int64_t G, float* dst, void* prep) {
+  auto do_update = [&](const AmuWeights& src, int64_t G, float* dst, void* prep, int copies) {
     AmuUpdArgs u{};
     u.src = src; u.partial = partial; u.G = (int32_t)G; u.H = (int32_t)H; u.h = S.h; u.w_dst = dst;
-    u.prep = prep; u.n_mats = 6; u.prep_bf16 = S.mma_bf16;
+    u.prep = prep; u.n_mats = 6; u.n_copies = copies; u.prep_bf16 = S.mma_bf16;
     return launched([&] { return launch_amu_update(u, st); });
   };
   auto bwd_args = [&](int64_t start, int64_t len, int64_t G) {
@@ -1714,7 +1718,9 @@ ttt_status_t run_amu_bwd(const ttt_problem_t* p, const Shape& S, int sync, const
       return int64_t(-1);
     return G;
   };
-  auto do_psum = [&](int64_t G, const float* base, float* dst, bool final, bool to_prep) {  // to_prep: into prep_h
+  // to_prep: into prep_h; next: also the copies of those weights, into prep_next
+  auto do_psum = [&](int64_t G, const float* base, float* dst, bool final, bool to_prep,
+                     const AmuWeights& next = AmuWeights{}, void* prep_next = nullptr) {
     AmuPsumArgs a{};
     a.partial = partial; a.G = (int32_t)G; a.H = (int32_t)H; a.h = S.h; a.base = base; a.dst = dst;
     if (final) { a.out1 = dW1_0; a.out2 = dW2_0; a.out3 = dW3_0; }
@@ -1725,11 +1731,12 @@ ttt_status_t run_amu_bwd(const ttt_problem_t* p, const Shape& S, int sync, const
   if (C == 0) {  // no tokens: O is empty, every adjoint is zero
     return do_psum(0, nullptr, wh, true, false) ? TTT_OK : TTT_EHIP;
   }
+    a.next = next; a.prep_next = prep_next;
   if (sync == TTT_SYNC_GCS) {
     float* wstar = wlist;
     if (!do_prep(w0, prep_w(0))) return TTT_EHIP;
     const int64_t Gg = do_grad(0, N, prep_w(0));
-    if (Gg < 0 || !do_update(w0, Gg, wstar, prep_w(1))) return TTT_EHIP;
+    if (Gg < 0 || !do_update(w0, Gg, wstar, prep_w(1), 6)) return TTT_EHIP;
     const int64_t Ga = do_apply_adj(0, N, prep_w(1));
     if (Ga < 0 || !do_psum(Ga, nullptr, wh, false, true)) return TTT_EHIP;
     const int64_t Gu = do_update_adj(0, N, prep_w(0));
@@ -1742,13 +1749,19 @@ ttt_status_t run_amu_bwd(const ttt_problem_t* p, const Shape& S, int sync, const
   if (!do_prep(w0, prep_w(0))) return TTT_EHIP;
   for (int64_t c = 0; c < C; ++c) {
     const int64_t G = do_grad(c * M, mlen(c), prep_w(c));
-    if (G < 0 || !do_update(wc(c), G, wlist + (c + 1) * H * 3 * dh, prep_w(c + 1))) return TTT_EHIP;
+    // the next gradient reads three copies; those that the ring still holds at
+    // the end, the reverse steps read all of
+    if (G < 0 || !do_update(wc(c), G, wlist + (c + 1) * H * 3 * dh, prep_w(c + 1), c + 1 <= C - ring ? 3 : 6))
+      return TTT_EHIP;
   }
   for (int64_t c = C - 1; c >= 0; --c) {
     const int64_t Ga = do_apply_adj(c * M, mlen(c), prep_w(c + 1));
     if (Ga < 0 || !do_psum(Ga, c == C - 1 ? nullptr : wh, wh, false, true)) return TTT_EHIP;
     const int64_t Gu = do_update_adj(c * M, mlen(c), prep_w(c));
-    if (Gu < 0 || !do_psum(Gu, wh, wh, c == 0, false)) return TTT_EHIP;
+    // W_{c-1}'s copies for the next chunk, where the ring has lost them
+    const bool next = c > 0 && c - 1 <= C - ring;
+    if (Gu < 0 || !do_psum(Gu, wh, wh, c == 0, false, next ? wc(c - 1) : AmuWeights{}, next ? prep_w(c - 1) : nullptr))
+      return TTT_EHIP;
   }
   return TTT_OK;
 }

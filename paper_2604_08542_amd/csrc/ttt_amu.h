@@ -54,6 +54,7 @@ struct AmuUpdArgs {
   float* wT3;
   void* prep;            // operand copies of the result as ttt_amu_prep writes them, nullable
   int32_t n_mats, prep_bf16;
+  int32_t n_copies;      // how many of them (0 .. n_copies - 1 of the list above): 3, 4 or 6
 };
 
 struct AmuPrepArgs {
@@ -87,7 +88,9 @@ struct AmuBwdArgs {
 };
 
 // dst = base + sum over the G shard partials in shard order (base nullable);
-// split copies of the result when out1..3 are set.  Packed [H][3*D*h].
+// split copies of the result when out1..3 are set.  Packed [H][3*D*h].  The
+// launch that ends a chunk of the chain's reverse mode also writes the operand
+// copies of the weights that the chunk before it starts from.
 struct AmuPsumArgs {
   const float* partial;
   int32_t G, H, h;
@@ -98,25 +101,27 @@ struct AmuPsumArgs {
   float* out3;
   void* prep;              // operand copies (six) of the result, nullable
   int32_t prep_bf16;
+  AmuWeights next;         // with prep_next: weights to copy
+  void* prep_next;         // their operand copies (six), nullable
 };
 
 #ifdef __HIPCC__
 // Operand copies (see the list above) of four consecutive elements v at
 // offset off of matrix mat (0 W1, 1 W2, 2 W3) of one head, o = the head's
-// n_mats matrices of dh = 64 h elements; called by all 256 threads of a
-// work-group for 1,024 consecutive elements.  Written by the kernels that step
+// matrices of dh = 64 h elements, of which the first n_copies (3, 4 or 6) are
+// written; called by all 256 threads of a work-group for 1,024 consecutive elements.  Written by the kernels that step
 // the weights or sum an adjoint, so that no launch of its own has to read
 // them back (7.7 us per launch at 16 heads, h = 256).
 template <typename MT>
-__device__ __forceinline__ void amu_put_prep(MT* o, int mat, int off, int h, int n_mats, const f32x4& v) {
+__device__ __forceinline__ void amu_put_prep(MT* o, int mat, int off, int h, int n_copies, const f32x4& v) {
   typedef MT mt4 __attribute__((ext_vector_type(4)));
   const int dh = D * h, off0 = off - 4 * (int)threadIdx.x;
   const mt4 m = {(MT)v[0], (MT)v[1], (MT)v[2], (MT)v[3]};
   if (mat == 1) {
     *reinterpret_cast<mt4*>(o + AMU_W2N * dh + off) = m;
-    put_transposed(o + AMU_W2D * dh + off0 / D, h, D, h, v);
+    if (n_copies > 3) put_transposed(o + AMU_W2D * dh + off0 / D, h, D, h, v);
   } else {
-    if (n_mats == 6) *reinterpret_cast<mt4*>(o + (mat ? AMU_W3D : AMU_W1D) * dh + off) = m;
+    if (n_copies == 6) *reinterpret_cast<mt4*>(o + (mat ? AMU_W3D : AMU_W1D) * dh + off) = m;
     put_transposed(o + (mat ? AMU_W3T : AMU_W1T) * dh + off0 / h, D, h, h, v);
   }
 }

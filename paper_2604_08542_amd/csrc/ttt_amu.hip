@@ -261,9 +261,9 @@ __global__ __launch_bounds__(256) void ttt_amu_update(AmuUpdArgs p) {
   if (p.prep) {
     const int64_t po = (int64_t)head * p.n_mats * dh;
     if (p.prep_bf16)
-      amu_put_prep(static_cast<bf16*>(p.prep) + po, mat, off, p.h, p.n_mats, wn);
+      amu_put_prep(static_cast<bf16*>(p.prep) + po, mat, off, p.h, p.n_copies, wn);
     else
-      amu_put_prep(static_cast<float*>(p.prep) + po, mat, off, p.h, p.n_mats, wn);
+      amu_put_prep(static_cast<float*>(p.prep) + po, mat, off, p.h, p.n_copies, wn);
   }
 }
 

@@ -449,29 +449,41 @@ __global__ __launch_bounds__(NW * 64) void ttt_amu_bwd_update(AmuBwdArgs p) {
   if (p.len > 0) t.write_partial(p.partial + ((int64_t)head * G + g) * (3 * DH), g1, g2, g3, w, -1.0f);
 }
 
-// dst = base + sum of the G shard partials (shard order), per head.
+// dst = base + sum of the G shard partials (shard order), per head; with
+// prep_next a second half of the grid writes the operand copies of `next`
+// (work-groups of their own, beside the sums: behind them, 16 heads at h = 128
+// took 1.5 us more per launch).
 __global__ __launch_bounds__(256) void ttt_amu_psum(AmuPsumArgs p) {
   const int dh = D * p.h;
   const int n4 = (3 * dh) / 4;
   const int nbpc = (n4 + 255) / 256;
-  const int head = blockIdx.x / nbpc, k = blockIdx.x % nbpc;
+  const bool copy = blockIdx.x >= (unsigned)(p.H * nbpc);
+  const int lin = copy ? blockIdx.x - p.H * nbpc : blockIdx.x;
+  const int head = lin / nbpc, k = lin % nbpc;
   const int i4 = k * 256 + threadIdx.x;
   if (i4 >= n4) return;
   const int idx = 4 * i4;
-  const int64_t hb = (int64_t)head * 3 * dh;
-  f32x4 s = p.base ? *reinterpret_cast<const f32x4*>(p.base + hb + idx) : (f32x4){0.f, 0.f, 0.f, 0.f};
-  const f32x4* part = reinterpret_cast<const f32x4*>(p.partial + (int64_t)head * p.G * 3 * dh) + i4;
-  s = add_shards(s, part, n4, p.G);
-  if (p.dst) *reinterpret_cast<f32x4*>(p.dst + hb + idx) = s;
   const int mat = idx / dh, off = idx % dh;
-  float* out = mat == 0 ? p.out1 : (mat == 1 ? p.out2 : p.out3);
-  if (out) *reinterpret_cast<f32x4*>(out + (int64_t)head * dh + off) = s;
-  if (p.prep) {
+  f32x4 s;
+  if (copy) {
+    const float* src = mat == 0 ? p.next.w1 : (mat == 1 ? p.next.w2 : p.next.w3);
+    s = *reinterpret_cast<const f32x4*>(src + (int64_t)head * p.next.stride + off);
+  } else {
+    const int64_t hb = (int64_t)head * 3 * dh;
+    s = p.base ? *reinterpret_cast<const f32x4*>(p.base + hb + idx) : (f32x4){0.f, 0.f, 0.f, 0.f};
+    const f32x4* part = reinterpret_cast<const f32x4*>(p.partial + (int64_t)head * p.G * 3 * dh) + i4;
+    s = add_shards(s, part, n4, p.G);
+    if (p.dst) *reinterpret_cast<f32x4*>(p.dst + hb + idx) = s;
+    float* out = mat == 0 ? p.out1 : (mat == 1 ? p.out2 : p.out3);
+    if (out) *reinterpret_cast<f32x4*>(out + (int64_t)head * dh + off) = s;
+  }
+  void* prep = copy ? p.prep_next : p.prep;
+  if (prep) {
     const int64_t po = (int64_t)head * 6 * dh;
     if (p.prep_bf16)
-      amu_put_prep(static_cast<bf16*>(p.prep) + po, mat, off, p.h, 6, s);
+      amu_put_prep(static_cast<bf16*>(prep) + po, mat, off, p.h, 6, s);
     else
-      amu_put_prep(static_cast<float*>(p.prep) + po, mat, off, p.h, 6, s);
+      amu_put_prep(static_cast<float*>(prep) + po, mat, off, p.h, 6, s);
   }
 }
 
@@ -501,7 +513,7 @@ hipError_t launch_amu_bwd_update(const AmuBwdArgs& a, int n_blocks, int h, bool 
 
 hipError_t launch_amu_psum(const AmuPsumArgs& a, hipStream_t st) {
   const int nbpc = ((3 * D * a.h) / 4 + 255) / 256;
-  hipLaunchKernelGGL(ttt_amu_psum, dim3(a.H * nbpc), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(ttt_amu_psum, dim3(a.H * nbpc * (a.prep_next ? 2 : 1)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
