@@ -1725,13 +1725,13 @@ ttt_status_t run_amu_bwd(const ttt_problem_t* p, const Shape& S, int sync, const
     a.partial = partial; a.G = (int32_t)G; a.H = (int32_t)H; a.h = S.h; a.base = base; a.dst = dst;
     if (final) { a.out1 = dW1_0; a.out2 = dW2_0; a.out3 = dW3_0; }
     a.prep = to_prep ? prep_h : nullptr; a.prep_bf16 = S.mma_bf16;
+    a.next = next; a.prep_next = prep_next;
     return launched([&] { return launch_amu_psum(a, st); });
   };
 
   if (C == 0) {  // no tokens: O is empty, every adjoint is zero
     return do_psum(0, nullptr, wh, true, false) ? TTT_OK : TTT_EHIP;
   }
-    a.next = next; a.prep_next = prep_next;
   if (sync == TTT_SYNC_GCS) {
     float* wstar = wlist;
     if (!do_prep(w0, prep_w(0))) return TTT_EHIP;
