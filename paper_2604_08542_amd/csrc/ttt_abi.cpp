@@ -103,13 +103,13 @@ LargeLayout large_layout(const Shape& s) {
   L.A = take(M * h * op);
   L.D = take(M * h * op);
   L.Aq = take(M * h * op);
-  L.Vn = take(M * d * 4);
+  L.Vn = take(s.mma_bf16 ? M * 4 : M * d * 4);  // BF16 products: V's row factors
   L.S1 = take((M + 127) / 128 * 128 * h * op);  // tile-native: whole 128-row tiles
   L.W1 = take(d * h * 4);
   L.W2 = take(d * h * 4);
   L.W1op = take(d * h * op);
   L.W2op = take(d * h * op);
-  L.loss_part = take(std::max((d / 128) * ((M + 127) / 128), SUM_PARTS) * 4);
+  L.loss_part = take((s.mma_bf16 ? sum_parts(d / 128, M) : (d / 128) * ((M + 127) / 128)) * 4);
   L.total = off;
   return L;
 }
@@ -141,12 +141,13 @@ LargeBwdLayout large_bwd_layout(const Shape& s) {
   L.dE = take(M * d * 4);
   L.S2 = take((M + 127) / 128 * 128 * h * op);  // tile-native
   L.P = take((M + 127) / 128 * 128 * h * op);  // tile-native
-  L.Dn = take(s.mma_bf16 ? (M + 127) / 128 * 128 * h * op : 0);  // tile-native
   L.Sq1 = take((M + 127) / 128 * 128 * h * op);  // tile-native
+  L.Dn = L.Sq1;  // (BF16 products) written when the apply adjoint has used Sq1
   L.dZq = take(M * h * op);
   L.dP = take(M * h * op);
-  L.dZa = take((M + 127) / 128 * 128 * h * op);  // tile-native
-  L.EWh = take((M + 127) / 128 * 128 * h * op);  // tile-native with BF16 products
+  // tile-native; BF16 products: each lane writes dZa over the S2 that it has read
+  L.dZa = s.mma_bf16 ? L.S2 : take((M + 127) / 128 * 128 * h * op);
+  L.EWh = take(s.mma_bf16 ? (M + 127) / 128 * 128 * h * op : M * h * op);  // BF16 products: tile-native
   L.dZ = take(M * h * op);
   L.W1nop = take(d * h * op);
   L.W2nop = take(d * h * op);
@@ -156,7 +157,8 @@ LargeBwdLayout large_bwd_layout(const Shape& s) {
   L.Wh2op = take(d * h * op);
   L.tot1 = take(d * h * 4);  // GCS: the adjoint of W0 (the apply adjoint plus every chunk's update terms)
   L.tot2 = take(d * h * 4);
-  L.deta_part = take(std::max((d / 128 + h / 128) * ((M + 127) / 128), 2 * SUM_PARTS) * 4);
+  L.deta_part = take((s.mma_bf16 ? sum_parts(d / 64, M) + sum_parts(h / 128, M)
+                                 : (d / 128 + h / 128) * ((M + 127) / 128)) * 4);
   L.deta = take(4);
   L.total = off;
   return L;
@@ -182,9 +184,9 @@ LargeAmuLayout large_amu_layout(const Shape& s) {
   L.Kn = take(M * d * op);
   L.Qn = take(M * d * op);
   L.E = take(M * d * op);
-  L.Vn = take(M * d * 4);
+  L.Vn = take(s.mma_bf16 ? M * 4 : M * d * 4);  // BF16 products: V's row factors
   const size_t Mt = (M + 127) / 128 * 128;  // Z3, G1, G3 tile-native in the forward step: whole 128-row tiles
-  L.Z3 = take(Mt * h * op);
+  L.Z3 = take(s.mma_bf16 ? 0 : Mt * h * op);  // BF16 products: stays in the registers
   L.Hd = take(M * h * op);
   L.G1 = take(Mt * h * op);
   L.G3 = take(Mt * h * op);
@@ -206,7 +208,7 @@ LargeAmuLayout large_amu_layout(const Shape& s) {
 // last ([C+1][3][d h] FP32).
 struct LargeAmuBwdLayout {
   LargeAmuLayout f;
-  size_t dOn, Ydot, dq, dk, dv, S, S1, S2, Zd3, Sd, Hdot, T2, dHh, aZ1, aZ3, aZd1, aZd3, Wnop[3], Wh[3], Whop[3],
+  size_t dOn, Ydot, dq, dk, dv, Z3, S, S1, S2, Zd3, Sd, Hdot, T2, dHh, aZ1, aZ3, aZd1, aZd3, Wnop[3], Wh[3], Whop[3],
       tot[3], wlist, total;
 };
 LargeAmuBwdLayout large_amu_bwd_layout(const Shape& s, int64_t n_tokens, int sync) {
@@ -224,10 +226,14 @@ LargeAmuBwdLayout large_amu_bwd_layout(const Shape& s, int64_t n_tokens, int syn
   L.Ydot = take(M * d * 4);
   L.dq = take(M * d * 4);
   L.dk = take(M * d * 4);
-  L.dv = take(M * d * 4);
-  // whole 128-row tiles: S, S1, S2, Zd3, Sd, T2, dHh are tile-native in the reverse step
-  for (size_t* b : {&L.S, &L.S1, &L.S2, &L.Zd3, &L.Sd, &L.Hdot, &L.T2, &L.dHh, &L.aZ1, &L.aZ3, &L.aZd1, &L.aZd3})
-    *b = take((M + 127) / 128 * 128 * h * op);
+  // whole 128-row tiles: Z3, S, S1, S2, Zd3, Sd, T2, dHh are tile-native in the reverse step
+  const size_t Mt = (M + 127) / 128 * 128;
+  for (size_t* b : {&L.S, &L.S1, &L.Zd3, &L.Sd, &L.Hdot, &L.T2, &L.aZ1, &L.aZ3, &L.aZd1, &L.aZd3})
+    *b = take(Mt * h * op);
+  // held in registers by one form or the other
+  L.Z3 = s.mma_bf16 ? take(Mt * h * op) : L.f.Z3;
+  L.dv = take(s.mma_bf16 ? 0 : M * d * 4);
+  for (size_t* b : {&L.S2, &L.dHh}) *b = take(s.mma_bf16 ? 0 : Mt * h * op);
   for (int m = 0; m < 3; ++m) {
     L.Wnop[m] = take(d * h * op);
     L.Wh[m] = take(d * h * 4);
@@ -1545,7 +1551,7 @@ ttt_status_t run_amu_bwd_large(const ttt_problem_t* p, const Shape& S, int sync,
       b.dOn = at<char>(ws, L.dOn);
       b.Vn = at<float>(ws, L.f.Vn); b.Ydot = at<float>(ws, L.Ydot);
       b.dq = at<float>(ws, L.dq); b.dk = at<float>(ws, L.dk); b.dv = at<float>(ws, L.dv);
-      b.Z3 = at<char>(ws, L.f.Z3); b.Hd = at<char>(ws, L.f.Hd);
+      b.Z3 = at<char>(ws, L.Z3); b.Hd = at<char>(ws, L.f.Hd);
       b.S = at<char>(ws, L.S); b.S1 = at<char>(ws, L.S1); b.S2 = at<char>(ws, L.S2); b.Zd3 = at<char>(ws, L.Zd3);
       b.Sd = at<char>(ws, L.Sd); b.Hdot = at<char>(ws, L.Hdot); b.T2 = at<char>(ws, L.T2); b.dHh = at<char>(ws, L.dHh);
       b.aZ1 = at<char>(ws, L.aZ1); b.aZ3 = at<char>(ws, L.aZ3); b.aZd1 = at<char>(ws, L.aZd1);

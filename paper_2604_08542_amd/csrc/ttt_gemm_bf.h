@@ -537,7 +537,7 @@ inline int gemm(const GemmArgs& g, const EP& ep, hipStream_t st) {
   }
   return (int)std::min<int64_t>(tiles, MAX_WG);
 }
-static_assert(SUM_PARTS >= (size_t)MAX_WG * NW, "a partial per wave of a launch");
+static_assert(MAX_WG == 256 && NW == 8, "sum_parts counts the waves of a launch");
 inline GemmArgs product(const bf16* A, int lda, int a_rows, const bf16* B, int ldb, int b_rows, int M, int N, int K) {
   GemmArgs g{};
   g.A[0] = A; g.B[0] = B;

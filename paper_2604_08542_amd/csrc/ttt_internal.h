@@ -13,8 +13,11 @@ namespace ttt {
 // the token tensors (head offset applied), every product is a GEMM over
 // operands streamed from HBM.
 // BF16 products: a launch has at most 256 work-groups of 8 waves; its scalar
-// sums have one partial per wave.
-constexpr size_t SUM_PARTS = 256 * 8;
+// sums have one partial per wave.  The most that a product over `rows` token
+// rows has, with `cols` of the narrowest tiles across.
+inline size_t sum_parts(size_t cols, size_t rows) {
+  return 8 * std::min<size_t>(256, cols * ((rows + 127) / 128));
+}
 struct LargeNormArgs {
   const void* K;
   const void* V;
@@ -51,7 +54,7 @@ struct LargeStepArgs {
   float* W2;
   void* W1op;     // operand copies of the masters
   void* W2op;
-  float* loss_part;  // [max(d/128 * ceil(rows/128), SUM_PARTS)]
+  float* loss_part;  // [d/128 * ceil(rows/128)] (BF16 products: [sum_parts])
   float* loss;       // nullable: the chunk's loss
 };
 // (BF16 products: ttt_large_bf.hip, ttt_large_bwd_bf.hip)

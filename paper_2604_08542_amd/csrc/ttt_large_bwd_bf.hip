@@ -147,7 +147,7 @@ struct EpPE : Ep<EpPE> {
   }
 };
 // u1 = K Wh1: dP = -eta u1 s'(Z) rows, dZa = -eta u1 P s''(Z) tile-native;
-// -<u1, D> into the partials.
+// -<u1, D> into the partials.  dza may be s2: a lane writes what it has read.
 struct EpU1 : Ep<EpU1> {
   static constexpr bool AHEAD = false;
   bf16* dp;
