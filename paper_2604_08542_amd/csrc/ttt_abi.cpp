@@ -2106,9 +2106,14 @@ ttt_status_t ttt_gcm_fwd(const ttt_problem_t* p, const void* X, const void* Wqkv
 
 // Reverse mode of the layer: workspace regions.  The unit runs on views of
 // the projection P [N][3D] (Q, K, V at column offsets 0, D, 2D, token pitch
-// 3D), so its problem is the layer's with that pitch.
+// 3D), so its problem is the layer's with that pitch.  The BF16 form's sums of
+// the runs of a weight gradient sit in tensors that are not alive beside it:
+// dWo's in dP, extra and dO (written after it), dWqkv's in extra, dO, P, O and dG
+// (used up before it); `extra` holds what does not fit, up to the bytes of the
+// FP32 form's G, and past that there are fewer runs.
 struct GcmBwdLayout {
-  size_t P, O, dO, dP, dG, G, part, wpart, ckpt, unit, total;
+  size_t P, O, dO, dP, dG, G, part, extra, ckpt, unit, total;
+  int runs_o, runs_p;
   ttt_problem_t pu;
 };
 static ttt_status_t gcm_bwd_layout(const ttt_problem_t* p, GcmBwdLayout* L) {
@@ -2134,15 +2139,29 @@ static ttt_status_t gcm_bwd_layout(const ttt_problem_t* p, GcmBwdLayout* L) {
     off = align_up(off + bytes);
     return o;
   };
-  L->P = take((size_t)N * 3 * D * io);
-  L->O = take((size_t)N * 3 * D * io);
-  L->dO = take((size_t)N * 3 * D * io);
-  L->dP = take((size_t)N * 3 * D * io);
-  L->dG = take((size_t)N * D * io);
+  const size_t row3 = (size_t)N * 3 * D * io, row1 = (size_t)N * D * io, slab_part = (size_t)((N + 255) / 256) * 3 * D * 4;
+  size_t part = slab_part, extra = 0;
+  L->runs_o = L->runs_p = 1;
+  if (S.io_bf16) {
+    const size_t wo = (size_t)D * D * 4, wp = 3 * wo;  // bytes of one run's sums
+    part = std::max(part, gcm_part_floats(N, D) * 4);
+    const size_t most = 2 * row1 - std::min(2 * row1, part - slab_part);
+    const int64_t runs_o = gcm_runs(D, D, N), runs_p = gcm_runs(D, 3 * D, N);
+    auto lacks = [](int64_t runs, size_t run, size_t free) {
+      return runs > 1 && (size_t)runs * run > free ? (size_t)runs * run - free : 0;
+    };
+    extra = std::min(most, std::max(lacks(runs_o, wo, 2 * row3), lacks(runs_p, wp, 3 * row3 + row1)));
+    L->runs_o = (int)std::max<int64_t>(1, std::min<int64_t>(runs_o, (2 * row3 + extra) / wo));
+    L->runs_p = (int)std::max<int64_t>(1, std::min<int64_t>(runs_p, (3 * row3 + row1 + extra) / wp));
+  }
+  L->dP = take(row3);
+  L->extra = take(extra);
+  L->dO = take(row3);
+  L->P = take(row3);
+  L->O = take(row3);
+  L->dG = take(row1);
   L->G = take(S.io_bf16 ? 0 : (size_t)N * D * 4);
-  const size_t runs_o = gcm_runs(D, D, N), runs_p = gcm_runs(D, 3 * D, N);  // the BF16 form's weight gradients
-  L->part = take(std::max((size_t)((N + 255) / 256) * 3 * D, S.io_bf16 ? gcm_part_floats(N, D) : 0) * 4);
-  L->wpart = take(S.io_bf16 ? std::max(runs_o > 1 ? runs_o : 0, runs_p > 1 ? 3 * runs_p : 0) * D * D * 4 : 0);
+  L->part = take(part);
   L->ckpt = take((size_t)C * S.H * 2 * S.dh() * 4);
   L->unit = take(ub);
   L->total = off;
@@ -2191,7 +2210,9 @@ ttt_status_t ttt_gcm_bwd(const ttt_problem_t* p, const void* X, const void* Wqkv
     a.D = (int32_t)D; a.rows = N;
     a.X = X; a.Wqkv = Wqkv; a.bqkv = bqkv; a.Wo = Wo; a.bo = bo; a.alpha = alpha; a.dY = dY;
     a.P = b + L.P; a.O = b + L.O; a.G = reinterpret_cast<float*>(b + L.G); a.dG = b + L.dG; a.dO = b + L.dO;
-    a.dP = b + L.dP; a.part = reinterpret_cast<float*>(b + L.part); a.wpart = reinterpret_cast<float*>(b + L.wpart);
+    a.dP = b + L.dP; a.part = reinterpret_cast<float*>(b + L.part);
+    a.part_o = reinterpret_cast<float*>(b + L.dP); a.part_p = reinterpret_cast<float*>(b + L.extra);
+    a.runs_o = L.runs_o; a.runs_p = L.runs_p;
     a.dX = dX; a.dWqkv = dWqkv; a.dbqkv = dbqkv; a.dWo = dWo; a.dbo = dbo; a.dalpha = dalpha;
     // the projection, then the unit's forward with its checkpoints
     a.phase = 0;

@@ -248,11 +248,10 @@ __global__ __launch_bounds__(256) void k_runs(const float* part, int n, int64_t 
 }
 
 // dW = A^T B over all tokens, the tokens cut into runs.
-static void weight_grad(const bf16* A, int lda, const bf16* B, int ldb, int M, int N, int tokens, float* dw,
+static void weight_grad(const bf16* A, int lda, const bf16* B, int ldb, int M, int N, int tokens, int runs, float* dw,
                         float* part, hipStream_t st) {
   WArgs w{};
   w.tokens = tokens;
-  const int runs = gcm_runs(M, N, tokens);
   w.nsplit = runs;
   add_weight(w, A, lda, B, ldb, M, N, runs > 1 ? part : dw, nullptr, 1.0f, 0);
   wgrad(w, st);
@@ -309,12 +308,12 @@ hipError_t launch_gcm_bwd_bf(const GcmBwdArgs& a, hipStream_t st) {
     const dim3 cs((D + 63) / 64);
     hipLaunchKernelGGL(k_colsums, cs, dim3(1024), 0, st, a.part, n, pitch, D, a.dalpha);
     if (a.dbo) hipLaunchKernelGGL(k_colsums, cs, dim3(1024), 0, st, a.part + D, n, pitch, D, a.dbo);
-    weight_grad(O, D3, C(a.dG), D, D, D, rows, a.dWo, a.wpart, st);
+    weight_grad(O, D3, C(a.dG), D, D, D, rows, a.runs_o, a.dWo, a.part_o, st);
     EpBias eo{{}, {P(a.dO), nullptr, nullptr}, nullptr, D3, 0};
     gemm<KMAJ, KMAJ, 1>(product(C(a.dG), D, rows, C(a.Wo), D, D, rows, D, D), eo, st);
   } else {
     const bf16* dP = C(a.dP);
-    weight_grad(C(a.X), D, dP, D3, D, D3, rows, a.dWqkv, a.wpart, st);
+    weight_grad(C(a.X), D, dP, D3, D, D3, rows, a.runs_p, a.dWqkv, a.part_p, st);
     if (a.dbqkv) {
       const int ns = (rows + 255) / 256;
       hipLaunchKernelGGL(k_slab_sums, dim3((D3 + 255) / 256, ns), dim3(256), 0, st, dP, (int64_t)D3, rows, D3, a.part);

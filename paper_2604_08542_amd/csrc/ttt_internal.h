@@ -252,7 +252,9 @@ struct GcmBwdArgs {
   void* dO;            // [N][3D], the first D columns used
   const void* dP;      // [N][3D]
   float* part;         // column partial sums: FP32 form [ceil(N / 256)][3D], BF16 form gcm_part_floats
-  float* wpart;        // BF16 form: the runs' sums of a weight gradient
+  float* part_o;       // BF16 form: the runs' sums of dWo (over dP, dO) and of
+  float* part_p;       // dWqkv (over dO, P, O, dG)
+  int32_t runs_o, runs_p;
   void* dX;
   float* dWqkv;        // [D][3D]
   float* dbqkv;        // [3D], nullable

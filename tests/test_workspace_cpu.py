@@ -50,6 +50,19 @@ def test_large_states_take_no_more(lib, name, extra, shape, enough):
     assert 0 < getattr(lib, name)(ctypes.byref(prob(*shape)), *extra) <= enough
 
 
+@pytest.mark.parametrize("shape,enough", [
+    ((16, 64, 128, 2729, 918, L.TTT_BF16), 164739584),
+    ((2, 64, 128, 700, 300, L.TTT_BF16), 71534592),
+    ((32, 64, 256, 2050, 500, L.TTT_BF16), 323334656),
+    ((36, 64, 256, 1540, 500, L.TTT_BF16), 306945536),
+    ((24, 64, 128, 1100, 300, L.TTT_BF16), 139938304),
+    ((16, 64, 256, 43968, 10992, L.TTT_BF16), 1516417536),
+])
+def test_layer_reverse_takes_no_more(lib, shape, enough):
+    """Shapes whose weight gradients are cut into runs of tokens."""
+    assert 0 < lib.ttt_gcm_bwd_workspace_bytes(ctypes.byref(prob(*shape))) <= enough
+
+
 def test_paper_unit_large_state_holds_what_bf16_touches(lib):
     """BF16 products at 1024 x 4096: per chunk row the forward keeps K, Q, E (6 d
     bytes), V's factor and five hidden rows (10 h); the FP32 form one hidden row
