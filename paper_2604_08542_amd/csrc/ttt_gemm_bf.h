@@ -682,34 +682,40 @@ inline void add_weight(WArgs& a, const bf16* A, int lda, const bf16* B, int ldb,
 }
 // Tiles by the rounds of the launch and the measured rate of a work-group
 // (per CU, 256 x 256: 5.2 TFLOP/s, 128 x 256: 4.2, 128 x 128: 2.9).
-inline void wgrad(WArgs a, hipStream_t st) {
-  a.nsplit = std::max(1, std::min(a.nsplit, (a.tokens + KS - 1) / KS));
+struct WTile {
+  int bm, bn;
+  int64_t tiles;
+};
+inline WTile pick_wgrad(const WArgs& a) {
   struct {
     int bm, bn;
     double rate;
   } const kind[3] = {{256, 256, 5.2}, {128, 256, 4.2}, {128, 128, 2.9}};
-  int best = 2;
-  int64_t grid = 0;
+  WTile best{128, 128, 0};
   double bc = 1e30;
-  for (int c = 0; c < 3; ++c) {
+  for (const auto& k : kind) {
     int64_t tiles = 0, longest = 1;
     bool fits = true;
     for (int p = 0; p < a.np; ++p) {
-      fits = fits && a.p[p].M % kind[c].bm == 0 && a.p[p].N % kind[c].bn == 0;
-      tiles += (int64_t)(a.p[p].M / kind[c].bm) * (a.p[p].N / kind[c].bn) * a.nsplit;
+      fits = fits && a.p[p].M % k.bm == 0 && a.p[p].N % k.bn == 0;
+      tiles += (int64_t)(a.p[p].M / k.bm) * (a.p[p].N / k.bn) * a.nsplit;
       longest = std::max<int64_t>(longest, a.p[p].nterm);
     }
-    const double cost = (double)((tiles + MAX_WG - 1) / MAX_WG * longest) * kind[c].bm * kind[c].bn / kind[c].rate;
+    const double cost = (double)((tiles + MAX_WG - 1) / MAX_WG * longest) * k.bm * k.bn / k.rate;
     if (fits && cost < bc) {
       bc = cost;
-      best = c;
-      grid = std::min<int64_t>(tiles, MAX_WG);
+      best = {k.bm, k.bn, tiles};
     }
   }
-  const dim3 g((unsigned)grid), nt(NTHR);
-  if (best == 0)
+  return best;
+}
+inline void wgrad(WArgs a, hipStream_t st) {
+  a.nsplit = std::max(1, std::min(a.nsplit, (a.tokens + KS - 1) / KS));
+  const WTile t = pick_wgrad(a);
+  const dim3 g((unsigned)std::min<int64_t>(t.tiles, MAX_WG)), nt(NTHR);
+  if (t.bm == 256)
     hipLaunchKernelGGL(k_wgrad<TileL>, g, nt, 0, st, a);
-  else if (best == 1)
+  else if (t.bn == 256)
     hipLaunchKernelGGL(k_wgrad<TileH>, g, nt, 0, st, a);
   else
     hipLaunchKernelGGL(k_wgrad<TileS>, g, nt, 0, st, a);

@@ -254,3 +254,25 @@ hipError_t launch_large_amu_step_bf(const LargeAmuArgs& a, bool io_bf16, hipStre
 }
 
 }  // namespace ttt
+
+// Tile choice of the BF16 GEMM core, for tests that have to reach every tile:
+// rows of the tiles of a product of `nmat` matrices, and rows * 1000 + columns
+// of the tiles of a launch of weight terms.  Not part of the C ABI.
+extern "C" int32_t ttt_internal_gemm_tile(int32_t M, int32_t N, int32_t nmat, int64_t K) {
+  using namespace ttt::bfg;
+  const int cfg = pick_tile(M, N, nmat, K, true);
+  return cfg == T_L ? 256 : cfg == T_M ? 192 : 128;
+}
+extern "C" int32_t ttt_internal_wgrad_tile(int32_t np, const int32_t* M, const int32_t* N, const int32_t* nterm,
+                                           int32_t nsplit) {
+  using namespace ttt::bfg;
+  if (np < 1 || np > 3) return 0;
+  WArgs a{};
+  a.nsplit = nsplit;
+  for (int p = 0; p < np; ++p) {
+    add_weight(a, nullptr, 0, nullptr, 0, M[p], N[p], nullptr, nullptr, 1.0f, 1);
+    a.p[p].nterm = nterm[p];
+  }
+  const WTile t = pick_wgrad(a);
+  return t.bm * 1000 + t.bn;
+}
