@@ -299,10 +299,8 @@ hipError_t launch_gcm_bwd_bf(const GcmBwdArgs& a, hipStream_t st) {
     const bf16* O = C(a.O);
     EpGateBwd eg{{}, P(a.dG), C(a.dY), a.bo, a.alpha, a.part, D};
     const GemmArgs g = product(O, D3, rows, C(a.Wo), D, D, rows, D, D);
-    gemm<KMAJ, MNMAJ, 1>(g, eg, st);
     // the partials sit at the first rows of the waves' shares of the tiles
-    const int cfg = pick_tile(rows, D, 1, D, true);
-    const int step = cfg == T_L ? 4 : cfg == T_M ? 3 : 1;  // 32-row blocks per wave
+    const int step = gemm<KMAJ, MNMAJ, 1>(g, eg, st).blocks;
     const int n = ((rows + 31) / 32 + step - 1) / step;
     const int64_t pitch = (int64_t)step * 2 * D;
     const dim3 cs((D + 63) / 64);

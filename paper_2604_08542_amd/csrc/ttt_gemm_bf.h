@@ -489,6 +489,11 @@ struct Ep {
 // smaller tiles win where the larger ones leave CUs idle: 10,992 x 1024 over
 // 4096 is 172 tiles of 256 x 256 (87 us) but 232 of 192 x 256 (80 us).
 enum { T_L = 0, T_M = 1, T_S = 2 };
+// A launched product: its work-groups (the waves that write partials are 8
+// times as many) and the 32-row blocks of a wave.
+struct Launched {
+  int wgs, blocks;
+};
 inline int64_t gemm_tiles(int cfg, int M, int N, int nmat) {
   const int bm = cfg == T_L ? 256 : cfg == T_M ? 192 : 128;
   const int cn = nmat == 4 ? 64 : (cfg == T_S ? 128 : 256) / nmat;
@@ -513,29 +518,26 @@ inline int pick_tile(int M, int N, int nmat, int64_t K, bool kmaj_a) {
 }
 
 template <class TL, int LA, int LB, int NMAT, class EP>
-inline void launch_tile(const GemmArgs& g, const EP& ep, int64_t tiles, hipStream_t st) {
+inline Launched launch_tile(const GemmArgs& g, const EP& ep, int64_t tiles, hipStream_t st) {
   const int grid = (int)std::min<int64_t>(tiles, MAX_WG);
   hipLaunchKernelGGL((k_gemm<TL, LA, LB, NMAT, EP>), dim3(grid), dim3(NTHR), 0, st, g, ep);
+  return {grid, TL::MB};
 }
-// Launches one product; returns its work-groups (the waves that write
-// partials are 8 times as many).
+// Launches one product.
 template <int LA, int LB, int NMAT, class EP>
-inline int gemm(const GemmArgs& g, const EP& ep, hipStream_t st) {
+inline Launched gemm(const GemmArgs& g, const EP& ep, hipStream_t st) {
   const int cfg = pick_tile(g.M, g.N, NMAT, (int64_t)g.K * g.nseg, LA == KMAJ);
   const int64_t tiles = gemm_tiles(cfg, g.M, g.N, NMAT);
   if constexpr (NMAT == 4) {
-    if (cfg == T_L)
-      launch_tile<TileL4, LA, LB, NMAT>(g, ep, tiles, st);
-    else
-      launch_tile<TileS4, LA, LB, NMAT>(g, ep, tiles, st);
+    if (cfg == T_L) return launch_tile<TileL4, LA, LB, NMAT>(g, ep, tiles, st);
+    return launch_tile<TileS4, LA, LB, NMAT>(g, ep, tiles, st);
   } else {
-    if (cfg == T_L) launch_tile<TileL, LA, LB, NMAT>(g, ep, tiles, st);
+    if (cfg == T_L) return launch_tile<TileL, LA, LB, NMAT>(g, ep, tiles, st);
     if constexpr (LA == KMAJ) {
-      if (cfg == T_M) launch_tile<TileM, LA, LB, NMAT>(g, ep, tiles, st);
+      if (cfg == T_M) return launch_tile<TileM, LA, LB, NMAT>(g, ep, tiles, st);
     }
-    if (cfg == T_S) launch_tile<TileS, LA, LB, NMAT>(g, ep, tiles, st);
+    return launch_tile<TileS, LA, LB, NMAT>(g, ep, tiles, st);
   }
-  return (int)std::min<int64_t>(tiles, MAX_WG);
 }
 static_assert(MAX_WG == 256 && NW == 8, "sum_parts counts the waves of a launch");
 inline GemmArgs product(const bf16* A, int lda, int a_rows, const bf16* B, int ldb, int b_rows, int M, int N, int K) {

@@ -178,7 +178,7 @@ static hipError_t step_bf(const LargeStepArgs& a, hipStream_t st) {
     EpAct<true> e1{{}, A, S1, h};
     gemm<KMAJ, MNMAJ, 1>(product(Kn, d, M, W1, h, d, M, h, d), e1, st);
     EpRes<IOT> e2{{}, E, static_cast<const IOT*>(a.V), a.Vn, a.stride_tok, a.loss_part, d, 2.0f / (float)M};
-    const int wgs = gemm<KMAJ, MNMAJ, 1>(product(A, h, M, W2, d, h, M, d, h), e2, st);
+    const int wgs = gemm<KMAJ, MNMAJ, 1>(product(A, h, M, W2, d, h, M, d, h), e2, st).wgs;
     if (a.loss) hipLaunchKernelGGL(k_loss, dim3(1), dim3(256), 0, st, a.loss_part, wgs * NW, 1.0f / (float)M, a.loss);
     EpD e3{{}, D, S1, h};
     gemm<KMAJ, KMAJ, 1>(product(E, d, M, W2, d, h, M, h, d), e3, st);

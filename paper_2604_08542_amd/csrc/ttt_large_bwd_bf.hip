@@ -548,13 +548,13 @@ static hipError_t bwd_step_bf(const LargeBwdArgs& a, hipStream_t st) {
     GemmArgs yu = product(A, h, M, W2, d, h, M, d, h);
     yu.B[1] = Wh2;
     EpYU<IOT> e2{{}, E, a.dE, static_cast<const IOT*>(a.V), vinv, a.stride_tok, a.deta_part, d, scale, eta};
-    const int n1 = gemm<KMAJ, MNMAJ, 2>(yu, e2, st) * NW;
+    const int n1 = gemm<KMAJ, MNMAJ, 2>(yu, e2, st).wgs * NW;
     GemmArgs pe = product(E, d, M, W2, d, h, M, h, d);
     pe.B[1] = Wh2;
     EpPE e3{{}, D, Dn, Pn, EWh, S1, h};
     gemm<KMAJ, KMAJ, 2>(pe, e3, st);
     EpU1 e9{{}, dP, dZa, Dn, S1, Pn, S2, a.deta_part + n1, h, eta};
-    const int n2 = gemm<KMAJ, MNMAJ, 1>(product(Kn, d, M, Wh1, h, d, M, h, d), e9, st) * NW;
+    const int n2 = gemm<KMAJ, MNMAJ, 1>(product(Kn, d, M, Wh1, h, d, M, h, d), e9, st).wgs * NW;
     hipLaunchKernelGGL(k_deta, dim3(1), dim3(256), 0, st, a.deta_part, n1 + n2, a.deta);
     EpDY e11{{}, dY, a.dv, a.dE, d, scale};
     gemm<KMAJ, MNMAJ, 1>(product(dP, h, M, W2, d, h, M, d, h), e11, st);
