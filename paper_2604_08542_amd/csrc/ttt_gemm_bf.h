@@ -81,12 +81,16 @@ typedef __attribute__((address_space(3))) char lds_char;
 
 // 64 lanes x 16 bytes from global memory to LDS at byte address lds +
 // 16 * lane; reads past the resource's end deliver zeros.  The compiler does
-// not count these loads; the waits below do.
+// not count these loads; the waits below do.  (It warns that m0 is a reserved
+// register: the clobber is what keeps it from holding a value of its own there.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void dma16(u32x4 rs, int vo, int so, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(vo), "s"(rs),
                "s"(so)
-               : "memory");
+               : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // All but the newest N of this wave's memory operations are complete, then
 // the work-group's barrier.
 template <int N>
