@@ -29,7 +29,7 @@ hipError_t launch_norm(const NormArgs& a, bool io_bf16, hipStream_t st);
 
 // Sum of part[0..n) by a work-group of 256 threads in a fixed order: thread t
 // adds the run part[t c .. t c + c) in index order (c = ceil(n / 256)), then
-// thread 0 adds the run sums in thread order.  Valid in thread 0.
+// the run sums are added in a tree.  Valid in thread 0.
 __device__ __forceinline__ float fixed_sum(const float* part, int n) {
   __shared__ float run[256];
   const int t = threadIdx.x, c = (n + 255) / 256;
@@ -37,11 +37,12 @@ __device__ __forceinline__ float fixed_sum(const float* part, int n) {
   float s = 0.f;
   for (int i = i0; i < i1; ++i) s += part[i];
   run[t] = s;
-  __syncthreads();
-  float tot = 0.f;
-  if (t == 0)
-    for (int i = 0; i < 256; ++i) tot += run[i];
-  return tot;
+#pragma unroll
+  for (int m = 128; m >= 1; m >>= 1) {
+    __syncthreads();
+    if (t < m) run[t] += run[t + m];
+  }
+  return run[0];
 }
 
 // x rounded to BF16.

@@ -26,7 +26,9 @@
 namespace ttt {
 namespace bfg {
 
-// R = Y - V, E = scale R; sum of R^2 into the launch's partials.
+// R = Y - V, E = scale R; sum of R^2 into the launch's partials (a strip's
+// terms in one run, the strips in another: a lane's run over all of its tiles
+// would lose a rounding per element of the chunk).
 template <typename IOT>
 struct EpRes : Ep<EpRes<IOT>> {
   bf16* e;
@@ -56,13 +58,15 @@ struct EpRes : Ep<EpRes<IOT>> {
   __device__ __forceinline__ void strip(const Strip& st, const In& in, const f32x16 (&y)[NB]) {
     uint32_t pe[NB][8];
     const bool ok = st.valid();
+    float sum = 0.f;
 #pragma unroll
     for (int n = 0; n < NB; ++n)
       pack_each(pe[n], [&](int r) {
         const float R = y[n][r] - mul_rn(in.v[n].get(r), in.inv);
-        if (ok) acc = fmaf(R, R, acc);
+        if (ok) sum = fmaf(R, R, sum);
         return scale * R;
       });
+    acc += sum;
     st.template rows_out<NB>(e, ld, st.col, pe);
   }
   __device__ __forceinline__ void finish() { this->put_partial(loss_part, acc); }

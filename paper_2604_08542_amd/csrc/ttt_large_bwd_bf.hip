@@ -108,12 +108,13 @@ struct EpYU : Ep<EpYU<IOT>> {
     ev.v[0] = (u32x4){pk[0][0], pk[0][1], pk[0][2], pk[0][3]};
     ev.v[1] = (u32x4){pk[0][4], pk[0][5], pk[0][6], pk[0][7]};
     if (st.valid()) {
-      float dv[16];
+      float dv[16], sum = 0.f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        acc = fmaf(-x[1][r], ev.get(r), acc);
+        sum = fmaf(-x[1][r], ev.get(r), sum);
         dv[r] = -eta * x[1][r];
       }
+      acc += sum;
       store16(de + (int64_t)st.row() * ld + st.col + 16 * st.hf(), dv);
     }
     st.template rows_out<1>(e, ld, st.col, pk);
@@ -180,17 +181,19 @@ struct EpU1 : Ep<EpU1> {
   __device__ __forceinline__ void strip(const Strip& st, const In& in, const f32x16 (&u)[NB]) {
     uint32_t pd[NB][8];
     const bool ok = st.valid();
+    float sum = 0.f;
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
       uint32_t pz[8];
       pack_each(pz, [&](int r) {
         const float dd = -eta * u[n][r];
-        if (ok) acc = fmaf(-u[n][r], in.d[n].get(r), acc);
+        if (ok) sum = fmaf(-u[n][r], in.d[n].get(r), sum);
         return dd * in.p[n].get(r) * in.s2[n].get(r);
       });
       nat_store(dza, nat_at(st.row0, st.col + 32 * n, ld), pz);
       pack_each(pd[n], [&](int r) { return (-eta * u[n][r]) * in.s1[n].get(r); });
     }
+    acc += sum;
     st.template rows_out<NB>(dp, ld, st.col, pd);
   }
   __device__ __forceinline__ void finish() { this->put_partial(part, acc); }
