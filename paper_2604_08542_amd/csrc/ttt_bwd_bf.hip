@@ -19,19 +19,27 @@
 //    shards do not fill the CUs);
 //  - LDS is what is left beside them: the BF16 rows of K, E and dY (transposing
 //    reads give their columns) and one staged [token][hidden] tile that A, dP,
-//    D and dZ take in turn.  V and K enter the residual and the normalisation
-//    adjoints in FP32 from the token tensors, in the layout of the 16x16
-//    results, times the row's factor;
+//    D and dZ take in turn.  At h = 256 V and K enter the residual and the
+//    normalisation adjoints in FP32 from the token tensors, in the layout of the
+//    16x16 results, times the row's factor, and the row factors and row dots sit
+//    in the padding of the row tiles;
+//  - at h = 128 two FP32 row tiles fit as well (F32T): normalised V for the
+//    residual, and the way of dV, dK and dQ to the threads that hold the raw
+//    rows, which take the dots and store 16 bytes at a time (with one wave per
+//    SIMD a step is as long as its instructions).  The rows are requested before
+//    the matrices, and the apply's first tile behind the last update tile;
 //  - loads and stores of rows past the end are dropped by the buffer range
 //    check, so the tile has no branches that would widen a wait;
 //  - 256 registers per lane suffice only because values are formed where they
 //    are written here (the empty asm statements): left to itself the compiler
 //    sinks the adjoint of Z, the d(eta) sum and the LDS addresses across
 //    barriers, which spilled up to 260 registers (344 us).
-// The row factors and the row dots of the normalisation adjoints sit in the
-// padding of the row tiles.  Measured per step, 16 heads x 5,496 tokens, BF16:
-// h = 256 211 -> 107 us; h = 128, 6,000 tokens, 93 -> 63 us.  (One wave per SIMD
-// with two hidden blocks and 512 registers spills 170 of them.)
+// Measured per step, 16 heads, BF16, on one machine, against one kernel that
+// read its matrices from the L2 per tile: h = 256, 5,496 tokens 181 -> 122 us; h =
+// 128, 6,000 tokens 114 -> 68 us (without the FP32 row tiles 87), one tile per
+// shard (320 tokens) 14.1 -> 13.8 us (without 16.2), the whole reverse call of 8
+// such chunks 188 -> 167 us (without 195).  (One wave per SIMD with two hidden
+// blocks and 512 registers spills 170 of them.)
 //
 // Phases of an update tile, a barrier after each: Z, A (stage A) | A W2 -> E,
 // A Wh2 | P, K Wh1 -> D, dP (stage dP) | dP W2 -> dY, dots of dV | dV; stage D;
@@ -57,11 +65,15 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
   constexpr bool SPLIT = NW == 8;  // the two row tensors go to the two halves of the group
   constexpr int EPT = 8;        // row mapping: 8 lanes x 8 elements per token
   constexpr int SZ = (int)sizeof(IOT);
+  constexpr bool F32T = NW == 4;  // FP32 row tiles beside the matrices: see the adjoints below
+  constexpr int FL = D + 4;
 
   __shared__ __attribute__((aligned(16))) bf16 xb_[NG][TT * RL];  // K or Q rows
   __shared__ __attribute__((aligned(16))) bf16 eb_[NG][TT * RL];  // E rows
   __shared__ __attribute__((aligned(16))) bf16 yb_[NG][TT * RL];  // dY or dO rows
   __shared__ __attribute__((aligned(16))) bf16 st_[NG][TT * SL];  // staged tile
+  __shared__ __attribute__((aligned(16))) float vt_[NG][F32T ? TT * FL : 1];  // normalised V rows
+  __shared__ __attribute__((aligned(16))) float gt_[NG][F32T ? TT * FL : 1];  // dV, dK or dQ before its norm adjoint
   __shared__ __attribute__((aligned(16))) bf16 wl[4][DH];    // matrices as [d][hid], 16-byte chunks of row d at c ^ f(d)
 
   Lane L;
@@ -70,6 +82,7 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
   L.hid = 32 * L.w + L.l32;
   const int tid = threadIdx.x - grp * NW * 64;  // in the group
   bf16 *const xb = xb_[grp], *const eb = eb_[grp], *const yb = yb_[grp], *const st = st_[grp];
+  float *const vt = vt_[grp], *const gt = gt_[grp];
   // Shard g of a slot (active sequence * H + head); NG consecutive shards share
   // the work-group, in step: a group without a tile left runs on zeros.
   const int G = p.G, per_slot = (G + NG - 1) / NG;
@@ -81,10 +94,10 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
   const int64_t hoff = (int64_t)head * p.stride_head;
   const bool norm_q = p.flags & 1u, norm_k = p.flags & 2u, norm_v = p.flags & 4u;
 
-  // Row data in the padding of the tiles (8 floats per row): xb, yb: the eight
-  // partial dots of dK or dQ, of dV; eb: per tile parity the factors of the
-  // two normalised tensors, negative where the adjoint has no projection (norm
-  // at the floor, or not normalised).
+  // h = 256: row data in the padding of the tiles (8 floats per row): xb, yb:
+  // the eight partial dots of dK or dQ, of dV; eb: per tile parity the factors of
+  // the two normalised tensors.  A factor is negative where the adjoint has no
+  // projection (norm at the floor, or not normalised).
   auto pad = [](bf16* t, int row) { return reinterpret_cast<float*>(t + row * RL + D); };
 
   // Matrices (of the prepared operands, 0..3 are W1, W2, Wh1, Wh2 as [hid][d],
@@ -95,9 +108,12 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
   // multiply tokens in several products, also in registers.
   enum { W1 = 0, W2 = 1, WH1 = 2, WH2 = 3 };
   bf16x8 wf[4 * DH / 8 / NT];  // all requested before any is needed
+  auto request = [&] {
 #pragma unroll
-  for (int n = 0; n < 4 * DH / 8 / NT; ++n)
-    wf[n] = *reinterpret_cast<const bf16x8*>(prep + 4 * DH + (NT * n + threadIdx.x) * 8);
+    for (int n = 0; n < 4 * DH / 8 / NT; ++n)
+      wf[n] = *reinterpret_cast<const bf16x8*>(prep + 4 * DH + (NT * n + threadIdx.x) * 8);
+  };
+  if constexpr (!F32T) request();
   // The wave's 16x16 output blocks: features 16 db .., token halves tb0 ..
   const int db16 = L.w & 3, tb0 = NBK == 2 ? 0 : L.w >> 2;
   // Those blocks of staged tile x matrix k, over the hidden axis.
@@ -198,12 +214,23 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
     float x[EPT], n = 1.f;
     const float sc = r.get(true, x, &n), inv = do_norm ? sc : 1.f;
     if (t) put_part<EPT>(&t[row * RL + col0], x, inv);
-    if ((rtid & 7) == 0) pad(eb, row)[2 * par + which] = do_norm && n > NORM_EPS ? inv : -inv;
+    const float f = do_norm && n > NORM_EPS ? inv : -inv;
+    if constexpr (F32T) {
+      if (!t) {
+#pragma unroll
+        for (int i = 0; i < EPT; i += 4)
+          *reinterpret_cast<f32x4*>(&vt[row * FL + col0 + i]) = (f32x4){mul_rn(x[i], inv), mul_rn(x[i + 1], inv),
+                                                                        mul_rn(x[i + 2], inv), mul_rn(x[i + 3], inv)};
+      }
+    } else {
+      if ((rtid & 7) == 0) pad(eb, row)[2 * par + which] = f;
+    }
+    return f;
   };
-
+  float fa = 0.f, fb = 0.f;  // F32T: factors of the rows just staged
   auto stage_rows = [&](bool update, int par) {
-    if (!second) put_row(ra, update ? norm_k : norm_q, xb, 0, par);
-    if (second || !SPLIT) put_row(SPLIT ? ra : rb, update && norm_v, update ? nullptr : yb, 1, par);
+    if (!second) fa = put_row(ra, update ? norm_k : norm_q, xb, 0, par);
+    if (second || !SPLIT) fb = put_row(SPLIT ? ra : rb, update && norm_v, update ? nullptr : yb, 1, par);
   };
 
   // ---- 16x16 result layout: token 16 tb + 4 g4 + r, feature 16 db16 + l16
@@ -263,17 +290,71 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
       }
   };
 
+  // The same with FP32 row tiles (h = 128, where they fit): g goes through gt to
+  // the threads that hold the raw rows, eight features of a token each, which
+  // need no dots through LDS, no second read of K, V or Q, and store 16 bytes
+  // at a time; the additions are the same ones in the same order.
+  auto put_g = [&](const float (&v)[NBK][4]) {
+#pragma unroll
+    for (int bi = 0; bi < NBK; ++bi)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) gt[(16 * (tb0 + bi) + 4 * L.g4 + r) * FL + 16 * db16 + L.l16] = v[bi][r];
+  };
+  auto store_rows = [&](__amdgpu_buffer_rsrc_t rs, const RowPart<IOT, EPT>& raw, float f) {
+    float g[EPT], xh[EPT];
+#pragma unroll
+    for (int i = 0; i < EPT; i += 4) {
+      const f32x4 q = *reinterpret_cast<const f32x4*>(&gt[row * FL + col0 + i]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) g[i + e] = q[e];
+    }
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) xh[i] = mul_rn((float)raw.v[i], fabsf(f));
+    float dot = g[0] * xh[0];
+#pragma unroll
+    for (int i = 1; i < EPT; ++i) dot = fmaf(g[i], xh[i], dot);
+    dot = lane_group_sum<D / EPT>(dot);
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) g[i] = (f > 0.f ? fmaf(-xh[i], dot, g[i]) : g[i]) * fabsf(f);
+    if constexpr (SZ == 2) {
+      __builtin_amdgcn_raw_buffer_store_b128((u32x4){pack_bf16x2(g[0], g[1]), pack_bf16x2(g[2], g[3]),
+                                                     pack_bf16x2(g[4], g[5]), pack_bf16x2(g[6], g[7])},
+                                             rs, row_off, 0, 0);
+    } else {
+#pragma unroll
+      for (int i = 0; i < EPT; i += 4)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, (f32x4){g[i], g[i + 1], g[i + 2], g[i + 3]}),
+                                               rs, row_off + 4 * i, 0, 0);
+    }
+  };
+
+  // F32T (latency counts: its shards have a tile or a few): the rows are
+  // requested before the matrices and staged while those arrive; a shard past
+  // the last update tile starts with the apply.
+  const bool update = !F32T || g0 < n_gt;
+  fetch(update ? p.K : p.Q, update ? p.V : p.dO, update ? grad_start : app_start, update ? gl : al, g);
+  if constexpr (F32T) {
+    fence();
+    request();
+    fence();
+    stage_rows(update, 0);
+  }
   // ------------------------------------------------ update adjoint of chunk s
   raw_t vr[NBK][4];
-  fetch(p.K, p.V, grad_start, gl, g);
-  load_elems(tile_rs(p.V, grad_start, gl, g), vr);
+  if constexpr (!F32T) load_elems(tile_rs(p.V, grad_start, gl, g), vr);
 #pragma unroll
   for (int n = 0; n < 4 * DH / 8 / NT; ++n) {
     const int i = NT * n + threadIdx.x, k = i / (DH / 8), d = (i / (HH / 8)) & (D - 1), c = i % (HH / 8);
     *reinterpret_cast<bf16x8*>(&wl[k][d * HH + 8 * (c ^ (4 * (d & 3) + ((d >> 2) & 3)))]) = wf[n];
   }
-  stage_rows(true, 0);
-  for (int t = g, par = 0; t - grp < n_gt; t += G, par ^= 1) {
+  if constexpr (!F32T) stage_rows(true, 0);
+  int par = 0;  // parity of the staged tile
+  RowPart<IOT, EPT> ca = ra, cb = rb;  // F32T: raw rows of the staged tile and their factors
+  float cfa = fa, cfb = fb;
+  for (int t = g; t - grp < n_gt; t += G, par ^= 1) {
+    // F32T: the apply's first tile is fetched and staged behind the last update
+    // tile (at h = 256 the choice costs more per tile than the wait it saves)
+    const bool more = !F32T || t + G - grp < n_gt;
     // Addresses derived from the lane are formed where they are used.
     asm volatile("" : "+v"(L.l), "+v"(L.l16), "+v"(L.l32), "+v"(L.hf), "+v"(L.g4));
     __syncthreads();
@@ -300,7 +381,14 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
       contract(W2, y);
       contract(WH2, aw);
       float vh[NBK][4], vf[NBK][4];
-      unit(vr, vh, vf, 1, par);
+      if constexpr (F32T) {
+#pragma unroll
+        for (int bi = 0; bi < NBK; ++bi)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) vh[bi][r] = vt[(16 * (tb0 + bi) + 4 * L.g4 + r) * FL + 16 * db16 + L.l16];
+      } else {
+        unit(vr, vh, vf, 1, par);
+      }
 #pragma unroll
       for (int bi = 0; bi < NBK; ++bi) {
         f32x4 E;
@@ -357,8 +445,8 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
     __syncthreads();
     // dE = -eta A Wh2 + dP W2;  dY = (2/M) dE, dV = -dY
     raw_t kr[NBK][4];
-    load_elems(tile_rs(p.K, grad_start, gl, t), kr);
-    fetch(p.K, p.V, grad_start, gl, t + G);  // past the last tile: zeros
+    if constexpr (!F32T) load_elems(tile_rs(p.K, grad_start, gl, t), kr);
+    fetch(more ? p.K : p.Q, more ? p.V : p.dO, more ? grad_start : app_start, more ? gl : al, more ? t + G : g);
     fence();
     float gv[NBK][4], vh[NBK][4], vf[NBK][4];
     {
@@ -374,11 +462,18 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
         }
         put_rows(yb, bi, dY);
       }
-      unit(vr, vh, vf, 1, par);
-      put_dots(gv, vh, yb);
+      if constexpr (F32T) {
+        put_g(gv);
+      } else {
+        unit(vr, vh, vf, 1, par);
+        put_dots(gv, vh, yb);
+      }
     }
     __syncthreads();
-    store_adj(tile_rs(p.dV, grad_start, gl, t), gv, vh, vf, yb);
+    if constexpr (F32T)
+      store_rows(tile_rs(p.dV, grad_start, gl, t), cb, cfb);
+    else
+      store_adj(tile_rs(p.dV, grad_start, gl, t), gv, vh, vf, yb);
     // stage D;  dA = -eta E Wh2^T + dY W2^T;  dZ += dA s'(Z);  token sums dP^T E
     // + A^T dY (W2) and K^T dZ (W1)
     uint32_t dZpk[8];
@@ -415,7 +510,7 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
     }
     __syncthreads();
     // dK = -eta D Wh1^T + dZ W1^T
-    load_elems(tile_rs(p.V, grad_start, gl, t + G), vr);
+    if constexpr (!F32T) load_elems(tile_rs(p.V, grad_start, gl, t + G), vr);
     fence();
     f32x4 k1[NBK] = {}, k2[NBK] = {};
     contract(WH1, k1);
@@ -428,21 +523,35 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
     for (int bi = 0; bi < NBK; ++bi)
 #pragma unroll
       for (int r = 0; r < 4; ++r) gk[bi][r] = fmaf(-eta, k1[bi][r], k2[bi][r]);
-    unit(kr, kh, kf, 0, par);
-    put_dots(gk, kh, xb);
+    if constexpr (F32T) {
+      put_g(gk);
+    } else {
+      unit(kr, kh, kf, 0, par);
+      put_dots(gk, kh, xb);
+    }
     // the next tile's rows (the row tiles were last read before the sums' barrier)
-    stage_rows(true, par ^ 1);
+    stage_rows(more, par ^ 1);
     __syncthreads();
-    store_adj(tile_rs(p.dK, grad_start, gl, t), gk, kh, kf, xb);
+    if constexpr (F32T)
+      store_rows(tile_rs(p.dK, grad_start, gl, t), ca, cfa);
+    else
+      store_adj(tile_rs(p.dK, grad_start, gl, t), gk, kh, kf, xb);
+    ca = ra;
+    cb = rb;
+    cfa = fa;
+    cfb = fb;
   }
 
   // ------------------------------------------------ apply adjoint of chunk s-1
-  __syncthreads();  // the last update tile's row data are read
-  fetch(p.Q, p.dO, app_start, al, g);
-  stage_rows(false, 0);
-  for (int t = g, par = 0; t - grp < n_at; t += G, par ^= 1) {
+  if constexpr (!F32T) {
+    __syncthreads();  // the last update tile's row data are read
+    fetch(p.Q, p.dO, app_start, al, g);
+    par = 0;
+    stage_rows(false, par);
+  }
+  for (int t = g; t - grp < n_at; t += G, par ^= 1) {
     raw_t qr[NBK][4];
-    load_elems(tile_rs(p.Q, app_start, al, t), qr);
+    if constexpr (!F32T) load_elems(tile_rs(p.Q, app_start, al, t), qr);
     fetch(p.Q, p.dO, app_start, al, t + G);
     __syncthreads();
     // Zq = Q W1, dZq = (dO W2^T) s'(Zq); token sums Aq^T dO and Q^T dZq
@@ -487,11 +596,20 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
     for (int bi = 0; bi < NBK; ++bi)
 #pragma unroll
       for (int r = 0; r < 4; ++r) gq[bi][r] = c[bi][r];
-    unit(qr, qh, qf, 0, par);
-    put_dots(gq, qh, xb);
+    if constexpr (F32T) {
+      put_g(gq);
+    } else {
+      unit(qr, qh, qf, 0, par);
+      put_dots(gq, qh, xb);
+    }
     stage_rows(false, par ^ 1);
     __syncthreads();
-    store_adj(tile_rs(p.dQ, app_start, al, t), gq, qh, qf, xb);
+    if constexpr (F32T)
+      store_rows(tile_rs(p.dQ, app_start, al, t), ca, cfa);
+    else
+      store_adj(tile_rs(p.dQ, app_start, al, t), gq, qh, qf, xb);
+    ca = ra;
+    cfa = fa;
   }
 
   // ------------------------------------------------ shard partials
@@ -528,8 +646,8 @@ static hipError_t launch_bwd_step_bf_t(const BwdStepArgs& a, int n_blocks, hipSt
 hipError_t launch_bwd_step_bf(const BwdStepArgs& a, int n_blocks, int h, bool io_bf16, hipStream_t st) {
   if (h == 128) {
     // Up to one shard per CU each has a work-group of its own, past that two
-    // share one: 160 shards of one tile 14.2 against 16.2 us, 352 shards 18.5
-    // shared (22.4 for one work-group per shard without matrices in LDS).
+    // share one: 160 shards of one tile 13.2 against 16.0 us, 352 shards 23.4
+    // against 17.9 us.
     if (n_blocks <= 256)
       return io_bf16 ? launch_bwd_step_bf_t<bf16, 4, 1>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 4, 1>(a, n_blocks, st);
     return io_bf16 ? launch_bwd_step_bf_t<bf16, 4, 2>(a, n_blocks, st) : launch_bwd_step_bf_t<float, 4, 2>(a, n_blocks, st);
