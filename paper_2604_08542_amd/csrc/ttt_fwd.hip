@@ -800,29 +800,33 @@ __global__ __launch_bounds__(256) void ttt_update(UpdStepArgs p) {
       for (int e = 0; e < n_ent; ++e) {
         const int64_t sl = gcs ? (int64_t)e * p.H + head : slot;
         const f32x4* part = reinterpret_cast<const f32x4*>(p.partial + sl * p.G * 2 * dh) + i4;
-        // the shards past the last multiple of 4, for stream 0
-        const int nr = q == 0 ? p.G - g4 : 0;
-        f32x4 r[3];
+        // every stream has nq shards; the nr past the last multiple of 4 are stream 0's
+        const int nq = g4 >> 2, nr = p.G - g4;
+        f32x4 r[3] = {};
 #pragma unroll
-        for (int j = 0; j < 3; ++j) r[j] = part[(int64_t)(g4 < p.G ? min(g4 + j, p.G - 1) : 0) * n4];
-        // 8 loads in flight (past the stream's end: of its last shard, not
-        // added), added in shard order.  Before, only full eights were loaded
-        // together and the rest one by one: of 282 shards a chain of 8 chunks of
-        // 9,000 tokens, h = 128, takes 370 us against 399.
-        for (int gg = q; gg < g4; gg += 32) {
-          f32x4 v[8];
+        for (int j = 0; j < 3; ++j)
+          if (j < nr) r[j] = part[(int64_t)(g4 + j) * n4];
+        if (nq <= 2) {
+          if (nq > 0) sq += part[(int64_t)q * n4];
+          if (nq > 1) sq += part[(int64_t)(q + 4) * n4];
+        } else {
+          // 8 loads in flight (past the stream's end: of its last shard, not
+          // added), added in shard order
+          for (int k0 = 0; k0 < nq; k0 += 8) {
+            f32x4 v[8];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) v[j] = part[(int64_t)min(gg + 4 * j, g4 - 4 + q) * n4];
+            for (int j = 0; j < 8; ++j) v[j] = part[(int64_t)(q + 4 * min(k0 + j, nq - 1)) * n4];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const f32x4 a = sq + v[j];
-            sq = gg + 4 * j < g4 ? a : sq;
+            for (int j = 0; j < 8; ++j) {
+              const f32x4 a = sq + v[j];
+              sq = k0 + j < nq ? a : sq;
+            }
           }
         }
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
           const f32x4 a = sq + r[j];
-          sq = j < nr ? a : sq;
+          sq = q == 0 && j < nr ? a : sq;
         }
       }
       f32x4 t;  // lanes 0 and 2: s0 + s1 and s2 + s3
