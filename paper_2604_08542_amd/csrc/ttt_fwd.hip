@@ -890,9 +890,9 @@ __global__ __launch_bounds__(256) void ttt_update(UpdStepArgs p) {
 // wave per SIMD, and the 512 work-groups of a launch ran in two rounds; bounded
 // to 256 two work-groups share a CU: BF16, 16 heads x 6,000 tokens x 8 chunks 424
 // -> 347 us, all chunks synchronised 262 -> 183 us (BF16 products of FP32 rows,
-// which spill: 431 -> 409 and 284 -> 238 us).
-template <typename IOT, int NW, bool BF>
-__global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void ttt_fwd_step(FwdStepArgs p) {
+// which spill: 431 -> 409 and 284 -> 238 us).  WPS is that bound, waves per SIMD.
+template <typename IOT, int NW, bool BF, int WPS>
+__global__ __launch_bounds__(NW * 64, WPS) void ttt_fwd_step(FwdStepArgs p) {
   constexpr int DH = D * NW * 32;
   const int lin = xcd_linear_block();
   const int slot = lin / p.G, g = lin % p.G;
@@ -1144,21 +1144,28 @@ __global__ void ttt_zero_words(uint32_t* p, int n) {
 }
 
 // ----------------------------------------------------------------- launchers
-template <typename IOT, bool BF, int NW>
+template <typename IOT, bool BF, int NW, int WPS>
 static hipError_t launch_fwd_step_t(const FwdStepArgs& a, int n_blocks, hipStream_t st) {
-  hipLaunchKernelGGL((ttt_fwd_step<IOT, NW, BF>), dim3(n_blocks), dim3(NW * 64), 0, st, a);
+  hipLaunchKernelGGL((ttt_fwd_step<IOT, NW, BF, WPS>), dim3(n_blocks), dim3(NW * 64), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_fwd_step(const FwdStepArgs& a, int n_blocks, int h, bool io_bf16, bool mma_bf16, hipStream_t st) {
   if (h == 128) {
-    if (io_bf16) return launch_fwd_step_t<bf16, true, 4>(a, n_blocks, st);
-    return mma_bf16 ? launch_fwd_step_t<float, true, 4>(a, n_blocks, st)
-                    : launch_fwd_step_t<float, false, 4>(a, n_blocks, st);
+    // FP32 rows: bounded to two waves per SIMD the kernel spills (28 registers
+    // with BF16 products, 9 without), which pays only where a CU has two
+    // work-groups to run: 16 heads x 350 tokens (176 work-groups) x 4 chunks 68.0 us
+    // bounded, 64.7 not (FP32 products 90.8, 88.9); 16 heads x 700 tokens (352) x 8
+    // chunks 178 bounded, 205 not.
+    const bool one = n_blocks <= 256;
+    if (io_bf16) return launch_fwd_step_t<bf16, true, 4, 2>(a, n_blocks, st);
+    if (mma_bf16)
+      return one ? launch_fwd_step_t<float, true, 4, 1>(a, n_blocks, st) : launch_fwd_step_t<float, true, 4, 2>(a, n_blocks, st);
+    return one ? launch_fwd_step_t<float, false, 4, 1>(a, n_blocks, st) : launch_fwd_step_t<float, false, 4, 2>(a, n_blocks, st);
   }
-  if (io_bf16) return launch_fwd_step_t<bf16, true, 8>(a, n_blocks, st);
-  return mma_bf16 ? launch_fwd_step_t<float, true, 8>(a, n_blocks, st)
-                  : launch_fwd_step_t<float, false, 8>(a, n_blocks, st);
+  if (io_bf16) return launch_fwd_step_t<bf16, true, 8, 1>(a, n_blocks, st);
+  return mma_bf16 ? launch_fwd_step_t<float, true, 8, 1>(a, n_blocks, st)
+                  : launch_fwd_step_t<float, false, 8, 1>(a, n_blocks, st);
 }
 
 hipError_t launch_update(const UpdStepArgs& a, int n_blocks, hipStream_t st) {
