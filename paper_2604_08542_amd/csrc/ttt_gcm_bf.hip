@@ -146,8 +146,8 @@ struct EpGateBwd : Ep<EpGateBwd> {
       const bool hi = l & m;
 #pragma unroll
       for (int i = 0; i < k; ++i) {
-        const float give = hi ? v[i] : v[i + k], keep = hi ? v[i + k] : v[i];
-        v[i] = keep + __shfl_xor(give, m, 64);
+        const float a = v[i], b = v[i + k];  // (a choice between the elements themselves puts v in scratch)
+        v[i] = (hi ? b : a) + __shfl_xor(hi ? a : b, m, 64);
       }
     }
     return v[0] + __shfl_xor(v[0], 1, 64);
