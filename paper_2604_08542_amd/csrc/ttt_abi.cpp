@@ -273,14 +273,14 @@ WsLayout ws_layout(const Shape& s, int64_t n_chains) {
   L.pp = off;  // forward: ping-pong weights per chain
   off = align_up(off + 2 * (size_t)n_chains * wbytes);
   // backward: two adjoint buffers per chain, the recomputed last weights,
-  // operand copies (8 matrices per chain of one launch, float-sized slots),
+  // operand copies (per chain of one launch eight matrices, in BF16 four),
   // per-sequence final adjoints and d(eta) sums (shared initial weights)
   L.adj = off;
   off = align_up(off + 2 * (size_t)n_chains * wbytes);
   L.wlast = off;
   off = align_up(off + (size_t)n_chains * wbytes);
   L.prep = off;
-  off = align_up(off + (size_t)std::min<int64_t>(n_chains, (int64_t)MAXS * s.H) * 8 * s.dh() * sizeof(float));
+  off = align_up(off + (size_t)std::min<int64_t>(n_chains, (int64_t)MAXS * s.H) * s.dh() * (s.mma_bf16 ? 4 * 2 : 8 * 4));
   L.fin = off;
   off = align_up(off + (size_t)n_chains * wbytes);
   L.deta_seq = off;

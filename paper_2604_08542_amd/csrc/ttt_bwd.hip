@@ -404,10 +404,16 @@ __global__ __launch_bounds__(NW * 64, 2) void ttt_bwd_step(BwdStepArgs p) {
 }
 
 // Operand copies for one backward step, per (active sequence, head): W_s and
-// the carried adjoint Wh (zeros when absent), each of W1 [d][h] and W2 [h][d]
-// written in the matrix-core operand type as [hid][d] and [d][hid] (BF16: only
-// the latter, ttt_bwd_step_bf transposes as it reads), so that every operand
-// fragment is one contiguous vector load.
+// the carried adjoint Wh (zeros when absent) in the matrix-core operand type:
+// with FP32 products W1, W2, Wh1, Wh2 as [hid][d], then the four as [d][hid], so
+// that every operand fragment is one contiguous vector load; in BF16 the latter
+// four alone (ttt_bwd_step_bf transposes as it reads).
+template <typename MT>
+struct Copies {
+  static constexpr bool HD = std::is_same_v<MT, float>;  // [hid][d] too
+  static constexpr int DH = HD ? 4 : 0;                  // first [d][hid] matrix
+  static constexpr int N = DH + 4;
+};
 template <typename MT>
 __global__ __launch_bounds__(256) void ttt_bwd_prep(BwdPrepArgs p) {
   const int dh = D * p.h;
@@ -417,22 +423,23 @@ __global__ __launch_bounds__(256) void ttt_bwd_prep(BwdPrepArgs p) {
   if (idx >= dh) return;
   const float* W = p.w_src[ai] + (int64_t)head * 2 * dh;
   const float* Wh = p.wh_src[ai] ? p.wh_src[ai] + (int64_t)head * 2 * dh : nullptr;
-  MT* o = static_cast<MT*>(p.prep) + (int64_t)chain * 8 * dh;
+  MT* o = static_cast<MT*>(p.prep) + (int64_t)chain * Copies<MT>::N * dh;
   const int h = p.h;
   const int d = idx / h, hh = idx % h;    // idx = d*h + hh: W1 element (d, hh)
   const int hh2 = idx / D, d2 = idx % D;  // idx = hh2*D + d2: W2 element (hh2, d2)
   const float w1 = W[idx], h1 = Wh ? Wh[idx] : 0.f;
   const float w2 = W[dh + idx], h2 = Wh ? Wh[dh + idx] : 0.f;
-  if constexpr (std::is_same_v<MT, float>) {
+  if constexpr (Copies<MT>::HD) {
     o[0 * dh + hh * D + d] = (MT)w1;     // W1 as [hid][d]
     o[1 * dh + idx] = (MT)w2;            // W2 as [hid][d]
     o[2 * dh + hh * D + d] = (MT)h1;
     o[3 * dh + idx] = (MT)h2;
   }
-  o[4 * dh + idx] = (MT)w1;            // W1 as [d][hid]
-  o[5 * dh + d2 * h + hh2] = (MT)w2;   // W2 as [d][hid]
-  o[6 * dh + idx] = (MT)h1;
-  o[7 * dh + d2 * h + hh2] = (MT)h2;
+  o += Copies<MT>::DH * dh;
+  o[0 * dh + idx] = (MT)w1;            // W1 as [d][hid]
+  o[1 * dh + d2 * h + hh2] = (MT)w2;   // W2 as [d][hid]
+  o[2 * dh + idx] = (MT)h1;
+  o[3 * dh + d2 * h + hh2] = (MT)h2;
 }
 
 hipError_t launch_bwd_prep(const BwdPrepArgs& a, int n_active, bool mma_bf16, hipStream_t st) {
@@ -451,19 +458,20 @@ template <typename MT>
 __device__ __forceinline__ void put_prep(MT* o, int idx, int dh, int h, const f32x4& w, const f32x4& wh) {
   typedef MT mt4 __attribute__((ext_vector_type(4)));
   const mt4 m = {(MT)w[0], (MT)w[1], (MT)w[2], (MT)w[3]}, mh = {(MT)wh[0], (MT)wh[1], (MT)wh[2], (MT)wh[3]};
-  constexpr bool HD = std::is_same_v<MT, float>;  // [hid][d] too
+  constexpr bool HD = Copies<MT>::HD;
+  MT* od = o + Copies<MT>::DH * dh;
   const int i0 = idx - 4 * (int)threadIdx.x;
   if (i0 < dh) {
-    *reinterpret_cast<mt4*>(o + 4 * dh + idx) = m;
-    *reinterpret_cast<mt4*>(o + 6 * dh + idx) = mh;
+    *reinterpret_cast<mt4*>(od + idx) = m;
+    *reinterpret_cast<mt4*>(od + 2 * dh + idx) = mh;
     if constexpr (HD) {
       put_transposed(o + 0 * dh + i0 / h, D, h, h, w);
       put_transposed(o + 2 * dh + i0 / h, D, h, h, wh);
     }
   } else {
     const int i2 = idx - dh;
-    put_transposed(o + 5 * dh + (i0 - dh) / D, h, D, h, w);
-    put_transposed(o + 7 * dh + (i0 - dh) / D, h, D, h, wh);
+    put_transposed(od + 1 * dh + (i0 - dh) / D, h, D, h, w);
+    put_transposed(od + 3 * dh + (i0 - dh) / D, h, D, h, wh);
     if constexpr (HD) {
       *reinterpret_cast<mt4*>(o + 1 * dh + i2) = m;
       *reinterpret_cast<mt4*>(o + 3 * dh + i2) = mh;
@@ -502,13 +510,13 @@ __global__ __launch_bounds__(256) void ttt_bwd_reduce(BwdReduceArgs p) {
       *reinterpret_cast<f32x4*>((final ? p.fin_base : p.wh_dst_base) + cw + idx) = s;
     }
     if (p.prep_next && p.next_slot[ai] >= 0) {
-      const int64_t pc = ((int64_t)p.next_slot[ai] * p.H + head) * 8 * dh;
+      const int64_t pc = (int64_t)p.next_slot[ai] * p.H + head;
       const f32x4 wv =
           *reinterpret_cast<const f32x4*>(p.ckpt + (p.ckpt_row[ai] * p.H + head) * 2 * dh + idx);
       if (p.prep_bf16)
-        put_prep(static_cast<bf16*>(p.prep_next) + pc, idx, dh, p.h, wv, s);
+        put_prep(static_cast<bf16*>(p.prep_next) + pc * Copies<bf16>::N * dh, idx, dh, p.h, wv, s);
       else
-        put_prep(static_cast<float*>(p.prep_next) + pc, idx, dh, p.h, wv, s);
+        put_prep(static_cast<float*>(p.prep_next) + pc * Copies<float>::N * dh, idx, dh, p.h, wv, s);
     }
   }
   if (k == 0 && threadIdx.x == 0) {

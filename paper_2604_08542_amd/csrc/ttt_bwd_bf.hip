@@ -90,7 +90,7 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
   const int slot = lin / per_slot, g0 = lin % per_slot * NG, g = g0 + grp;
   const int ai = slot / p.H, head = slot % p.H;
   const float eta = p.eta;
-  const bf16* prep = static_cast<const bf16*>(p.prep) + (int64_t)slot * 8 * DH;
+  const bf16* prep = static_cast<const bf16*>(p.prep) + (int64_t)slot * 4 * DH;
   const int64_t hoff = (int64_t)head * p.stride_head;
   const bool norm_q = p.flags & 1u, norm_k = p.flags & 2u, norm_v = p.flags & 4u;
 
@@ -100,8 +100,7 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
   // projection (norm at the floor, or not normalised).
   auto pad = [](bf16* t, int row) { return reinterpret_cast<float*>(t + row * RL + D); };
 
-  // Matrices (of the prepared operands, 0..3 are W1, W2, Wh1, Wh2 as [hid][d],
-  // 4..7 the same as [d][hid]): all four in LDS as [d][hid], row d's 16-byte
+  // Matrices (W1, W2, Wh1, Wh2 as [d][hid]): all four in LDS, row d's 16-byte
   // chunk c at c ^ (4 (d & 3) + (d / 4 & 3)), which spreads both the straight
   // reads of 16 rows (contractions over hid) and the transposing ones of 4
   // rows x 64 bytes (contractions over d) over all banks; W1 and W2, which
@@ -111,7 +110,7 @@ __global__ __launch_bounds__(NW * NG * 64) void ttt_bwd_step_bf(BwdStepArgs p) {
   auto request = [&] {
 #pragma unroll
     for (int n = 0; n < 4 * DH / 8 / NT; ++n)
-      wf[n] = *reinterpret_cast<const bf16x8*>(prep + 4 * DH + (NT * n + threadIdx.x) * 8);
+      wf[n] = *reinterpret_cast<const bf16x8*>(prep + (NT * n + threadIdx.x) * 8);
   };
   if constexpr (!F32T) request();
   // The wave's 16x16 output blocks: features 16 db .., token halves tb0 ..

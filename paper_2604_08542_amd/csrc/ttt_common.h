@@ -346,7 +346,7 @@ struct BwdStepArgs {
   void* dK;
   void* dV;
   int64_t stride_tok, stride_head;
-  const void* prep;     // per (active sequence, head) 8 operand matrices of D*h (see ttt_bwd_prep)
+  const void* prep;     // per (active sequence, head) eight (BF16: four) operand matrices of D*h (see ttt_bwd_prep)
   int32_t H;
   uint32_t flags;
   float eta;

@@ -276,10 +276,10 @@ hipError_t launch_gcm_gemm_bf(const GcmGemmArgs& a, hipStream_t st) {
     if (a.kind == 0) {
       EpBias ep{{}, {static_cast<bf16*>(a.q) + off, static_cast<bf16*>(a.k) + off, static_cast<bf16*>(a.v) + off},
                 a.bias, D, D};
-      gemm<KMAJ, MNMAJ, 1>(product(static_cast<const bf16*>(a.x) + off, D, rows, w, 3 * D, D, rows, 3 * D, D), ep, st);
+      gemm<MNMAJ, 1>(product(static_cast<const bf16*>(a.x) + off, D, rows, w, 3 * D, D, rows, 3 * D, D), ep, st);
     } else {
       EpGate ep{{}, static_cast<bf16*>(a.y) + off, static_cast<const bf16*>(a.x) + off, a.bias, a.alpha, D};
-      gemm<KMAJ, MNMAJ, 1>(product(static_cast<const bf16*>(a.o) + off, D, rows, w, D, D, rows, D, D), ep, st);
+      gemm<MNMAJ, 1>(product(static_cast<const bf16*>(a.o) + off, D, rows, w, D, D, rows, D, D), ep, st);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -294,13 +294,13 @@ hipError_t launch_gcm_bwd_bf(const GcmBwdArgs& a, hipStream_t st) {
   auto P = [](void* p) { return static_cast<bf16*>(p); };
   if (a.phase == 0) {
     EpBias ep{{}, {P(a.P), nullptr, nullptr}, a.bqkv, D3, 0};
-    gemm<KMAJ, MNMAJ, 1>(product(C(a.X), D, rows, C(a.Wqkv), D3, D, rows, D3, D), ep, st);
+    gemm<MNMAJ, 1>(product(C(a.X), D, rows, C(a.Wqkv), D3, D, rows, D3, D), ep, st);
   } else if (a.phase == 1) {
     const bf16* O = C(a.O);
     EpGateBwd eg{{}, P(a.dG), C(a.dY), a.bo, a.alpha, a.part, D};
     const GemmArgs g = product(O, D3, rows, C(a.Wo), D, D, rows, D, D);
     // the partials sit at the first rows of the waves' shares of the tiles
-    const int step = gemm<KMAJ, MNMAJ, 1>(g, eg, st).blocks;
+    const int step = gemm<MNMAJ, 1>(g, eg, st).blocks;
     const int n = ((rows + 31) / 32 + step - 1) / step;
     const int64_t pitch = (int64_t)step * 2 * D;
     const dim3 cs((D + 63) / 64);
@@ -308,7 +308,7 @@ hipError_t launch_gcm_bwd_bf(const GcmBwdArgs& a, hipStream_t st) {
     if (a.dbo) hipLaunchKernelGGL(k_colsums, cs, dim3(1024), 0, st, a.part + D, n, pitch, D, a.dbo);
     weight_grad(O, D3, C(a.dG), D, D, D, rows, a.runs_o, a.dWo, a.part_o, st);
     EpBias eo{{}, {P(a.dO), nullptr, nullptr}, nullptr, D3, 0};
-    gemm<KMAJ, KMAJ, 1>(product(C(a.dG), D, rows, C(a.Wo), D, D, rows, D, D), eo, st);
+    gemm<KMAJ, 1>(product(C(a.dG), D, rows, C(a.Wo), D, D, rows, D, D), eo, st);
   } else {
     const bf16* dP = C(a.dP);
     weight_grad(C(a.X), D, dP, D3, D, D3, rows, a.runs_p, a.dWqkv, a.part_p, st);
@@ -318,7 +318,7 @@ hipError_t launch_gcm_bwd_bf(const GcmBwdArgs& a, hipStream_t st) {
       hipLaunchKernelGGL(k_colsums, dim3((D3 + 63) / 64), dim3(1024), 0, st, a.part, ns, (int64_t)D3, D3, a.dbqkv);
     }
     EpAdd ex{{}, P(a.dX), C(a.dY), D};
-    gemm<KMAJ, KMAJ, 1>(product(dP, D3, rows, C(a.Wqkv), D3, D, rows, D, D3), ex, st);
+    gemm<KMAJ, 1>(product(dP, D3, rows, C(a.Wqkv), D3, D, rows, D, D3), ex, st);
   }
   return hipGetLastError();
 }

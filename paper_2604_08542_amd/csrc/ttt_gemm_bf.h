@@ -58,7 +58,7 @@ struct Tile {
   static_assert(WM * WN == NW, "8 waves");
 };
 using TileL = Tile<4, 2, 2, 4>;   // 256 x 256
-using TileM = Tile<3, 2, 2, 4>;   // 192 x 256 (k-major A)
+using TileM = Tile<3, 2, 2, 4>;   // 192 x 256
 using TileH = Tile<2, 2, 2, 4>;   // 128 x 256
 using TileS = Tile<1, 2, 4, 2>;   // 128 x 128
 using TileL4 = Tile<2, 4, 4, 2>;  // 256 x 4 matrices of 64 columns
@@ -362,18 +362,17 @@ __device__ __forceinline__ void tile_at(int t, int mt, int nt, int& im, int& in)
 }
 // This work-group's index with the work-groups of one XCD consecutive.
 __device__ __forceinline__ int xcd_index(int& first, int& count, int total) {
-  const int x = blockIdx.x & 7, nb = gridDim.x;
+  const int x = blockIdx.x & 7;
   // XCD x owns items [first, first + count) of total
   const int q = total >> 3, r = total & 7;
   first = x * q + min(x, r);
   count = q + (x < r);
-  (void)nb;
   return blockIdx.x >> 3;
 }
 
-template <class TL, int LA, int LB, int NMAT, class EP>
+template <class TL, int LB, int NMAT, class EP>
 __global__ __launch_bounds__(NTHR) void k_gemm(GemmArgs g, EP ep) {
-  using MC = Machine<TL, LA, LB, NMAT>;
+  using MC = Machine<TL, KMAJ, LB, NMAT>;
   constexpr int CN = TL::BN / NMAT;  // columns per tile (of each matrix)
   __shared__ __attribute__((aligned(1024))) char sm[MC::LDS];
   MC mc;
@@ -382,7 +381,7 @@ __global__ __launch_bounds__(NTHR) void k_gemm(GemmArgs g, EP ep) {
   int first, count;
   const int j0 = xcd_index(first, count, mt * nt), stride = (gridDim.x + 7 - (blockIdx.x & 7)) >> 3;
   const int nks = (g.K + KS - 1) / KS, nk = nks * g.nseg;
-  const int ka = MC::kbytes(LA, g.lda), kb = MC::kbytes(LB, g.ldb);
+  const int ka = MC::kbytes(KMAJ, g.lda), kb = MC::kbytes(LB, g.ldb);
   // the load cursor: tile index, segment, slice of the segment
   u32x4 ra, rb[MC::PB];
   int lt = j0, lseg = 0, lk = 0;
@@ -503,11 +502,11 @@ inline int64_t gemm_tiles(int cfg, int M, int N, int nmat) {
   const int cn = nmat == 4 ? 64 : (cfg == T_S ? 128 : 256) / nmat;
   return (int64_t)((M + bm - 1) / bm) * (N / cn);
 }
-inline int pick_tile(int M, int N, int nmat, int64_t K, bool kmaj_a) {
+inline int pick_tile(int M, int N, int nmat, int64_t K) {
   int best = T_S;
   double bc = 1e30;
   for (int cfg : {T_L, T_M, T_S}) {
-    if (cfg == T_M && (!kmaj_a || nmat == 4)) continue;
+    if (cfg == T_M && nmat == 4) continue;
     if (nmat < 4 && N % ((cfg == T_S ? 128 : 256) / nmat)) continue;
     const int bm = cfg == T_L ? 256 : cfg == T_M ? 192 : 128, bn = cfg == T_S && nmat < 4 ? 128 : 256;
     const double rate = cfg == T_L ? 5.2e6 : cfg == T_M ? 5.0e6 : (nmat == 4 ? 4.0e6 : 2.9e6);
@@ -521,26 +520,24 @@ inline int pick_tile(int M, int N, int nmat, int64_t K, bool kmaj_a) {
   return best;
 }
 
-template <class TL, int LA, int LB, int NMAT, class EP>
+template <class TL, int LB, int NMAT, class EP>
 inline Launched launch_tile(const GemmArgs& g, const EP& ep, int64_t tiles, hipStream_t st) {
   const int grid = (int)std::min<int64_t>(tiles, MAX_WG);
-  hipLaunchKernelGGL((k_gemm<TL, LA, LB, NMAT, EP>), dim3(grid), dim3(NTHR), 0, st, g, ep);
+  hipLaunchKernelGGL((k_gemm<TL, LB, NMAT, EP>), dim3(grid), dim3(NTHR), 0, st, g, ep);
   return {grid, TL::MB};
 }
-// Launches one product.
-template <int LA, int LB, int NMAT, class EP>
+// Launches one product (A k-major, B in layout LB).
+template <int LB, int NMAT, class EP>
 inline Launched gemm(const GemmArgs& g, const EP& ep, hipStream_t st) {
-  const int cfg = pick_tile(g.M, g.N, NMAT, (int64_t)g.K * g.nseg, LA == KMAJ);
+  const int cfg = pick_tile(g.M, g.N, NMAT, (int64_t)g.K * g.nseg);
   const int64_t tiles = gemm_tiles(cfg, g.M, g.N, NMAT);
   if constexpr (NMAT == 4) {
-    if (cfg == T_L) return launch_tile<TileL4, LA, LB, NMAT>(g, ep, tiles, st);
-    return launch_tile<TileS4, LA, LB, NMAT>(g, ep, tiles, st);
+    if (cfg == T_L) return launch_tile<TileL4, LB, NMAT>(g, ep, tiles, st);
+    return launch_tile<TileS4, LB, NMAT>(g, ep, tiles, st);
   } else {
-    if (cfg == T_L) return launch_tile<TileL, LA, LB, NMAT>(g, ep, tiles, st);
-    if constexpr (LA == KMAJ) {
-      if (cfg == T_M) return launch_tile<TileM, LA, LB, NMAT>(g, ep, tiles, st);
-    }
-    return launch_tile<TileS, LA, LB, NMAT>(g, ep, tiles, st);
+    if (cfg == T_L) return launch_tile<TileL, LB, NMAT>(g, ep, tiles, st);
+    if (cfg == T_M) return launch_tile<TileM, LB, NMAT>(g, ep, tiles, st);
+    return launch_tile<TileS, LB, NMAT>(g, ep, tiles, st);
   }
 }
 static_assert(MAX_WG == 256 && NW == 8, "sum_parts counts the waves of a launch");

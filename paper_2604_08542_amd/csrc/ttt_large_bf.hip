@@ -180,12 +180,12 @@ static hipError_t step_bf(const LargeStepArgs& a, hipStream_t st) {
   if (en != hipSuccess) return en;
   if (a.grad) {
     EpAct<true> e1{{}, A, S1, h};
-    gemm<KMAJ, MNMAJ, 1>(product(Kn, d, M, W1, h, d, M, h, d), e1, st);
+    gemm<MNMAJ, 1>(product(Kn, d, M, W1, h, d, M, h, d), e1, st);
     EpRes<IOT> e2{{}, E, static_cast<const IOT*>(a.V), a.Vn, a.stride_tok, a.loss_part, d, 2.0f / (float)M};
-    const int wgs = gemm<KMAJ, MNMAJ, 1>(product(A, h, M, W2, d, h, M, d, h), e2, st).wgs;
+    const int wgs = gemm<MNMAJ, 1>(product(A, h, M, W2, d, h, M, d, h), e2, st).wgs;
     if (a.loss) hipLaunchKernelGGL(k_loss, dim3(1), dim3(256), 0, st, a.loss_part, wgs * NW, 1.0f / (float)M, a.loss);
     EpD e3{{}, D, S1, h};
-    gemm<KMAJ, KMAJ, 1>(product(E, d, M, W2, d, h, M, h, d), e3, st);
+    gemm<KMAJ, 1>(product(E, d, M, W2, d, h, M, h, d), e3, st);
     WArgs w{};
     w.tokens = M;
     add_weight(w, Kn, d, D, h, d, h, a.W1, a.masters_only ? nullptr : W1, -a.eta, 1);
@@ -194,9 +194,9 @@ static hipError_t step_bf(const LargeStepArgs& a, hipStream_t st) {
   }
   if (a.O) {
     EpAct<false> e6{{}, Aq, nullptr, h};
-    gemm<KMAJ, MNMAJ, 1>(product(Qn, d, M, W1, h, d, M, h, d), e6, st);
+    gemm<MNMAJ, 1>(product(Qn, d, M, W1, h, d, M, h, d), e6, st);
     EpOut<IOT> e7{{}, static_cast<IOT*>(a.O), a.stride_tok};
-    gemm<KMAJ, MNMAJ, 1>(product(Aq, h, M, W2, d, h, M, d, h), e7, st);
+    gemm<MNMAJ, 1>(product(Aq, h, M, W2, d, h, M, d, h), e7, st);
   }
   return hipGetLastError();
 }
@@ -226,9 +226,9 @@ static hipError_t amu_step_bf(const LargeAmuArgs& a, hipStream_t st) {
     GemmArgs z = product(Kn, d, M, W1, h, d, M, h, d);
     z.B[1] = W3;
     EpSwi<true> e2{{}, Hd, G1, G3, h};
-    gemm<KMAJ, MNMAJ, 2>(z, e2, st);
+    gemm<MNMAJ, 2>(z, e2, st);
     EpD2 e3{{}, G1, G3, D1, D3, h};
-    gemm<KMAJ, KMAJ, 1>(product(E, d, M, W2, d, h, M, h, d), e3, st);
+    gemm<KMAJ, 1>(product(E, d, M, W2, d, h, M, h, d), e3, st);
     // the step sizes are inside the loss: W <- W - grad
     WArgs w{};
     w.tokens = M;
@@ -241,9 +241,9 @@ static hipError_t amu_step_bf(const LargeAmuArgs& a, hipStream_t st) {
     GemmArgs z = product(Qn, d, M, W1, h, d, M, h, d);
     z.B[1] = W3;
     EpSwi<false> e7{{}, Hd, nullptr, nullptr, h};
-    gemm<KMAJ, MNMAJ, 2>(z, e7, st);
+    gemm<MNMAJ, 2>(z, e7, st);
     EpOut<IOT> e8{{}, static_cast<IOT*>(a.O), a.stride_tok};
-    gemm<KMAJ, MNMAJ, 1>(product(Hd, h, M, W2, d, h, M, d, h), e8, st);
+    gemm<MNMAJ, 1>(product(Hd, h, M, W2, d, h, M, d, h), e8, st);
   }
   return hipGetLastError();
 }
@@ -264,7 +264,7 @@ hipError_t launch_large_amu_step_bf(const LargeAmuArgs& a, bool io_bf16, hipStre
 // of the tiles of a launch of weight terms.  Not part of the C ABI.
 extern "C" int32_t ttt_internal_gemm_tile(int32_t M, int32_t N, int32_t nmat, int64_t K) {
   using namespace ttt::bfg;
-  const int cfg = pick_tile(M, N, nmat, K, true);
+  const int cfg = pick_tile(M, N, nmat, K);
   return cfg == T_L ? 256 : cfg == T_M ? 192 : 128;
 }
 extern "C" int32_t ttt_internal_wgrad_tile(int32_t np, const int32_t* M, const int32_t* N, const int32_t* nterm,

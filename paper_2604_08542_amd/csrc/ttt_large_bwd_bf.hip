@@ -534,40 +534,40 @@ static hipError_t bwd_step_bf(const LargeBwdArgs& a, hipStream_t st) {
     int ldo = d;
     const bf16* dO = rows_operand<IOT>(a.dO, a.stride_tok, a.dOn, M, d, &ldo, st);
     EpAct<true> e4{{}, Aq, Sq1, h};
-    gemm<KMAJ, MNMAJ, 1>(product(Qn, d, M, W1n, h, d, M, h, d), e4, st);
+    gemm<MNMAJ, 1>(product(Qn, d, M, W1n, h, d, M, h, d), e4, st);
     EpD e6{{}, dZq, Sq1, h};
-    gemm<KMAJ, KMAJ, 1>(product(dO, ldo, M, W2n, d, h, M, h, d), e6, st);
+    gemm<KMAJ, 1>(product(dO, ldo, M, W2n, d, h, M, h, d), e6, st);
     WArgs w{};
     w.tokens = M;
     add_weight(w, Aq, h, dO, ldo, h, d, a.Wh2, Wh2, 1.0f, 1);
     add_weight(w, Qn, d, dZq, h, d, h, a.Wh1, Wh1, 1.0f, 1);
     wgrad(w, st);
     EpF32 e8{{}, a.dq, d, 1.0f};
-    gemm<KMAJ, KMAJ, 1>(product(dZq, h, M, W1n, h, d, M, d, h), e8, st);
+    gemm<KMAJ, 1>(product(dZq, h, M, W1n, h, d, M, d, h), e8, st);
   }
   if (a.update) {
     EpAct3 e1{{}, A, S1, S2, h};
-    gemm<KMAJ, MNMAJ, 1>(product(Kn, d, M, W1, h, d, M, h, d), e1, st);
+    gemm<MNMAJ, 1>(product(Kn, d, M, W1, h, d, M, h, d), e1, st);
     GemmArgs yu = product(A, h, M, W2, d, h, M, d, h);
     yu.B[1] = Wh2;
     EpYU<IOT> e2{{}, E, a.dE, static_cast<const IOT*>(a.V), vinv, a.stride_tok, a.deta_part, d, scale, eta};
-    const int n1 = gemm<KMAJ, MNMAJ, 2>(yu, e2, st).wgs * NW;
+    const int n1 = gemm<MNMAJ, 2>(yu, e2, st).wgs * NW;
     GemmArgs pe = product(E, d, M, W2, d, h, M, h, d);
     pe.B[1] = Wh2;
     EpPE e3{{}, D, Dn, Pn, EWh, S1, h};
-    gemm<KMAJ, KMAJ, 2>(pe, e3, st);
+    gemm<KMAJ, 2>(pe, e3, st);
     EpU1 e9{{}, dP, dZa, Dn, S1, Pn, S2, a.deta_part + n1, h, eta};
-    const int n2 = gemm<KMAJ, MNMAJ, 1>(product(Kn, d, M, Wh1, h, d, M, h, d), e9, st).wgs * NW;
+    const int n2 = gemm<MNMAJ, 1>(product(Kn, d, M, Wh1, h, d, M, h, d), e9, st).wgs * NW;
     hipLaunchKernelGGL(k_deta, dim3(1), dim3(256), 0, st, a.deta_part, n1 + n2, a.deta);
     EpDY e11{{}, dY, a.dv, a.dE, d, scale};
-    gemm<KMAJ, MNMAJ, 1>(product(dP, h, M, W2, d, h, M, d, h), e11, st);
+    gemm<MNMAJ, 1>(product(dP, h, M, W2, d, h, M, d, h), e11, st);
     EpDZ e13{{}, dZ, EWh, dZa, S1, h, eta};
-    gemm<KMAJ, KMAJ, 1>(product(dY, d, M, W2, d, h, M, h, d), e13, st);
+    gemm<KMAJ, 1>(product(dY, d, M, W2, d, h, M, h, d), e13, st);
     GemmArgs dk = product(D, h, M, Wh1, h, d, M, d, h);
     dk.A[1] = dZ; dk.B[1] = W1;
     dk.nseg = 2; dk.seg0_scale = -eta;
     EpF32 e14{{}, a.dk, d, 1.0f};
-    gemm<KMAJ, KMAJ, 1>(dk, e14, st);
+    gemm<KMAJ, 1>(dk, e14, st);
     // the weight terms of the update adjoint (the adjoint of W_c in the chain)
     WArgs w{};
     w.tokens = M;
@@ -606,9 +606,9 @@ static hipError_t amu_bwd_step_bf(const LargeAmuBwdArgs& a, hipStream_t st) {
     GemmArgs z = product(Qn, d, M, W1n, h, d, M, h, d);
     z.B[1] = W3n;
     EpSwi<true> q1{{}, Hd, S1, S, h};  // Hq, F1, F3
-    gemm<KMAJ, MNMAJ, 2>(z, q1, st);
+    gemm<MNMAJ, 2>(z, q1, st);
     EpD2 q2{{}, S1, S, aZ1, aZ3, h};  // dZq1, dZq3
-    gemm<KMAJ, KMAJ, 1>(product(dO, ldo, M, W2n, d, h, M, h, d), q2, st);
+    gemm<KMAJ, 1>(product(dO, ldo, M, W2n, d, h, M, h, d), q2, st);
     WArgs w{};
     w.tokens = M;
     add_weight(w, Qn, d, aZ1, h, d, h, a.Wh[0], Wh1, 1.0f, 1);
@@ -619,29 +619,29 @@ static hipError_t amu_bwd_step_bf(const LargeAmuBwdArgs& a, hipStream_t st) {
     q.A[1] = aZ3; q.B[1] = W3n;
     q.nseg = 2;
     EpF32 g1{{}, a.dq, d, 1.0f};
-    gemm<KMAJ, KMAJ, 1>(q, g1, st);
+    gemm<KMAJ, 1>(q, g1, st);
   }
   if (a.update) {
     GemmArgs z = product(Kn, d, M, W1, h, d, M, h, d);
     z.B[1] = W3; z.B[2] = Wh1; z.B[3] = Wh3;
     EpTan e1{{}, Hd, Hdot, S, S1, Z3, Zd3, Sd, T2, h};
-    gemm<KMAJ, MNMAJ, 4>(z, e1, st);
+    gemm<MNMAJ, 4>(z, e1, st);
     GemmArgs y = product(Hdot, h, M, W2, d, h, M, d, h);
     y.A[1] = Hd; y.B[1] = Wh2;
     y.nseg = 2;
     EpF32 ey{{}, a.Ydot, d, 1.0f};
-    gemm<KMAJ, MNMAJ, 1>(y, ey, st);
+    gemm<MNMAJ, 1>(y, ey, st);
     GemmArgs dh = product(E, d, M, W2, d, h, M, h, d);
     dh.B[1] = Wh2;
     EpAdj e9{{}, Z3, Sd, S, Zd3, S1, T2, aZ1, aZ3, aZd1, aZd3, h};
-    gemm<KMAJ, KMAJ, 2>(dh, e9, st);
+    gemm<KMAJ, 2>(dh, e9, st);
     GemmArgs k = product(aZ1, h, M, W1, h, d, M, d, h);
     k.A[1] = aZ3; k.B[1] = W3;
     k.A[2] = aZd1; k.B[2] = Wh1;
     k.A[3] = aZd3; k.B[3] = Wh3;
     k.nseg = 4;
     EpF32 ek{{}, a.dk, d, -1.0f};
-    gemm<KMAJ, KMAJ, 1>(k, ek, st);
+    gemm<KMAJ, 1>(k, ek, st);
     // the weight terms (after the last use of Wh, which they change in the chain)
     WArgs w{};
     w.tokens = M;
