@@ -19,9 +19,8 @@ __device__ __forceinline__ float silu_sig(float z, float& sg) {
   return z * sg;
 }
 
-template <typename T>
-__device__ __forceinline__ void put(T* p, float v) {
-  *p = (T)v;
+__device__ __forceinline__ void put(float* p, float v) {
+  *p = v;
 }
 
 // Epilogues derive from this.  An epilogue that reads an input per element
@@ -55,32 +54,26 @@ struct is_tiled<E, std::void_t<decltype(E::TILED)>> : std::bool_constant<E::TILE
 
 constexpr int BN = 128;   // work-group tile width
 constexpr int NTH = 256;  // 4 waves, each a (BM/2) x 64 quarter of the BM x 128 tile
-// contraction slice per LDS stage
-template <typename T>
-constexpr int bk() {
-  static_assert(sizeof(T) == 4, "FP32 products");
-  return 32;
-}
+constexpr int BK = 32;    // contraction slice per LDS stage
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // A lane's 16 values of one 32x32 block in the tile-native layout (see
-// EpBase): 16 * sizeof(T) contiguous bytes at base + blk * 1024 + lane * 16.
-template <typename T>
+// EpBase): 64 contiguous bytes at base + blk * 1024 + lane * 16.
 struct Native16 {
-  static constexpr int W = (int)sizeof(T);  // 16-byte words per lane and block
+  static constexpr int W = 4;  // 16-byte words per lane and block
   u32x4 v[W];
-  __device__ __forceinline__ static T* at(T* base, int64_t blk) {
+  __device__ __forceinline__ static float* at(float* base, int64_t blk) {
     return base + blk * 1024 + (threadIdx.x & 63) * 16;
   }
-  __device__ __forceinline__ static Native16 load(const T* base, int64_t blk) {
+  __device__ __forceinline__ static Native16 load(const float* base, int64_t blk) {
     Native16 r;
-    const u32x4* src = reinterpret_cast<const u32x4*>(at(const_cast<T*>(base), blk));
+    const u32x4* src = reinterpret_cast<const u32x4*>(at(const_cast<float*>(base), blk));
 #pragma unroll
     for (int i = 0; i < W; ++i) r.v[i] = src[i];
     return r;
   }
-  __device__ __forceinline__ static void store(T* base, int64_t blk, const Native16& n) {
+  __device__ __forceinline__ static void store(float* base, int64_t blk, const Native16& n) {
     u32x4* dst = reinterpret_cast<u32x4*>(at(base, blk));
 #pragma unroll
     for (int i = 0; i < W; ++i) dst[i] = n.v[i];
@@ -95,9 +88,8 @@ enum { KMAJ = 0, MNMAJ = 1 };
 // with lane (l32, hf) holding k = 2j + hf.  Pitches (in 4-byte LDS banks): 33
 // (k-major, 4-byte reads down a column), 132 (mn-major, consecutive lanes on
 // consecutive banks).
-template <typename T, int ROWS>
+template <int ROWS>
 struct Tile {
-  static constexpr int BK = bk<T>();
   static constexpr int KLD = BK + 1;    // pitch of a k-major tile [ROWS][BK]
   static constexpr int MLD = ROWS + 4;  // pitch of an mn-major tile [BK][ROWS]
   static constexpr int ELEMS = ROWS * KLD > BK * MLD ? ROWS * KLD : BK * MLD;
@@ -108,12 +100,11 @@ struct Tile {
 // of the m/n axis, k0 .. k0+BK of the contraction).  Loads go through a
 // buffer resource that covers exactly the valid part of the operand, so rows
 // past its end (ragged token counts) read as zero.
-template <typename T, int LAYOUT, int ROWS>
+template <int LAYOUT, int ROWS>
 struct Stage {
-  static constexpr int BK = bk<T>();
-  static constexpr int BYTES = ROWS * BK * (int)sizeof(T);
+  static constexpr int BYTES = ROWS * BK * 4;
   static constexpr int PER = BYTES / NTH / 16;  // 16-byte loads per thread
-  static constexpr int EPC = 16 / (int)sizeof(T);  // elements per 16-byte chunk
+  static constexpr int EPC = 4;  // elements per 16-byte chunk
   u32x4 r[PER];
   // This thread's byte offsets of its chunks for the slice at k0 = 0; a
   // slice at k0 adds the uniform kbytes(ld) * k0.
@@ -132,17 +123,17 @@ struct Stage {
         row = c / CPR;
         col = mn0 + (c % CPR) * EPC;
       }
-      vo[i] = (row * ld + col) * (int)sizeof(T);
+      vo[i] = (row * ld + col) * 4;
     }
   }
   __device__ __forceinline__ static int kbytes(int ld) {
-    return LAYOUT == KMAJ ? (int)sizeof(T) : ld * (int)sizeof(T);
+    return LAYOUT == KMAJ ? 4 : ld * 4;
   }
   __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, const int (&vo)[PER], int kofs) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) r[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo[i] + kofs, 0, 0);
   }
-  __device__ __forceinline__ void store(T* lds) const {
+  __device__ __forceinline__ void store(float* lds) const {
     const int tid = threadIdx.x;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -150,10 +141,10 @@ struct Stage {
       int off;
       if constexpr (LAYOUT == KMAJ) {
         constexpr int CPR = BK / EPC;
-        off = (c / CPR) * Tile<T, ROWS>::KLD + (c % CPR) * EPC;
+        off = (c / CPR) * Tile<ROWS>::KLD + (c % CPR) * EPC;
       } else {
         constexpr int CPR = ROWS / EPC;
-        off = (c / CPR) * Tile<T, ROWS>::MLD + (c % CPR) * EPC;
+        off = (c / CPR) * Tile<ROWS>::MLD + (c % CPR) * EPC;
       }
       if constexpr (LAYOUT == MNMAJ) {
         *reinterpret_cast<u32x4*>(lds + off) = r[i];
@@ -168,51 +159,46 @@ struct Stage {
 
 // Operand fragment of product step j for the 32-wide block starting at mn
 // (tile-local) of a staged tile.
-template <typename T, int LAYOUT, int ROWS>
-__device__ __forceinline__ auto frag(const T* t, int mn, int j) {
+template <int LAYOUT, int ROWS>
+__device__ __forceinline__ auto frag(const float* t, int mn, int j) {
   const int l = threadIdx.x & 63, l32 = l & 31, hf = l >> 5;
-  using TL = Tile<T, ROWS>;
+  using TL = Tile<ROWS>;
   if constexpr (LAYOUT == KMAJ)
     return t[(mn + l32) * TL::KLD + 2 * j + hf];
   else
     return t[(2 * j + hf) * TL::MLD + mn + l32];
 }
 
-// Product steps per contraction slice.
-template <typename T>
-constexpr int ksteps() {
-  return bk<T>() / 2;
-}
+constexpr int KSTEPS = BK / 2;  // products per contraction slice
 
 // C tile (this work-group's BM x 128) accumulated over the whole
 // contraction, then handed to the epilogue element by element:
 // ep(row, col, value, ep.load(row, col)); rows past the operand's end are the
 // epilogue's to skip (in load as well).
-template <typename T, int LA, int LB, int BM, typename EP>
-__device__ __forceinline__ void gemm_tile(const T* A, int lda, int a_rows, const T* B, int ldb, int b_rows, int K,
-                                          int m0, int n0, EP& ep) {
+template <int LA, int LB, int BM, typename EP>
+__device__ __forceinline__ void gemm_tile(const float* A, int lda, int a_rows, const float* B, int ldb, int b_rows,
+                                          int K, int m0, int n0, EP& ep) {
   constexpr int MB = BM / 64;  // 32-row blocks per wave (each wave: BM/2 rows x 64 columns)
-  __shared__ __attribute__((aligned(16))) T sa[2][Tile<T, BM>::ELEMS];
-  __shared__ __attribute__((aligned(16))) T sb[2][Tile<T, BN>::ELEMS];
+  __shared__ __attribute__((aligned(16))) float sa[2][Tile<BM>::ELEMS];
+  __shared__ __attribute__((aligned(16))) float sb[2][Tile<BN>::ELEMS];
   const int w = threadIdx.x >> 6, wm = (w >> 1) * (BM / 2), wn = (w & 1) * 64;
   // buffer resources over the valid rows of each operand
-  auto rsrc = [](const T* p, int rows, int ld) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), (short)0, rows * ld * (int)sizeof(T), 0x00020000);
+  auto rsrc = [](const float* p, int rows, int ld) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, rows * ld * 4, 0x00020000);
   };
   const auto ra = rsrc(A, a_rows, lda), rb = rsrc(B, b_rows, ldb);
   // Three-stage pipeline: while slice kt is multiplied out of one LDS
   // buffer, slice kt+1 waits in the other and slice kt+2 is in flight from
   // HBM into registers (two register stages, alternating), so a global load
   // has two slices of products to arrive before it is needed.
-  using SA = Stage<T, LA, BM>;
-  using SB = Stage<T, LB, BN>;
+  using SA = Stage<LA, BM>;
+  using SB = Stage<LB, BN>;
   SA ga[2];
   SB gb[2];
   int voa[SA::PER], vob[SB::PER];
   SA::offsets(lda, m0, voa);
   SB::offsets(ldb, n0, vob);
-  const int ka = SA::kbytes(lda) * bk<T>(), kb = SB::kbytes(ldb) * bk<T>();  // bytes per slice
-  constexpr int BK = bk<T>();
+  const int ka = SA::kbytes(lda) * BK, kb = SB::kbytes(ldb) * BK;  // bytes per slice
   const int nk = (K + BK - 1) / BK;
   f32x16 acc[MB][2] = {};
   // Every load and LDS store below is unconditional (a slice past the end
@@ -236,17 +222,17 @@ __device__ __forceinline__ void gemm_tile(const T* A, int lda, int a_rows, const
     }
     // every operand fragment of the slice is read before the products, so
     // the LDS latency is paid once per slice, not once per product step
-    using FT = decltype(frag<T, LB, BN>(sb[P], wn, 0));
-    FT fb[ksteps<T>()][2], fa[ksteps<T>()][MB];
+    using FT = decltype(frag<LB, BN>(sb[P], wn, 0));
+    FT fb[KSTEPS][2], fa[KSTEPS][MB];
 #pragma unroll
-    for (int j = 0; j < ksteps<T>(); ++j) {
-      fb[j][0] = frag<T, LB, BN>(sb[P], wn, j);
-      fb[j][1] = frag<T, LB, BN>(sb[P], wn + 32, j);
+    for (int j = 0; j < KSTEPS; ++j) {
+      fb[j][0] = frag<LB, BN>(sb[P], wn, j);
+      fb[j][1] = frag<LB, BN>(sb[P], wn + 32, j);
 #pragma unroll
-      for (int bm = 0; bm < MB; ++bm) fa[j][bm] = frag<T, LA, BM>(sa[P], wm + 32 * bm, j);
+      for (int bm = 0; bm < MB; ++bm) fa[j][bm] = frag<LA, BM>(sa[P], wm + 32 * bm, j);
     }
 #pragma unroll
-    for (int j = 0; j < ksteps<T>(); ++j) {
+    for (int j = 0; j < KSTEPS; ++j) {
 #pragma unroll
       for (int bm = 0; bm < MB; ++bm) {
         acc[bm][0] = mma32(fa[j][bm], fb[j][0], acc[bm][0]);
@@ -312,10 +298,10 @@ __device__ __forceinline__ float fixed_order_sum(const float* part, int n) {
 }
 
 // One launch of one product; grid (N / 128, ceil(M / 128)).
-template <typename T, int LA, int LB, int BM, typename EP>
-__global__ __launch_bounds__(NTH) void k_gemm(const T* A, int lda, int a_rows, const T* B, int ldb, int b_rows,
+template <int LA, int LB, int BM, typename EP>
+__global__ __launch_bounds__(NTH) void k_gemm(const float* A, int lda, int a_rows, const float* B, int ldb, int b_rows,
                                                 int K, EP ep) {
-  gemm_tile<T, LA, LB, BM>(A, lda, a_rows, B, ldb, b_rows, K, blockIdx.y * BM, blockIdx.x * BN, ep);
+  gemm_tile<LA, LB, BM>(A, lda, a_rows, B, ldb, b_rows, K, blockIdx.y * BM, blockIdx.x * BN, ep);
 }
 
 }  // namespace large

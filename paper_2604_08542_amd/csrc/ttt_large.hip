@@ -39,10 +39,10 @@ namespace large {
 // ------------------------------------------------------------- epilogues
 // A = SiLU(Z), S1 = SiLU'(Z) (for the gradient; S1 in the tile-native
 // layout, read back by EpD in the same grid) or only A (for the apply).
-template <typename T, bool GRAD>
+template <bool GRAD>
 struct EpAct : EpBase {
-  T* a;
-  T* s1;
+  float* a;
+  float* s1;
   int ld, rows;
   static constexpr bool TILED = GRAD;
   __device__ __forceinline__ void operator()(int r, int c, float z, In) {
@@ -54,8 +54,8 @@ struct EpAct : EpBase {
   __device__ __forceinline__ void block(int64_t blk, int row0, int col, const f32x16& z, TIn) {
     const int hf = (threadIdx.x >> 5) & 1;
     union {
-      T t[16];
-      Native16<T> n;
+      float t[16];
+      Native16 n;
     } sv;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -63,17 +63,16 @@ struct EpAct : EpBase {
       float sg;
       const float av = silu_sig(z[r], sg);
       if (row < rows) put(a + (int64_t)row * ld + col, av);
-      sv.t[r] = (T)fmaf(av, 1.0f - sg, sg);
+      sv.t[r] = fmaf(av, 1.0f - sg, sg);
     }
-    u32x4* dst = reinterpret_cast<u32x4*>(Native16<T>::at(s1, blk));
+    u32x4* dst = reinterpret_cast<u32x4*>(Native16::at(s1, blk));
 #pragma unroll
-    for (int i = 0; i < Native16<T>::W; ++i) dst[i] = sv.n.v[i];
+    for (int i = 0; i < Native16::W; ++i) dst[i] = sv.n.v[i];
   }
 };
 // R = Y - V, E = scale * R; sum of R^2 of this tile into loss_part[tile].
-template <typename T>
 struct EpRes {
-  T* e;
+  float* e;
   const float* v;
   float* loss_part;
   int ld, rows;
@@ -98,40 +97,38 @@ struct EpRes {
   }
 };
 // D = P * S1.
-template <typename T>
 struct EpD : EpBase {
-  T* d;
-  const T* s1;  // tile-native layout, written by EpAct<T, true> over the same grid
+  float* d;
+  const float* s1;  // tile-native layout, written by EpAct<T, true> over the same grid
   int ld, rows;
   static constexpr bool TILED = true;
-  typedef Native16<T> TIn;
+  typedef Native16 TIn;
   __device__ __forceinline__ TIn tload(int64_t blk) const {
     TIn r;
-    const u32x4* src = reinterpret_cast<const u32x4*>(Native16<T>::at(const_cast<T*>(s1), blk));
+    const u32x4* src = reinterpret_cast<const u32x4*>(Native16::at(const_cast<float*>(s1), blk));
 #pragma unroll
-    for (int i = 0; i < Native16<T>::W; ++i) r.v[i] = src[i];
+    for (int i = 0; i < Native16::W; ++i) r.v[i] = src[i];
     return r;
   }
   __device__ __forceinline__ void block(int64_t, int row0, int col, const f32x16& p, const TIn& n) {
     const int hf = (threadIdx.x >> 5) & 1;
     union {
-      T t[16];
-      Native16<T> n;
+      float t[16];
+      Native16 n;
     } sv;
     sv.n = n;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = row0 + c32_row(r, hf);
-      if (row < rows) put(d + (int64_t)row * ld + col, p[r] * (float)sv.t[r]);
+      if (row < rows) put(d + (int64_t)row * ld + col, p[r] * sv.t[r]);
     }
   }
 };
 // W -= eta * G (FP32 master), then the operand copy of the new W (nullable:
 // masters only, while a sum of several gradients is being taken).
-template <typename T>
 struct EpUpd : EpBase {
   float* w;
-  T* wop;
+  float* wop;
   int ld;
   float eta;
   const float* from;  // the W stepped from (w itself, or the masters of the step before)
@@ -145,32 +142,30 @@ struct EpUpd : EpBase {
   }
 };
 // O rows of the chunk into the strided token tensor.
-template <typename IOT>
 struct EpOut : EpBase {
-  IOT* o;  // first token of the chunk, head offset applied
+  float* o;  // first token of the chunk, head offset applied
   int64_t stride_tok;
   int rows;
   __device__ __forceinline__ void operator()(int r, int c, float y, In) {
     if (r >= rows) return;
-    o[(int64_t)r * stride_tok + c] = (IOT)y;
+    o[(int64_t)r * stride_tok + c] = (float)y;
   }
 };
 
-// A product stored as it is ([rows][ld], operand type).
-template <typename T>
+// A product stored as it is ([rows][ld]).
 struct EpStoreTiled : EpBase {  // the product in the tile-native layout (read by EpSwi over the same grid)
-  T* z;
+  float* z;
   static constexpr bool TILED = true;
   __device__ __forceinline__ void block(int64_t blk, int, int, const f32x16& v, TIn) {
     union {
-      T t[16];
-      Native16<T> n;
+      float t[16];
+      Native16 n;
     } sv;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sv.t[r] = (T)v[r];
-    u32x4* dst = reinterpret_cast<u32x4*>(Native16<T>::at(z, blk));
+    for (int r = 0; r < 16; ++r) sv.t[r] = v[r];
+    u32x4* dst = reinterpret_cast<u32x4*>(Native16::at(z, blk));
 #pragma unroll
-    for (int i = 0; i < Native16<T>::W; ++i) dst[i] = sv.n.v[i];
+    for (int i = 0; i < Native16::W; ++i) dst[i] = sv.n.v[i];
   }
 };
 // Z1 = x W1 of the memory unit with Z3 = x W3 stored: Hd = SiLU(Z1) Z3; for
@@ -178,21 +173,21 @@ struct EpStoreTiled : EpBase {  // the product in the tile-native layout (read b
 // (towards W1) and G3 = SiLU(Z1) (towards W3).
 // Z3, G1 and G3 are in the tile-native layout (written and read by products
 // of one chunk step over the same grid); Hd is an operand, row-major.
-template <typename T, bool GRAD>
+template <bool GRAD>
 struct EpSwi : EpBase {
-  const T* z3;
-  T* hd;
-  T* g1;
-  T* g3;
+  const float* z3;
+  float* hd;
+  float* g1;
+  float* g3;
   int ld, rows;
   static constexpr bool TILED = true;
-  typedef Native16<T> TIn;
-  __device__ __forceinline__ TIn tload(int64_t blk) const { return Native16<T>::load(z3, blk); }
+  typedef Native16 TIn;
+  __device__ __forceinline__ TIn tload(int64_t blk) const { return Native16::load(z3, blk); }
   __device__ __forceinline__ void block(int64_t blk, int row0, int col, const f32x16& z1, const TIn& z3n) {
     const int hf = (threadIdx.x >> 5) & 1;
     union U {
-      T t[16];
-      Native16<T> n;
+      float t[16];
+      Native16 n;
     } z3v, gv1, gv3;
     z3v.n = z3n;
 #pragma unroll
@@ -200,39 +195,38 @@ struct EpSwi : EpBase {
       const int row = row0 + c32_row(r, hf);
       float sg;
       const float sv = silu_sig(z1[r], sg);
-      const float zz = (float)z3v.t[r];
+      const float zz = z3v.t[r];
       if (row < rows) put(hd + (int64_t)row * ld + col, sv * zz);
       if constexpr (GRAD) {
-        gv1.t[r] = (T)(zz * fmaf(sv, 1.0f - sg, sg));
-        gv3.t[r] = (T)sv;
+        gv1.t[r] = (zz * fmaf(sv, 1.0f - sg, sg));
+        gv3.t[r] = sv;
       }
     }
     if constexpr (GRAD) {
-      Native16<T>::store(g1, blk, gv1.n);
-      Native16<T>::store(g3, blk, gv3.n);
+      Native16::store(g1, blk, gv1.n);
+      Native16::store(g3, blk, gv3.n);
     }
   }
 };
 // dH = E W2^T: D1 = dH G1, D3 = dH G3.
-template <typename T>
 struct EpD2 : EpBase {
-  const T* g1;  // tile-native, from EpSwi<T, true> over the same grid
-  const T* g3;
-  T* d1;
-  T* d3;
+  const float* g1;  // tile-native, from EpSwi<T, true> over the same grid
+  const float* g3;
+  float* d1;
+  float* d3;
   int ld, rows;
   static constexpr bool TILED = true;
   struct TIn {
-    Native16<T> a, b;
+    Native16 a, b;
   };
   __device__ __forceinline__ TIn tload(int64_t blk) const {
-    return {Native16<T>::load(g1, blk), Native16<T>::load(g3, blk)};
+    return {Native16::load(g1, blk), Native16::load(g3, blk)};
   }
   __device__ __forceinline__ void block(int64_t, int row0, int col, const f32x16& dh, const TIn& g) {
     const int hf = (threadIdx.x >> 5) & 1;
     union U {
-      T t[16];
-      Native16<T> n;
+      float t[16];
+      Native16 n;
     } a, b;
     a.n = g.a;
     b.n = g.b;
@@ -241,8 +235,8 @@ struct EpD2 : EpBase {
       const int row = row0 + c32_row(r, hf);
       if (row >= rows) continue;
       const int64_t i = (int64_t)row * ld + col;
-      put(d1 + i, dh[r] * (float)a.t[r]);
-      put(d3 + i, dh[r] * (float)b.t[r]);
+      put(d1 + i, dh[r] * a.t[r]);
+      put(d3 + i, dh[r] * b.t[r]);
     }
   }
 };
@@ -250,26 +244,21 @@ struct EpD2 : EpBase {
 // ------------------------------------------------------------- kernels
 // Row normalisation of the chunk's K, V, Q rows (one wave per token; each
 // lane holds runs of 4 consecutive elements, 256 elements per wave pass, at
-// most 16 passes): Kn, Qn in the operand type, Vn in FP32 (the residual is
-// formed in FP32).
-template <typename IOT, typename T>
+// most 16 passes): Kn, Qn, Vn.
 __global__ __launch_bounds__(256) void k_norm(LargeNormArgs p) {
-  typedef IOT iov4 __attribute__((ext_vector_type(4)));
-  typedef T opv4 __attribute__((ext_vector_type(4)));
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), l = threadIdx.x & 63;
   if (row >= p.rows) return;
   const int passes = p.d / 256;
   for (int which = 0; which < 3; ++which) {
-    const IOT* src = static_cast<const IOT*>(which == 0 ? p.K : which == 1 ? p.V : p.Q) +
-                     (int64_t)row * p.stride_tok;
+    const float* src = static_cast<const float*>(which == 0 ? p.K : which == 1 ? p.V : p.Q) +
+                       (int64_t)row * p.stride_tok;
     const bool nrm = (p.flags >> (which == 0 ? 1 : which == 1 ? 2 : 0)) & 1u;
     f32x4 x[16];
     float ss = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       if (i < passes) {
-        const iov4 v = *reinterpret_cast<const iov4*>(src + 256 * i + 4 * l);
-        x[i] = (f32x4){(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+        x[i] = *reinterpret_cast<const f32x4*>(src + 256 * i + 4 * l);
 #pragma unroll
         for (int e = 0; e < 4; ++e) ss = fmaf(x[i][e], x[i][e], ss);
       }
@@ -282,10 +271,7 @@ __global__ __launch_bounds__(256) void k_norm(LargeNormArgs p) {
       if (i < passes) {
         const f32x4 y = x[i] * inv;
         const int64_t o = (int64_t)row * p.d + 256 * i + 4 * l;
-        if (which == 1)
-          *reinterpret_cast<f32x4*>(p.Vn + o) = y;
-        else
-          *reinterpret_cast<opv4*>(static_cast<T*>(which == 0 ? p.Kn : p.Qn) + o) = (opv4){(T)y[0], (T)y[1], (T)y[2], (T)y[3]};
+        *reinterpret_cast<f32x4*>((which == 1 ? p.Vn : static_cast<float*>(which == 0 ? p.Kn : p.Qn)) + o) = y;
       }
     }
   }
@@ -303,13 +289,12 @@ __global__ void k_init_w(const float* w1, const float* w2, float* m1, float* m2,
   }
 }
 
-// E = -eta_i Vn_i of the memory unit's chunk, in the operand type.
-template <typename T>
-__global__ __launch_bounds__(256) void k_amu_e(T* e, const float* vn, const float* eta, int64_t eta_stride, int rows,
-                                               int d) {
+// E = -eta_i Vn_i of the memory unit's chunk.
+__global__ __launch_bounds__(256) void k_amu_e(float* e, const float* vn, const float* eta, int64_t eta_stride,
+                                               int rows, int d) {
   const int64_t n = (int64_t)rows * d;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    e[i] = (T)(-eta[(i / d) * eta_stride] * vn[i]);
+    e[i] = (-eta[(i / d) * eta_stride] * vn[i]);
 }
 
 template <typename T>
@@ -324,7 +309,6 @@ __global__ __launch_bounds__(NTH) void k_loss(const float* part, int n, float in
   if (threadIdx.x == 0) *out = s * inv_m;
 }
 
-template <typename T, typename IOT>
 hipError_t step_t(const LargeStepArgs& a, hipStream_t st) {
   const int M = a.rows, d = a.d, h = a.h;
   // tile rows: 128 for the products over the chunk's tokens (two waves per
@@ -335,102 +319,101 @@ hipError_t step_t(const LargeStepArgs& a, hipStream_t st) {
   // work-groups) are slower for these 10,992-token contractions
   constexpr int BMT = 128, BMW = 128;
   const int mt = (M + BMT - 1) / BMT;
-  T* Kn = static_cast<T*>(a.Kn);
-  T* Qn = static_cast<T*>(a.Qn);
-  T* E = static_cast<T*>(a.E);
-  T* Aa = static_cast<T*>(a.A);
-  T* Dd = static_cast<T*>(a.D);
-  T* Aq = static_cast<T*>(a.Aq);
-  T* W1o = static_cast<T*>(a.W1op);
-  T* W2o = static_cast<T*>(a.W2op);
+  float* Kn = static_cast<float*>(a.Kn);
+  float* Qn = static_cast<float*>(a.Qn);
+  float* E = static_cast<float*>(a.E);
+  float* Aa = static_cast<float*>(a.A);
+  float* Dd = static_cast<float*>(a.D);
+  float* Aq = static_cast<float*>(a.Aq);
+  float* W1o = static_cast<float*>(a.W1op);
+  float* W2o = static_cast<float*>(a.W2op);
   LargeNormArgs na{a.K, a.V, a.Q, a.stride_tok, a.flags, M, d, a.Kn, a.Vn, a.Qn};
-  hipLaunchKernelGGL((k_norm<IOT, T>), dim3((M + 3) / 4), dim3(256), 0, st, na);
+  hipLaunchKernelGGL(k_norm, dim3((M + 3) / 4), dim3(256), 0, st, na);
   if (a.grad) {
     // Z = Kn W1 -> A, S1
-    EpAct<T, true> e1{{}, Aa, static_cast<T*>(a.S1), h, M};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, MNMAJ, BMT, EpAct<T, true>>), dim3(h / BN, mt), dim3(NTH), 0, st, Kn, d, M,
+    EpAct<true> e1{{}, Aa, static_cast<float*>(a.S1), h, M};
+    hipLaunchKernelGGL((k_gemm<KMAJ, MNMAJ, BMT, EpAct<true>>), dim3(h / BN, mt), dim3(NTH), 0, st, Kn, d, M,
                        W1o, h, d, d, e1);
     // Y = A W2 -> E, loss partials
-    EpRes<T> e2{E, a.Vn, a.loss_part, d, M, 2.0f / (float)M};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, MNMAJ, BMT, EpRes<T>>), dim3(d / BN, mt), dim3(NTH), 0, st, Aa, h, M, W2o, d,
+    EpRes e2{E, a.Vn, a.loss_part, d, M, 2.0f / (float)M};
+    hipLaunchKernelGGL((k_gemm<KMAJ, MNMAJ, BMT, EpRes>), dim3(d / BN, mt), dim3(NTH), 0, st, Aa, h, M, W2o, d,
                        h, h, e2);
     if (a.loss) hipLaunchKernelGGL(k_loss, dim3(1), dim3(NTH), 0, st, a.loss_part, (d / BN) * mt, 1.0f / (float)M,
                                    a.loss);
     // P = E W2^T -> D
-    EpD<T> e3{{}, Dd, static_cast<const T*>(a.S1), h, M};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, KMAJ, BMT, EpD<T>>), dim3(h / BN, mt), dim3(NTH), 0, st, E, d, M, W2o, d, h, d,
+    EpD e3{{}, Dd, static_cast<const float*>(a.S1), h, M};
+    hipLaunchKernelGGL((k_gemm<KMAJ, KMAJ, BMT, EpD>), dim3(h / BN, mt), dim3(NTH), 0, st, E, d, M, W2o, d, h, d,
                        e3);
     // W1 -= eta Kn^T D ; W2 -= eta A^T E (contractions over the chunk's tokens)
-    EpUpd<T> e4{{}, a.W1, a.masters_only ? nullptr : W1o, h, a.eta, a.W1};
-    hipLaunchKernelGGL((k_gemm<T, MNMAJ, MNMAJ, BMW, EpUpd<T>>), dim3(h / BN, d / BMW), dim3(NTH), 0, st, Kn, d, M, Dd,
+    EpUpd e4{{}, a.W1, a.masters_only ? nullptr : W1o, h, a.eta, a.W1};
+    hipLaunchKernelGGL((k_gemm<MNMAJ, MNMAJ, BMW, EpUpd>), dim3(h / BN, d / BMW), dim3(NTH), 0, st, Kn, d, M, Dd,
                        h, M, M, e4);
-    EpUpd<T> e5{{}, a.W2, a.masters_only ? nullptr : W2o, d, a.eta, a.W2};
-    hipLaunchKernelGGL((k_gemm<T, MNMAJ, MNMAJ, BMW, EpUpd<T>>), dim3(d / BN, h / BMW), dim3(NTH), 0, st, Aa, h, M, E, d,
+    EpUpd e5{{}, a.W2, a.masters_only ? nullptr : W2o, d, a.eta, a.W2};
+    hipLaunchKernelGGL((k_gemm<MNMAJ, MNMAJ, BMW, EpUpd>), dim3(d / BN, h / BMW), dim3(NTH), 0, st, Aa, h, M, E, d,
                        M, M, e5);
   }
   if (a.O) {
-    EpAct<T, false> e6{{}, Aq, nullptr, h, M};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, MNMAJ, BMT, EpAct<T, false>>), dim3(h / BN, mt), dim3(NTH), 0, st, Qn, d, M, W1o,
+    EpAct<false> e6{{}, Aq, nullptr, h, M};
+    hipLaunchKernelGGL((k_gemm<KMAJ, MNMAJ, BMT, EpAct<false>>), dim3(h / BN, mt), dim3(NTH), 0, st, Qn, d, M, W1o,
                        h, d, d, e6);
-    EpOut<IOT> e7{{}, static_cast<IOT*>(a.O), a.stride_tok, M};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, MNMAJ, BMT, EpOut<IOT>>), dim3(d / BN, mt), dim3(NTH), 0, st, Aq, h, M, W2o, d,
+    EpOut e7{{}, static_cast<float*>(a.O), a.stride_tok, M};
+    hipLaunchKernelGGL((k_gemm<KMAJ, MNMAJ, BMT, EpOut>), dim3(d / BN, mt), dim3(NTH), 0, st, Aq, h, M, W2o, d,
                        h, h, e7);
   }
   return hipGetLastError();
 }
 
-template <typename T, typename IOT>
 hipError_t amu_step_t(const LargeAmuArgs& a, hipStream_t st) {
   const int M = a.rows, d = a.d, h = a.h;
   constexpr int BMT = 128, BMW = 128;  // as in step_t
   const int mt = (M + BMT - 1) / BMT;
-  T* Kn = static_cast<T*>(a.Kn);
-  T* Qn = static_cast<T*>(a.Qn);
-  T* E = static_cast<T*>(a.E);
-  T* Z3 = static_cast<T*>(a.Z3);
-  T* Hd = static_cast<T*>(a.Hd);
-  T* G1 = static_cast<T*>(a.G1);
-  T* G3 = static_cast<T*>(a.G3);
-  T* D1 = static_cast<T*>(a.D1);
-  T* D3 = static_cast<T*>(a.D3);
-  T* W1o = static_cast<T*>(a.W1op);
-  T* W2o = static_cast<T*>(a.W2op);
-  T* W3o = static_cast<T*>(a.W3op);
+  float* Kn = static_cast<float*>(a.Kn);
+  float* Qn = static_cast<float*>(a.Qn);
+  float* E = static_cast<float*>(a.E);
+  float* Z3 = static_cast<float*>(a.Z3);
+  float* Hd = static_cast<float*>(a.Hd);
+  float* G1 = static_cast<float*>(a.G1);
+  float* G3 = static_cast<float*>(a.G3);
+  float* D1 = static_cast<float*>(a.D1);
+  float* D3 = static_cast<float*>(a.D3);
+  float* W1o = static_cast<float*>(a.W1op);
+  float* W2o = static_cast<float*>(a.W2op);
+  float* W3o = static_cast<float*>(a.W3op);
   LargeNormArgs na{a.K, a.V, a.Q, a.stride_tok, a.flags, M, d, a.Kn, a.Vn, a.Qn};
-  hipLaunchKernelGGL((k_norm<IOT, T>), dim3((M + 3) / 4), dim3(256), 0, st, na);
+  hipLaunchKernelGGL(k_norm, dim3((M + 3) / 4), dim3(256), 0, st, na);
   if (a.grad) {
-    EpStoreTiled<T> e1{{}, Z3};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, MNMAJ, BMT, EpStoreTiled<T>>), dim3(h / BN, mt), dim3(NTH), 0, st, Kn, d, M, W3o,
+    EpStoreTiled e1{{}, Z3};
+    hipLaunchKernelGGL((k_gemm<KMAJ, MNMAJ, BMT, EpStoreTiled>), dim3(h / BN, mt), dim3(NTH), 0, st, Kn, d, M, W3o,
                        h, d, d, e1);
-    EpSwi<T, true> e2{{}, Z3, Hd, G1, G3, h, M};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, MNMAJ, BMT, EpSwi<T, true>>), dim3(h / BN, mt), dim3(NTH), 0, st, Kn, d, M,
+    EpSwi<true> e2{{}, Z3, Hd, G1, G3, h, M};
+    hipLaunchKernelGGL((k_gemm<KMAJ, MNMAJ, BMT, EpSwi<true>>), dim3(h / BN, mt), dim3(NTH), 0, st, Kn, d, M,
                        W1o, h, d, d, e2);
     const int64_t ne = (int64_t)M * d;
-    hipLaunchKernelGGL(k_amu_e<T>, dim3((unsigned)std::min<int64_t>((ne + 255) / 256, 4096)), dim3(256), 0, st, E,
+    hipLaunchKernelGGL(k_amu_e, dim3((unsigned)std::min<int64_t>((ne + 255) / 256, 4096)), dim3(256), 0, st, E,
                        a.Vn, a.eta, a.eta_stride, M, d);
-    EpD2<T> e3{{}, G1, G3, D1, D3, h, M};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, KMAJ, BMT, EpD2<T>>), dim3(h / BN, mt), dim3(NTH), 0, st, E, d, M, W2o, d, h,
+    EpD2 e3{{}, G1, G3, D1, D3, h, M};
+    hipLaunchKernelGGL((k_gemm<KMAJ, KMAJ, BMT, EpD2>), dim3(h / BN, mt), dim3(NTH), 0, st, E, d, M, W2o, d, h,
                        d, e3);
     // the step sizes are inside the loss: W <- W - grad
-    EpUpd<T> u1{{}, a.W1, a.write_op ? W1o : nullptr, h, 1.0f, a.from1 ? a.from1 : a.W1};
-    hipLaunchKernelGGL((k_gemm<T, MNMAJ, MNMAJ, BMW, EpUpd<T>>), dim3(h / BN, d / BMW), dim3(NTH), 0, st, Kn, d, M, D1,
+    EpUpd u1{{}, a.W1, a.write_op ? W1o : nullptr, h, 1.0f, a.from1 ? a.from1 : a.W1};
+    hipLaunchKernelGGL((k_gemm<MNMAJ, MNMAJ, BMW, EpUpd>), dim3(h / BN, d / BMW), dim3(NTH), 0, st, Kn, d, M, D1,
                        h, M, M, u1);
-    EpUpd<T> u3{{}, a.W3, a.write_op ? W3o : nullptr, h, 1.0f, a.from3 ? a.from3 : a.W3};
-    hipLaunchKernelGGL((k_gemm<T, MNMAJ, MNMAJ, BMW, EpUpd<T>>), dim3(h / BN, d / BMW), dim3(NTH), 0, st, Kn, d, M, D3,
+    EpUpd u3{{}, a.W3, a.write_op ? W3o : nullptr, h, 1.0f, a.from3 ? a.from3 : a.W3};
+    hipLaunchKernelGGL((k_gemm<MNMAJ, MNMAJ, BMW, EpUpd>), dim3(h / BN, d / BMW), dim3(NTH), 0, st, Kn, d, M, D3,
                        h, M, M, u3);
-    EpUpd<T> u2{{}, a.W2, a.write_op ? W2o : nullptr, d, 1.0f, a.from2 ? a.from2 : a.W2};
-    hipLaunchKernelGGL((k_gemm<T, MNMAJ, MNMAJ, BMW, EpUpd<T>>), dim3(d / BN, h / BMW), dim3(NTH), 0, st, Hd, h, M, E,
+    EpUpd u2{{}, a.W2, a.write_op ? W2o : nullptr, d, 1.0f, a.from2 ? a.from2 : a.W2};
+    hipLaunchKernelGGL((k_gemm<MNMAJ, MNMAJ, BMW, EpUpd>), dim3(d / BN, h / BMW), dim3(NTH), 0, st, Hd, h, M, E,
                        d, M, M, u2);
   }
   if (a.O) {
-    EpStoreTiled<T> e6{{}, Z3};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, MNMAJ, BMT, EpStoreTiled<T>>), dim3(h / BN, mt), dim3(NTH), 0, st, Qn, d, M, W3o,
+    EpStoreTiled e6{{}, Z3};
+    hipLaunchKernelGGL((k_gemm<KMAJ, MNMAJ, BMT, EpStoreTiled>), dim3(h / BN, mt), dim3(NTH), 0, st, Qn, d, M, W3o,
                        h, d, d, e6);
-    EpSwi<T, false> e7{{}, Z3, Hd, nullptr, nullptr, h, M};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, MNMAJ, BMT, EpSwi<T, false>>), dim3(h / BN, mt), dim3(NTH), 0, st, Qn, d, M,
+    EpSwi<false> e7{{}, Z3, Hd, nullptr, nullptr, h, M};
+    hipLaunchKernelGGL((k_gemm<KMAJ, MNMAJ, BMT, EpSwi<false>>), dim3(h / BN, mt), dim3(NTH), 0, st, Qn, d, M,
                        W1o, h, d, d, e7);
-    EpOut<IOT> e8{{}, static_cast<IOT*>(a.O), a.stride_tok, M};
-    hipLaunchKernelGGL((k_gemm<T, KMAJ, MNMAJ, BMT, EpOut<IOT>>), dim3(d / BN, mt), dim3(NTH), 0, st, Hd, h, M, W2o, d,
+    EpOut e8{{}, static_cast<float*>(a.O), a.stride_tok, M};
+    hipLaunchKernelGGL((k_gemm<KMAJ, MNMAJ, BMT, EpOut>), dim3(d / BN, mt), dim3(NTH), 0, st, Hd, h, M, W2o, d,
                        h, h, e8);
   }
   return hipGetLastError();
@@ -449,18 +432,18 @@ hipError_t init_t(const float* w1, const float* w2, float* m1, float* m2, void* 
 hipError_t launch_large_step(const LargeStepArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st) {
   using namespace large;
   if (mma_bf16) return launch_large_step_bf(a, io_bf16, st);
-  return step_t<float, float>(a, st);
+  return step_t(a, st);
 }
 
 hipError_t launch_large_norm(const LargeNormArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((large::k_norm<float, float>), dim3((a.rows + 3) / 4), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(large::k_norm, dim3((a.rows + 3) / 4), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_large_amu_step(const LargeAmuArgs& a, bool io_bf16, bool mma_bf16, hipStream_t st) {
   using namespace large;
   if (mma_bf16) return launch_large_amu_step_bf(a, io_bf16, st);
-  return amu_step_t<float, float>(a, st);
+  return amu_step_t(a, st);
 }
 
 hipError_t launch_large_cast(const float* src, void* dst, int64_t n, bool mma_bf16, hipStream_t st) {
