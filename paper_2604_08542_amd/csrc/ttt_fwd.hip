@@ -369,7 +369,7 @@ __device__ __forceinline__ void fwd_body_bf(const StepCtx& p) {
     // h = 128, where chains of few tiles a step run: all elements are requested
     // before the first is packed (a step of one tile 11.1 -> 10.4 us; one head,
     // 256 chunks of 1,374 tokens 3.87 -> 3.73 ms).  At h = 256 the compiler's own
-    // order is faster (16 heads, 64 frames: 694 against 711 us).
+    // order is faster (16 heads, 64 frames: 639 against 646 us).
     float r1[32], r2[32], ry[2][32];
 #pragma unroll
     for (int k = 0; k < 32; ++k) {
