@@ -691,6 +691,7 @@ ttt_status_t run_backward(const ttt_problem_t* p, const Shape& S, int B, const i
       bs.prep = prep; bs.H = (int32_t)H; bs.flags = p->flags; bs.eta = p->eta; bs.G = (int32_t)G;
       bs.partial = partial; bs.partial_deta = pdeta; bs.n_active = na;
       BwdReduceArgs rd{};
+      rd.shards_first = S.mma_bf16 ? 0 : 1;
       rd.partial = partial; rd.partial_deta = pdeta; rd.n_active = na; rd.G = (int32_t)G;
       rd.H = (int32_t)H; rd.h = S.h;
       rd.wh_src_base = r == 0 ? nullptr : adj[(r + 1) % 2];
@@ -836,6 +837,7 @@ ttt_status_t run_gcs_backward(const ttt_problem_t* p, const Shape& S, const void
   auto reduce_args = [&](const float* src, float* dst, bool final, int first, int64_t G) {
     BwdReduceArgs r{};
     r.wh_src_base = src; r.wh_dst_base = dst; r.dst1 = dW1_0; r.dst2 = dW2_0; r.deta_base = deta;
+    r.shards_first = S.mma_bf16 ? 0 : 1;
     r.partial = partial; r.partial_deta = pdeta; r.n_active = 1; r.G = (int32_t)G; r.H = (int32_t)H; r.h = S.h;
     r.seq[0] = 0; r.flags[0] = (final ? 1 : 0) | (first ? 2 : 0); r.next_slot[0] = -1;
     return r;

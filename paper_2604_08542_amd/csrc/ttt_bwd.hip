@@ -33,8 +33,9 @@
 // spilled 70 registers, because the compiler kept the terms of the d(eta) sum
 // and the factors of dZ across barriers; formed where they are written (the
 // empty asm statements), with the tile of dK on that of dE, two work-groups fit
-// a CU and nothing spills: per step of 32 heads x 2,999 tokens at h = 128 336 ->
-// 265 us, 16 heads x 5,000 tokens at h = 256 466 -> 371 us.
+// a CU at h = 128 (5 registers spill) and nothing spills at h = 256: per step of
+// 32 heads x 2,999 tokens at h = 128 336 -> 265 us, 16 heads x 5,000 tokens at h =
+// 256 466 -> 371 us.
 #include <hip/hip_runtime.h>
 
 #include "ttt_common.h"
@@ -499,7 +500,15 @@ __global__ __launch_bounds__(256) void ttt_bwd_reduce(BwdReduceArgs p) {
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
     if (p.wh_src_base) s = *reinterpret_cast<const f32x4*>(p.wh_src_base + cw + idx);
     const f32x4* part = reinterpret_cast<const f32x4*>(p.partial + (int64_t)chain * p.G * 2 * dh) + i4;
-    s = add_shards(s, part, n4, p.G);
+    // FP32 operands: the carried adjoint last, so that it takes one rounding and
+    // not one per shard.  (Fewer shards with more tiles each had made dW 1.7% less
+    // exact, 16 heads, three sequences, chunks of 2,999 tokens; so it is 8% more.)
+    // BF16 operands keep the order: the rounding of later chunks' operands would
+    // enlarge the change.
+    if (p.shards_first)
+      s += add_shards2(part, n4, p.G);
+    else
+      s = add_shards(s, part, n4, p.G);
     if (final && !p.fin_base) {
       const int64_t fo = ((int64_t)(p.dst_per_seq ? b : 0) * p.H + head) * dh;
       if (idx < dh)
@@ -521,9 +530,9 @@ __global__ __launch_bounds__(256) void ttt_bwd_reduce(BwdReduceArgs p) {
   }
   if (k == 0 && threadIdx.x == 0) {
     float* dt = p.deta_base + (int64_t)b * p.H + head;
-    float sd = first ? 0.f : *dt;
-    for (int gg = 0; gg < p.G; ++gg) sd += p.partial_deta[(int64_t)chain * p.G + gg];
-    *dt = sd;
+    float sd = first ? 0.f : *dt, sum = p.shards_first ? 0.f : sd;
+    for (int gg = 0; gg < p.G; ++gg) sum += p.partial_deta[(int64_t)chain * p.G + gg];
+    *dt = p.shards_first ? sd + sum : sum;
   }
 }
 

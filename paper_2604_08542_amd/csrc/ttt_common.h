@@ -74,6 +74,26 @@ __device__ __forceinline__ f32x4 add_shards(f32x4 s, const f32x4* part, int64_t 
   return s;
 }
 
+// The sum of the shards in two streams (even and odd shards).
+__device__ __forceinline__ f32x4 add_shards2(const f32x4* part, int64_t stride, int G) {
+  f32x4 s[2] = {};
+  int gg = 0;
+  for (; gg + 8 <= G; gg += 8) {
+    f32x4 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = part[(int64_t)(gg + q) * stride];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s[q & 1] += v[q];
+  }
+  for (; gg + 2 <= G; gg += 2) {
+    const f32x4 a = part[(int64_t)gg * stride], b = part[(int64_t)(gg + 1) * stride];
+    s[0] += a;
+    s[1] += b;
+  }
+  if (gg < G) s[0] += part[(int64_t)gg * stride];
+  return s[0] + s[1];
+}
+
 // ----------------------------------------------------------------- SiLU family
 // sigma(z) from one exp2 and one reciprocal (both hardware transcendentals).
 __device__ __forceinline__ float sigmoid(float z) {
@@ -382,6 +402,7 @@ struct BwdReduceArgs {
   float* deta_base;          // deta of sequence b at deta_base + b*H
   const float* partial;
   const float* partial_deta;
+  int32_t shards_first;      // sum the shards, then add the carried adjoint (else one shard after another to it)
   int32_t n_active, G, H, h;
   int32_t seq[MAXS];
   int32_t flags[MAXS];       // bit 0: final step of this sequence; bit 1: first step (deta starts at 0)
