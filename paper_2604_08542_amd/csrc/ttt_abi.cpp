@@ -280,7 +280,8 @@ WsLayout ws_layout(const Shape& s, int64_t n_chains) {
   L.wlast = off;
   off = align_up(off + (size_t)n_chains * wbytes);
   L.prep = off;
-  off = align_up(off + (size_t)std::min<int64_t>(n_chains, (int64_t)MAXS * s.H) * s.dh() * (s.mma_bf16 ? 4 * 2 : 8 * 4));
+  const size_t copies = s.mma_bf16 ? 4 * 2 : 8 * 4;  // bytes per weight element
+  off = align_up(off + (size_t)std::min<int64_t>(n_chains, (int64_t)MAXS * s.H) * s.dh() * copies);
   L.fin = off;
   off = align_up(off + (size_t)n_chains * wbytes);
   L.deta_seq = off;
@@ -2141,7 +2142,8 @@ static ttt_status_t gcm_bwd_layout(const ttt_problem_t* p, GcmBwdLayout* L) {
     off = align_up(off + bytes);
     return o;
   };
-  const size_t row3 = (size_t)N * 3 * D * io, row1 = (size_t)N * D * io, slab_part = (size_t)((N + 255) / 256) * 3 * D * 4;
+  const size_t row3 = (size_t)N * 3 * D * io, row1 = (size_t)N * D * io;
+  const size_t slab_part = (size_t)((N + 255) / 256) * 3 * D * 4;
   size_t part = slab_part, extra = 0;
   L->runs_o = L->runs_p = 1;
   if (S.io_bf16) {

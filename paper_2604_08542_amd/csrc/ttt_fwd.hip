@@ -1160,8 +1160,10 @@ hipError_t launch_fwd_step(const FwdStepArgs& a, int n_blocks, int h, bool io_bf
     const bool one = n_blocks <= 256;
     if (io_bf16) return launch_fwd_step_t<bf16, true, 4, 2>(a, n_blocks, st);
     if (mma_bf16)
-      return one ? launch_fwd_step_t<float, true, 4, 1>(a, n_blocks, st) : launch_fwd_step_t<float, true, 4, 2>(a, n_blocks, st);
-    return one ? launch_fwd_step_t<float, false, 4, 1>(a, n_blocks, st) : launch_fwd_step_t<float, false, 4, 2>(a, n_blocks, st);
+      return one ? launch_fwd_step_t<float, true, 4, 1>(a, n_blocks, st)
+                 : launch_fwd_step_t<float, true, 4, 2>(a, n_blocks, st);
+    return one ? launch_fwd_step_t<float, false, 4, 1>(a, n_blocks, st)
+               : launch_fwd_step_t<float, false, 4, 2>(a, n_blocks, st);
   }
   if (io_bf16) return launch_fwd_step_t<bf16, true, 8, 1>(a, n_blocks, st);
   return mma_bf16 ? launch_fwd_step_t<float, true, 8, 1>(a, n_blocks, st)
